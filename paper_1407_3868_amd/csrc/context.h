@@ -234,11 +234,6 @@ int star_smatrix_checked(double a1, double a2, int a3, double k2, mpsl_c128 kp, 
 // when nothing comes up from below.  Amplitudes are divided by gamma of their
 // layer, as in the spectral representation of Section 5.2.
 void stack_node(const mpsl_ctx *ctx, zc lam, zc &Rup, zc &Rdn, zc &T);
-// Per-layer plane-wave amplitudes for field evaluation: A[j] the downgoing
-// wave at the top interface of layer j, B[j] the upgoing one at its bottom
-// (A[0] = B[L-1] = 0), g[j] gamma of layer j, from the particle-layer
-// densities sp, sm, the particle spectra Pp, Pm and the source amplitude gs.
-void stack_amplitudes(const mpsl_ctx *ctx, zc lam, zc gs, zc sp, zc sm, zc Pp, zc Pm, zc *A, zc *B, zc *g);
 // The 2 x 2 map (P+, P-) -> (sigma+, sigma-) row-major in m[0..3] and the
 // source factors in m[4..5] (sigma+/- per unit source amplitude).
 void layer_map(const mpsl_ctx *ctx, zc lam, zc m[6]);

@@ -90,11 +90,20 @@ int launch_to_fp64(mpsl_ctx *ctx, const void *x32, void *x64, int64_t len);
 // Deterministic pseudo-random complex vector (n_complex entries) in precision prec.
 int launch_fill_hash(mpsl_ctx *ctx, int prec, void *v, int64_t n_complex, uint32_t seed);
 
-// Row a7: field at receivers.  gl: double2[L][ns] gamma per layer; amp:
-// double2[L][2][ns] downgoing amplitude at the top and upgoing at the bottom
-// of each layer; yint: double[L-1] interface heights (all device).
-int launch_field(mpsl_ctx *ctx, const void *beta, const void *gl, const void *amp, const void *yint,
-                 const double *src, int64_t nr, const void *rcv, void *u);
+// Row a7: total field of one source at receivers (field.hip), from the
+// spectra and densities of the coefficients (double2[2][ns] each).
+struct FieldShape {
+  int pchunks, nchunks;  // chunks of the particles and of the contour nodes
+  int64_t batch;         // receivers per launch
+};
+FieldShape field_shape(const mpsl_ctx *ctx, int64_t nr, bool small);
+// Bytes of the scratch that launch_field needs.
+size_t field_scratch_bytes(const mpsl_ctx *ctx, const FieldShape &s);
+// Layer data that launch_field uploads; the caller keeps it until the stream is done.
+std::vector<double> field_stack(const mpsl_ctx *ctx);
+int launch_field(mpsl_ctx *ctx, const FieldShape &s, const std::vector<double> &layers, const void *beta,
+                 const void *spec, const void *sigma, const double *src, int64_t nr, const void *rcv, void *u,
+                 void *scratch);
 
 // Source chunks of the M2L grid for precision prec (tuned, set, or automatic).
 int chunks_m2l(const mpsl_ctx *ctx, int prec);

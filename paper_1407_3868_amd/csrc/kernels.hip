@@ -1283,72 +1283,6 @@ __global__ void k_to64(const float2 *__restrict__ a, double2 *__restrict__ b, in
 }
 
 // ---------------------------------------------------------------------------
-// Row a7: total field at receivers (eq. (36)), FP64.
-__global__ void k_field(const double2 *__restrict__ xy, const double2 *__restrict__ beta, int n, int p,
-                        const double2 *__restrict__ lam, const double2 *__restrict__ w,
-                        const double2 *__restrict__ gl, const double2 *__restrict__ amp,
-                        const double *__restrict__ yint, int L, int c, int ns, double k0, double kc, double r_enc,
-                        const int32_t *__restrict__ types, const double *__restrict__ rtype, double xs, double ys,
-                        const double2 *__restrict__ rcv, int64_t nr, double2 *__restrict__ u) {
-  const int64_t r = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (r >= nr) return;
-  const double X = rcv[r].x, Y = rcv[r].y;
-  // layer of the receiver: interfaces above it; the particle layer keeps y = 0
-  int layer = 0;
-  for (int i = 0; i < L - 1; ++i) layer += (Y < yint[i]) ? 1 : 0;
-  if (Y == yint[c - 1]) layer = c;
-  const bool hasA = layer > 0, hasB = layer < L - 1;
-  const double ta = hasA ? Y - yint[layer - 1] : 0.0;  // <= 0
-  const double tb = hasB ? Y - yint[layer] : 0.0;      // >= 0
-  const double2 *g = gl + static_cast<int64_t>(layer) * ns;
-  const double2 *A = amp + static_cast<int64_t>(2 * layer) * ns;
-  const double2 *B = A + ns;
-  cx<double> acc = mk(0.0, 0.0);
-  for (int q = 0; q < ns; ++q) {
-    const double lr = lam[q].x, li = lam[q].y;
-    const cx<double> gq = ld<double>(g[q]);
-    cx<double> s = mk(0.0, 0.0);
-    if (hasA) s = s + ld<double>(A[q]) * cexp_d(-li * X + gq.re * ta, lr * X + gq.im * ta);
-    if (hasB) s = s + ld<double>(B[q]) * cexp_d(-li * X - gq.re * tb, lr * X - gq.im * tb);
-    const double nn = gq.re * gq.re + gq.im * gq.im;
-    acc = acc + (1.0 / nn) * (ld<double>(w[q]) * mk(gq.re, -gq.im) * s);
-  }
-  acc = (1.0 / (4.0 * M_PI)) * acc;
-  bool inside = false;
-  if (layer == 0) {
-    const double dx = X - xs, dy = Y - ys;
-    const double z = k0 * sqrt(dx * dx + dy * dy);
-    acc = acc + mk(0.0, 0.25) * mk(j0(z), y0(z));
-  } else if (layer == c) {
-    const int P = 2 * p + 1;
-    for (int m = 0; m < n; ++m) {
-      const double dx = X - xy[m].x, dy = Y - xy[m].y;
-      const double rr = sqrt(dx * dx + dy * dy);
-      if (rr < (types ? rtype[types[m]] : r_enc)) inside = true;
-      const double z = kc * rr;
-      const cx<double> t = mk(dx / rr, dy / rr);
-      const double2 *b = beta + static_cast<int64_t>(m) * P;
-      cx<double> hprev = mk(j0(z), y0(z));
-      cx<double> hcur = mk(j1(z), y1(z));
-      acc = acc + hprev * ld<double>(b[p]);
-      cx<double> tq = t;
-      for (int q = 1; q <= p; ++q) {
-        if (q >= 2) {
-          const cx<double> hn = (2.0 * (q - 1) / z) * hcur - hprev;
-          hprev = hcur;
-          hcur = hn;
-          tq = tq * t;
-        }
-        const double sg = (q & 1) ? -1.0 : 1.0;
-        acc = acc + hcur * (tq * ld<double>(b[p + q]) + sg * (conj(tq) * ld<double>(b[p - q])));
-      }
-    }
-  }
-  if (inside) acc = mk<double>(NAN, NAN);
-  u[r] = st(acc);
-}
-
-// ---------------------------------------------------------------------------
 // Dispatch over the expansion order.
 #define MPSL_P_CASES(X) \
   X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16) X(17) \
@@ -1897,23 +1831,6 @@ int launch_fill_hash(mpsl_ctx *ctx, int prec, void *v, int64_t n_complex, uint32
 int launch_to_fp64(mpsl_ctx *ctx, const void *x32, void *x64, int64_t len) {
   hipLaunchKernelGGL(k_to64, dim3(cdiv(len, 256)), dim3(256), 0, ctx->stream, static_cast<const float2 *>(x32),
                      static_cast<double2 *>(x64), len);
-  LAUNCH_CHECK(ctx);
-  return MPSL_OK;
-}
-
-int launch_field(mpsl_ctx *ctx, const void *beta, const void *gl, const void *amp, const void *yint,
-                 const double *src, int64_t nr, const void *rcv, void *u) {
-  hipLaunchKernelGGL(k_field, dim3(cdiv(nr, 64)), dim3(64), 0, ctx->stream,
-                     static_cast<const double2 *>(ctx->gt.xy.p), static_cast<const double2 *>(beta),
-                     static_cast<int>(ctx->n), ctx->p, static_cast<const double2 *>(ctx->ct.lam.p),
-                     static_cast<const double2 *>(ctx->ct.gw.p) + 3 * ctx->ns,  // weights stored after g1,g2,g3
-                     static_cast<const double2 *>(gl), static_cast<const double2 *>(amp),
-                     static_cast<const double *>(yint), static_cast<int>(ctx->ks.size()), ctx->layer_c, ctx->ns,
-                     ctx->k1.real(), ctx->k2.real(), ctx->r_enc,
-                     (ctx->n_types > 1 && !ctx->ptype.empty()) ? static_cast<const int32_t *>(ctx->types_dev.p)
-                                                                : nullptr,
-                     static_cast<const double *>(ctx->rtype_dev.p), src[0], src[1],
-                     static_cast<const double2 *>(rcv), nr, static_cast<double2 *>(u));
   LAUNCH_CHECK(ctx);
   return MPSL_OK;
 }

@@ -138,37 +138,4 @@ int assign_stack(mpsl_ctx *ctx, int n_layers, const mpsl_c128 *k, const double *
   return MPSL_OK;
 }
 
-void stack_amplitudes(const mpsl_ctx *ctx, zc lam, zc gs, zc sp, zc sm, zc Pp, zc Pm, zc *A, zc *B, zc *g) {
-  StackWork w;
-  stack_recursion(ctx, lam, w);
-  const int L = static_cast<int>(ctx->ks.size()), c = ctx->layer_c;
-  for (int j = 0; j < L; ++j) {
-    g[j] = w.g[j];
-    A[j] = B[j] = zc(0.0, 0.0);
-  }
-  A[c] = sp;
-  B[c] = sm;
-  // upwards: (up a, down b) at the top interface of layer j + 1
-  zc a = w.e[c] * sm + Pp, b = sp;
-  for (int j = c - 1; j >= 1; --j) {
-    // u and du/dy continuous across interface j give the upgoing wave at the
-    // bottom of layer j; its downgoing wave follows from the layers above
-    const zc s = w.g[j] / w.g[j + 1] * (a + b), dl = (w.kap[j + 1] / w.kap[j]) * (b - a);
-    B[j] = 0.5 * (s - dl);
-    a = B[j] * w.e[j];
-    b = w.ru[j] * a + w.tau[j] * gs;
-    A[j] = b;
-  }
-  B[0] = w.g[0] / w.g[1] * (a + b) - gs;
-  // downwards: (down dn, up up) at the bottom interface of layer j - 1
-  zc dn = w.e[c] * sp + Pm, up = sm;
-  for (int j = c + 1; j <= L - 2; ++j) {
-    A[j] = 0.5 * (w.g[j] / w.g[j - 1] * (dn + up) + (w.kap[j - 1] / w.kap[j]) * (dn - up));
-    dn = A[j] * w.e[j];
-    up = w.rd[j] * dn;
-    B[j] = up;
-  }
-  A[L - 1] = w.g[L - 1] / w.g[L - 2] * (dn + up);
-}
-
 }  // namespace mpsl

@@ -423,48 +423,25 @@ namespace {
 int eval_field_one(mpsl_ctx *ctx, const double *src, const mpsl_c128 *beta, int64_t n_rcv, const double *rcv,
                    mpsl_c128 *u_out) {
   int rc = MPSL_OK;
-  const int ns = ctx->ns;
   const int64_t len = ctx->n * static_cast<int64_t>(2 * ctx->p + 1);
   if ((rc = mpsl::dev_alloc(ctx, ctx->xbuf, len * sizeof(double2)))) return rc;
   MPSL_HIP_TRY(ctx, hipMemcpyAsync(ctx->xbuf.p, beta, len * sizeof(double2), hipMemcpyHostToDevice, ctx->stream));
   if ((rc = mpsl::launch_m2s(ctx, MPSL_FP64, ctx->xbuf.p, ctx->spec.p))) return rc;
   if ((rc = mpsl::launch_reflect(ctx, ctx->spec.p, src, ctx->sigma.p))) return rc;
-  std::vector<zc> spec(2 * ns), sig(2 * ns);
-  MPSL_HIP_TRY(ctx, hipMemcpyAsync(spec.data(), ctx->spec.p, 2 * ns * sizeof(double2), hipMemcpyDeviceToHost, ctx->stream));
-  MPSL_HIP_TRY(ctx, hipMemcpyAsync(sig.data(), ctx->sigma.p, 2 * ns * sizeof(double2), hipMemcpyDeviceToHost, ctx->stream));
-  MPSL_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-  // amplitudes of every layer from the interface conditions, outward from the
-  // particle layer (source amplitude referenced to the top interface)
-  const int L = static_cast<int>(ctx->ks.size());
-  std::vector<zc> gl(static_cast<size_t>(L) * ns), amp(static_cast<size_t>(2 * L) * ns);
-  std::vector<zc> A(L), B(L), g(L);
-  const zc I(0.0, 1.0);
-  for (int q = 0; q < ns; ++q) {
-    const zc lam = ctx->lam[q];
-    const zc g0 = mpsl::gamma_branch(lam, ctx->k1);
-    const zc gs = std::exp(-I * lam * src[0] - g0 * (src[1] - ctx->yint[0]));
-    mpsl::stack_amplitudes(ctx, lam, gs, sig[q], sig[ns + q], spec[q], spec[ns + q], A.data(), B.data(), g.data());
-    for (int j = 0; j < L; ++j) {
-      gl[static_cast<size_t>(j) * ns + q] = g[j];
-      amp[static_cast<size_t>(2 * j) * ns + q] = A[j];
-      amp[static_cast<size_t>(2 * j + 1) * ns + q] = B[j];
-    }
-  }
   const size_t rb = static_cast<size_t>(n_rcv) * sizeof(double2);
-  const size_t gb = gl.size() * sizeof(double2), ab = amp.size() * sizeof(double2);
-  if ((rc = mpsl::dev_alloc(ctx, ctx->ybuf, 2 * rb + gb + ab + (L - 1) * sizeof(double)))) return rc;
-  char *base = static_cast<char *>(ctx->ybuf.p);
-  void *d_rcv = base;
-  void *d_u = base + rb;
-  void *d_gl = base + 2 * rb;
-  void *d_amp = base + 2 * rb + gb;
-  void *d_yint = base + 2 * rb + gb + ab;
+  mpsl::FieldShape shape = mpsl::field_shape(ctx, n_rcv, false);
+  rc = mpsl::dev_alloc(ctx, ctx->ybuf, 2 * rb + mpsl::field_scratch_bytes(ctx, shape));
+  if (rc == MPSL_ENOMEM) {
+    shape = mpsl::field_shape(ctx, n_rcv, true);
+    rc = mpsl::dev_alloc(ctx, ctx->ybuf, 2 * rb + mpsl::field_scratch_bytes(ctx, shape));
+  }
+  if (rc) return rc;
+  const std::vector<double> layers = mpsl::field_stack(ctx);
+  char *d_rcv = static_cast<char *>(ctx->ybuf.p), *d_u = d_rcv + rb;
   MPSL_HIP_TRY(ctx, hipMemcpyAsync(d_rcv, rcv, rb, hipMemcpyHostToDevice, ctx->stream));
-  MPSL_HIP_TRY(ctx, hipMemcpyAsync(d_gl, gl.data(), gb, hipMemcpyHostToDevice, ctx->stream));
-  MPSL_HIP_TRY(ctx, hipMemcpyAsync(d_amp, amp.data(), ab, hipMemcpyHostToDevice, ctx->stream));
-  MPSL_HIP_TRY(ctx, hipMemcpyAsync(d_yint, ctx->yint.data(), (L - 1) * sizeof(double), hipMemcpyHostToDevice,
-                                   ctx->stream));
-  if ((rc = mpsl::launch_field(ctx, ctx->xbuf.p, d_gl, d_amp, d_yint, src, n_rcv, d_rcv, d_u))) return rc;
+  if ((rc = mpsl::launch_field(ctx, shape, layers, ctx->xbuf.p, ctx->spec.p, ctx->sigma.p, src, n_rcv, d_rcv, d_u,
+                               d_u + rb)))
+    return rc;
   MPSL_HIP_TRY(ctx, hipMemcpyAsync(u_out, d_u, rb, hipMemcpyDeviceToHost, ctx->stream));
   MPSL_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
   for (int64_t i = 0; i < n_rcv; ++i)

@@ -36,55 +36,6 @@ constexpr double kTileW = 8.0, kTileH = 4.0, kIntervalL = 1.0, kDirect = 0.3;
 #define SOMM_P_CASES(X) \
   X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16) X(17) X(18) X(19) X(20)
 
-// sin and cos of r, |r| <= pi / 4, by their Taylor series (terms up to r^9
-// and r^10 in FP32, r^17 and r^18 in FP64: the first term left out is below
-// 2e-10 and 1e-19 there).
-__device__ inline void sincos_quarter(float r, float &s, float &c) {
-  const float r2 = r * r;
-  s = r * (1.0f + r2 * (-1.0f / 6 + r2 * (1.0f / 120 + r2 * (-1.0f / 5040 + r2 * (1.0f / 362880)))));
-  c = 1.0f + r2 * (-0.5f + r2 * (1.0f / 24 + r2 * (-1.0f / 720 + r2 * (1.0f / 40320 + r2 * (-1.0f / 3628800)))));
-}
-__device__ inline void sincos_quarter(double r, double &s, double &c) {
-  const double r2 = r * r;
-  double ps = 1.0 / 355687428096000.0, pc = 1.0 / 6402373705728000.0;  // 1/17!, 1/18!
-  ps = 1.0 / 1307674368000.0 - r2 * ps;   // 1/15!
-  ps = 1.0 / 6227020800.0 - r2 * ps;      // 1/13!
-  ps = 1.0 / 39916800.0 - r2 * ps;        // 1/11!
-  ps = 1.0 / 362880.0 - r2 * ps;          // 1/9!
-  ps = 1.0 / 5040.0 - r2 * ps;
-  ps = 1.0 / 120.0 - r2 * ps;
-  ps = 1.0 / 6.0 - r2 * ps;
-  s = r * (1.0 - r2 * ps);
-  pc = 1.0 / 20922789888000.0 - r2 * pc;  // 1/16!
-  pc = 1.0 / 87178291200.0 - r2 * pc;     // 1/14!
-  pc = 1.0 / 479001600.0 - r2 * pc;       // 1/12!
-  pc = 1.0 / 3628800.0 - r2 * pc;         // 1/10!
-  pc = 1.0 / 40320.0 - r2 * pc;
-  pc = 1.0 / 720.0 - r2 * pc;
-  pc = 1.0 / 24.0 - r2 * pc;
-  pc = 0.5 - r2 * pc;
-  c = 1.0 - r2 * pc;
-}
-
-// e^{a + i b} in the matvec precision.  The phase b (up to |lambda| times the
-// strip width) is reduced in FP64 to r = b - k pi/2, |r| <= pi/4, with a
-// two-term pi/2 (Cody and Waite); sin and cos of r come from the series
-// above in T and are rotated by k quarter turns; exp(a) in T.  In FP32 the
-// relative error is ~2e-7 (the result is rounded to FP32 anyway); in FP64 a
-// few units in the last place.  No large-argument path: every lane runs the
-// same instructions.
-template <typename T> __device__ inline cx<T> cexpT(double a, double b) {
-  constexpr double kHalfPiHi = 1.5707963267948966, kHalfPiLo = 6.123233995736766e-17;
-  const double k = rint(b * 0.6366197723675814);
-  const double r = fma(-k, kHalfPiLo, fma(-k, kHalfPiHi, b));
-  T sr, cr;
-  sincos_quarter(static_cast<T>(r), sr, cr);
-  const int qd = static_cast<int>(static_cast<long long>(k) & 3);
-  const T sn = qd == 0 ? sr : qd == 1 ? cr : qd == 2 ? -sr : -cr;
-  const T cs = qd == 0 ? cr : qd == 1 ? -sr : qd == 2 ? -cr : sr;
-  const T e = exp(static_cast<T>(a));
-  return {e * cs, e * sn};
-}
 __device__ inline cx<double> cexp64(double a, double b) { return cexpT<double>(a, b); }
 template <typename T> __device__ inline cx<T> cvt(cx<double> v) { return {static_cast<T>(v.re), static_cast<T>(v.im)}; }
 template <typename T> __device__ inline cx<double> up(cx<T> v) { return {static_cast<double>(v.re), static_cast<double>(v.im)}; }
