@@ -507,9 +507,7 @@ int matvec(mpsl_ctx *ctx, int prec, const void *x, void *y, int nrhs) {
     return rc;
   char *part = static_cast<char *>(ctx->part.p);
   char *part_b = part + static_cast<size_t>(ca) * len * esz;
-  if ((rc = launch_m2s(ctx, prec, x, ctx->spec.p, nrhs))) return rc;
-  if ((rc = launch_reflect(ctx, ctx->spec.p, nullptr, ctx->sigma.p, nrhs))) return rc;
-  if ((rc = launch_s2l_coef(ctx, ctx->sigma.p, nrhs))) return rc;
+  if ((rc = launch_m2s_coef(ctx, prec, x, nrhs))) return rc;
   if ((rc = launch_s2l(ctx, prec, part_b, cb, nrhs, pstride))) return rc;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   if (ctx->prof) {
@@ -532,8 +530,7 @@ int matvec(mpsl_ctx *ctx, int prec, const void *x, void *y, int nrhs) {
     ctx->ev_start.push_back(e0);
     ctx->ev_stop.push_back(e1);
   }
-  if ((rc = launch_fold_parts(ctx, prec, part, ca + cb, nrhs, pstride))) return rc;
-  return launch_sapply(ctx, prec, x, part, y, nrhs, pstride);
+  return launch_sapply(ctx, prec, x, part, ca + cb, y, nrhs, pstride);
 }
 
 int matvec(mpsl_ctx *ctx, int prec, const void *x, void *y) { return matvec(ctx, prec, x, y, 1); }
@@ -1106,7 +1103,7 @@ int mpsl_sapply_dev(mpsl_ctx *ctx, int prec, const void *x, const void *alpha, v
   MPSL_HIP_TRY(ctx, hipSetDevice(ctx->device));
   int rc = mpsl::build_tables(ctx);
   if (rc) return rc;
-  return mpsl::launch_sapply(ctx, prec, x, alpha, y);
+  return mpsl::launch_sapply(ctx, prec, x, const_cast<void *>(alpha), 1, y);
 }
 
 int mpsl_profile(mpsl_ctx *ctx, int enable) {
@@ -1187,7 +1184,7 @@ int mpsl_autotune(mpsl_ctx *ctx, int prec) {
       // timed with the fold of its c partial slots, which grows with c
       auto run = [&]() {
         int e = mpsl::launch_m2l(ctx, prec, ctx->xbuf.p, ctx->part.p, c, variant);
-        return e ? e : mpsl::launch_fold_parts(ctx, prec, ctx->part.p, c);
+        return e ? e : mpsl::launch_sum_parts(ctx, prec, ctx->part.p, c, ctx->part.p);
       };
       if ((rc = run())) break;  // warm-up
       if (hipEventRecord(e0, ctx->stream) != hipSuccess) { rc = MPSL_EHIP; break; }

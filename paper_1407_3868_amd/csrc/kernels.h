@@ -46,6 +46,9 @@ int launch_fmm_near(mpsl_ctx *ctx, int prec, const void *beta, void *out);
 // Row b1: M2S partial spectra and their reduction to spec (double2[2*ns]).
 // spec: double2[nrhs][2][ns].
 int launch_m2s(mpsl_ctx *ctx, int prec, const void *beta, void *spec, int nrhs = 1);
+// Rows b1 and b2 of the matvec: M2S, reflection and the S2L coefficients in
+// precision prec (the interpolated transforms keep the densities instead).
+int launch_m2s_coef(mpsl_ctx *ctx, int prec, const void *beta, int nrhs = 1);
 // Row b2: sigma = R spec (+ source), and the scaled S2L coefficient tables.
 // spec, sigma: double2[nrhs][2][ns] (spec may be null; src the same for every rhs).
 int launch_reflect(mpsl_ctx *ctx, const void *spec, const double *src, void *sigma, int nrhs = 1);
@@ -53,14 +56,12 @@ int launch_reflect(mpsl_ctx *ctx, const void *spec, const double *src, void *sig
 int launch_s2l_coef(mpsl_ctx *ctx, const void *sigma, int nrhs = 1);
 // Row b3: partial local expansions of the layer field into part[0 .. chunks).
 int launch_s2l(mpsl_ctx *ctx, int prec, void *part, int chunks, int nrhs = 1, int64_t pstride = 0);
-// Sum of partial buffers: alpha = sum_{c < chunks} part[c].
+// Sum of partial buffers: alpha = sum_{c < chunks} part[c] (alpha may be part).
 int launch_sum_parts(mpsl_ctx *ctx, int prec, const void *part, int chunks, void *alpha);
-// Partial buffers of each right-hand side summed in place into slot 0
-// (part + r * pstride holds chunks slots of n P entries).
-int launch_fold_parts(mpsl_ctx *ctx, int prec, void *part, int chunks, int nrhs = 1, int64_t pstride = 0);
-// Row a2 (MFMA): y = x - S_rot alpha  (x may be null: y = S_rot alpha);
-// alpha of right-hand side r at alpha + r * astride.
-int launch_sapply(mpsl_ctx *ctx, int prec, const void *x, const void *alpha, void *y, int nrhs = 1,
+// Row a2 (MFMA): y = x - S_rot alpha  (x may be null: y = S_rot alpha); alpha
+// of right-hand side r is the sum of `slots` buffers of n P entries at
+// alpha + r * astride.
+int launch_sapply(mpsl_ctx *ctx, int prec, const void *x, void *alpha, int slots, void *y, int nrhs = 1,
                   int64_t astride = 0);
 
 // GMRES helpers (FP64 complex vectors of length len; the k vectors of V in

@@ -270,19 +270,63 @@ __global__ __launch_bounds__(kThreads) void k_fmm_near(const cv_t<T> *__restrict
 }
 
 
+// M2S partials to spectra, and for the matvec on to the S2L coefficients: per
+// block 16 nodes, both sides, eight lanes per (node, side) taking every eighth
+// particle chunk (FP64 sums, added in order).  With spec the sums are stored
+// there; without, the block applies the reflection map (row b2) and writes
+// Up[s][q][n] = c_q sigma_s U[s][q][n] in the matvec's precision: one launch
+// for what were three, each a few microseconds of latency (5000 particles,
+// 1024 nodes, FP32: 15.4 + 4.6 + 4.7 us; 20000: 28.3 us for the sums alone,
+// whose lanes walked up to 109 chunks in series).
+constexpr int kNodeBlock = 16, kNodeLanes = 8;
 template <typename T>
-__global__ void k_m2s_reduce(const cv_t<T> *__restrict__ part, int ns, int chunks, int nrhs,
-                             double2 *__restrict__ spec) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= 2 * ns * nrhs) return;
-  const int rs = i / ns, q = i % ns;  // rs = 2 * rhs + side
+__global__ __launch_bounds__(2 * kNodeBlock *kNodeLanes) void k_nodes(
+    const cv_t<T> *__restrict__ part, int ns, int chunks, const double2 *__restrict__ R,
+    const double2 *__restrict__ cq, const double2 *__restrict__ U, int P, double2 *__restrict__ spec,
+    cv_t<T> *__restrict__ Up) {
+  __shared__ double2 sum[kNodeLanes][2][kNodeBlock];
+  __shared__ double2 val[2][kNodeBlock];
+  const int tid = threadIdx.x, qi = tid % kNodeBlock, s = tid / kNodeBlock & 1, cl = tid / (2 * kNodeBlock);
+  const int64_t r = blockIdx.y;
+  const int q0 = blockIdx.x * kNodeBlock, q = q0 + qi;
   double re = 0.0, im = 0.0;
-  for (int c = 0; c < chunks; ++c) {
-    const cv_t<T> v = part[(static_cast<int64_t>(rs) * chunks + c) * ns + q];
-    re += static_cast<double>(v.x);
-    im += static_cast<double>(v.y);
+  if (q < ns) {
+    const cv_t<T> *p = part + (2 * r + s) * chunks * static_cast<int64_t>(ns) + q;
+#pragma unroll 4
+    for (int c = cl; c < chunks; c += kNodeLanes) {
+      const cv_t<T> v = p[static_cast<int64_t>(c) * ns];
+      re += static_cast<double>(v.x);
+      im += static_cast<double>(v.y);
+    }
   }
-  spec[i] = make_double2(re, im);
+  sum[cl][s][qi] = make_double2(re, im);
+  __syncthreads();
+  if (cl == 0) {
+    cx<double> v = mk(0.0, 0.0);
+#pragma unroll
+    for (int c = 0; c < kNodeLanes; ++c) v = v + ld<double>(sum[c][s][qi]);
+    if (spec) {
+      if (q < ns) spec[(2 * r + s) * ns + q] = st(v);
+    } else {
+      sum[0][s][qi] = st(v);
+    }
+  }
+  if (spec) return;  // uniform over the grid
+  __syncthreads();
+  if (cl == 0) {
+    const int qc = min(q, ns - 1);
+    const cx<double> sg = ld<double>(R[4 * qc + 2 * s]) * ld<double>(sum[0][0][qi]) +
+                          ld<double>(R[4 * qc + 2 * s + 1]) * ld<double>(sum[0][1][qi]);
+    val[s][qi] = st(ld<double>(cq[qc]) * sg);
+  }
+  __syncthreads();
+  const int cnt = min(kNodeBlock, ns - q0) * P;
+  for (int i = tid; i < 2 * cnt; i += 2 * kNodeBlock * kNodeLanes) {
+    const int side = i >= cnt ? 1 : 0, e = i - side * cnt;
+    const int64_t base = static_cast<int64_t>(side) * ns * P + static_cast<int64_t>(q0) * P + e;
+    const cx<double> v = ld<double>(val[side][e / P]) * ld<double>(U[base]);
+    Up[2 * r * ns * P + base] = st(mk(static_cast<T>(v.re), static_cast<T>(v.im)));
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -330,70 +374,71 @@ __global__ void k_s2l_coef(const double2 *__restrict__ sigma, const double2 *__r
 
 
 // ---------------------------------------------------------------------------
+// Sum of the partial slots of one entry by four neighbouring lanes: lane g
+// takes the slots g, g + 4, ..., eight loads in flight, and the four sums are
+// added by two exchanges (a fixed order; every lane of the four gets the sum).
+// One lane per entry left small problems waiting for their loads in series
+// (1000 particles, p = 12, FP64: 25000 lanes, 384 slots, 35 us).
+constexpr int kSumLanes = 4;
 template <typename T>
-__global__ void k_sum_parts(const cv_t<T> *__restrict__ part, int chunks, int64_t len,
-                            cv_t<T> *__restrict__ out) {
-  const int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (i >= len) return;
-  T re = 0, im = 0;
-  for (int c = 0; c < chunks; ++c) {
-    const cv_t<T> v = part[c * len + i];
-    re += v.x;
-    im += v.y;
-  }
-  cv_t<T> o;
-  o.x = re;
-  o.y = im;
-  out[i] = o;
-}
-
-// In-place sum of the partial buffers of each right-hand side into slot 0:
-// part[r][0][i] = sum_c part[r][c][i]  (one lane per entry, fixed order).
-template <typename T>
-__global__ void k_fold_parts(cv_t<T> *__restrict__ part, int chunks, int64_t len, int64_t pstride) {
-  const int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (i >= len) return;
-  part += blockIdx.y * pstride;
-  // eight independent sums (slot c mod 8), so that eight loads are in flight,
-  // combined pairwise at the end: a fixed order for every launch
-  T re[8] = {0, 0, 0, 0, 0, 0, 0, 0}, im[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  int c = 0;
-  for (; c + 8 <= chunks; c += 8) {
+__device__ __forceinline__ cx<T> sum_slots(const cv_t<T> *part, int slots, int64_t len, int g) {
+  T re[2] = {0, 0}, im[2] = {0, 0};
+  int c = g;
+  for (; c + 7 * kSumLanes < slots; c += 8 * kSumLanes) {
     cv_t<T> v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = part[(c + u) * len + i];
+    for (int u = 0; u < 8; ++u) v[u] = part[(c + u * kSumLanes) * len];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      re[u] += v[u].x;
-      im[u] += v[u].y;
+      re[u & 1] += v[u].x;
+      im[u & 1] += v[u].y;
     }
   }
-  for (int u = 0; c < chunks; ++c, ++u) {
-    const cv_t<T> v = part[c * len + i];
-    re[u] += v.x;
-    im[u] += v.y;
+  cv_t<T> v[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) v[u] = c + u * kSumLanes < slots ? part[(c + u * kSumLanes) * len] : st(mk<T>(0, 0));
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    re[u & 1] += v[u].x;
+    im[u & 1] += v[u].y;
   }
-  cv_t<T> o;
-  o.x = ((re[0] + re[1]) + (re[2] + re[3])) + ((re[4] + re[5]) + (re[6] + re[7]));
-  o.y = ((im[0] + im[1]) + (im[2] + im[3])) + ((im[4] + im[5]) + (im[6] + im[7]));
-  part[i] = o;
+  cx<T> s = mk<T>(re[0] + re[1], im[0] + im[1]);
+#pragma unroll
+  for (int o = 1; o < kSumLanes; o <<= 1) {
+    s.re += __shfl_xor(s.re, o);
+    s.im += __shfl_xor(s.im, o);
+  }
+  return s;
+}
+
+// out[i] = sum_c part[c len + i] (out may be the first slot)
+template <typename T>
+__global__ __launch_bounds__(256) void k_sum_parts(const cv_t<T> *part, int slots, int64_t len,
+                                                   cv_t<T> *out) {
+  const int64_t t = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
+  const int64_t i = t / kSumLanes;
+  if (i >= len) return;
+  const int g = static_cast<int>(t % kSumLanes);
+  const cx<T> s = sum_slots<T>(part + i, slots, len, g);
+  if (g == 0) out[i] = st(s);
 }
 
 // Row a2 on the matrix cores: y^l = x^l - e^{-in psi_l} sum_n' S[n][n'] e^{in' psi_l} alpha^l_{n'},
-// alpha one buffer per right-hand side (partials folded first).  One block
-// per tile of 16 particles: all lanes rotate the tile's expansions (a
-// contiguous range of 16 P entries) into LDS as B[K = n'][N = particle];
-// wave w < MT then
+// alpha the sum of `slots` partial buffers per right-hand side.  One block
+// per tile of 16 particles: all lanes sum the partials of the tile's
+// expansions (a contiguous range of 16 P entries; HBM-bound where the slots
+// are many) and rotate them into LDS as B[K = n'][N = particle]; wave w < MT
+// then
 // multiplies row tile w of the shared S (A[M = n][K = n'], zero-padded to
 // 16 MT x KP) by B with 16x16x4 MFMA, the complex product as four real
 // chains (re += Sr Br - Si Bi, im += Sr Bi + Si Br); the result goes back
 // through LDS for coalesced stores.
 //   (MFMA operand layout: mfma4 in common.h.)
-constexpr int kSapplyThreads = 256;
+constexpr int kSapplyThreads = 512;  // with more than 8 partials to sum; 256 else
 
 template <typename T, int p>
 __global__ __launch_bounds__(kSapplyThreads) void k_sapply(const cv_t<T> *__restrict__ x,
-                                                           const cv_t<T> *__restrict__ alpha,
+                                                           const cv_t<T> *__restrict__ alpha, int slots,
                                                            const cv_t<T> *__restrict__ S,
                                                            const cv_t<T> *__restrict__ rot, int n,
                                                            cv_t<T> *__restrict__ y, int64_t astride,
@@ -401,7 +446,7 @@ __global__ __launch_bounds__(kSapplyThreads) void k_sapply(const cv_t<T> *__rest
   constexpr int P = 2 * p + 1;
   constexpr int MT = (P + 15) / 16;   // row tiles of S
   constexpr int KP = (P + 3) / 4 * 4; // K padded to the MFMA depth
-  static_assert(MT <= kSapplyThreads / 64, "one wave per row tile");
+  static_assert(MT <= 4, "one wave per row tile");
   {  // right-hand side
     const int64_t off = static_cast<int64_t>(blockIdx.y) * n * P;
     if (x) x += off;
@@ -414,7 +459,7 @@ __global__ __launch_bounds__(kSapplyThreads) void k_sapply(const cv_t<T> *__rest
   __shared__ int32_t tt[16];  // particle types of the tile (-1 past the end)
   const int tid = threadIdx.x;
   const int l0 = blockIdx.x * 16;
-  for (int i = tid; i < KP * 16; i += kSapplyThreads) {
+  for (int i = tid; i < KP * 16; i += blockDim.x) {
     Bre[i / 16][i % 16] = 0;
     Bim[i / 16][i % 16] = 0;
   }
@@ -422,10 +467,26 @@ __global__ __launch_bounds__(kSapplyThreads) void k_sapply(const cv_t<T> *__rest
   __syncthreads();
   const int cnt = min(16, n - l0) * P;  // entries of the tile
   const int64_t base = static_cast<int64_t>(l0) * P;
-  for (int i = tid; i < cnt; i += kSapplyThreads) {
-    const cx<T> s = ld<T>(alpha[base + i]) * ld<T>(rot[base + i]);
-    Bre[i % P][i / P] = s.re;
-    Bim[i % P][i / P] = s.im;
+  const int nthr = blockDim.x;
+  const int64_t len = static_cast<int64_t>(n) * P;
+  if (slots <= 8) {  // few slots: one lane per entry
+    for (int i = tid; i < cnt; i += nthr) {
+      cx<T> s = ld<T>(alpha[base + i]);
+#pragma unroll 4
+      for (int c = 1; c < slots; ++c) s = s + ld<T>(alpha[c * len + base + i]);
+      s = s * ld<T>(rot[base + i]);
+      Bre[i % P][i / P] = s.re;
+      Bim[i % P][i / P] = s.im;
+    }
+  } else {
+    for (int t = tid; t < cnt * kSumLanes; t += nthr) {
+      const int i = t / kSumLanes, g = t % kSumLanes;
+      const cx<T> s = sum_slots<T>(alpha + base + i, slots, len, g) * ld<T>(rot[base + i]);
+      if (g == 0) {
+        Bre[i % P][i / P] = s.re;
+        Bim[i % P][i / P] = s.im;
+      }
+    }
   }
   const int w = tid >> 6, lane = tid & 63;
   const int row = w * 16 + (lane & 15);
@@ -442,7 +503,7 @@ __global__ __launch_bounds__(kSapplyThreads) void k_sapply(const cv_t<T> *__rest
     }
     __syncthreads();  // B written (first pass) or the previous S consumed
     const cv_t<T> *St = S + static_cast<int64_t>(t) * P * P;
-    for (int i = tid; i < MT * 16 * KP; i += kSapplyThreads) {
+    for (int i = tid; i < MT * 16 * KP; i += nthr) {
       const int r = i / KP, c = i % KP;
       const cx<T> v = (r < P && c < P) ? ld<T>(St[r * P + c]) : mk<T>(0, 0);
       Sre[r][c] = v.re;
@@ -471,7 +532,7 @@ __global__ __launch_bounds__(kSapplyThreads) void k_sapply(const cv_t<T> *__rest
     }
   }
   __syncthreads();
-  for (int i = tid; i < cnt; i += kSapplyThreads) {
+  for (int i = tid; i < cnt; i += nthr) {
     cx<T> r = conj(ld<T>(rot[base + i])) * Yt[i];
     if (x) r = ld<T>(x[base + i]) - r;
     y[base + i] = st(r);
@@ -1601,7 +1662,7 @@ int launch_fmm_near(mpsl_ctx *ctx, int prec, const void *beta, void *out) {
 }
 
 template <typename T>
-static int launch_m2s_t(mpsl_ctx *ctx, const void *beta, void *spec, int nrhs) {
+static int launch_m2s_t(mpsl_ctx *ctx, const void *beta, int nrhs) {
   const int n = static_cast<int>(ctx->n);
   const int chunks = chunks_m2s(ctx, nrhs, std::is_same<T, double>::value ? MPSL_FP64 : MPSL_FP32);
   const int chunk_len = cdiv(n, chunks);
@@ -1619,16 +1680,44 @@ static int launch_m2s_t(mpsl_ctx *ctx, const void *beta, void *spec, int nrhs) {
     default: return set_err(ctx, MPSL_EUNSUPPORTED, "expansion order outside 1..20");
   }
   LAUNCH_CHECK(ctx);
-  hipLaunchKernelGGL(k_m2s_reduce<T>, dim3(cdiv(2 * ctx->ns * nrhs, 256)), dim3(256), 0, ctx->stream,
-                     static_cast<const cv_t<T> *>(part), ctx->ns, chunks, nrhs, static_cast<double2 *>(spec));
+  return MPSL_OK;
+}
+
+template <typename T>
+static int launch_nodes_t(mpsl_ctx *ctx, void *spec, int nrhs) {
+  const bool f64 = std::is_same<T, double>::value;
+  const int chunks = chunks_m2s(ctx, nrhs, f64 ? MPSL_FP64 : MPSL_FP32);
+  hipLaunchKernelGGL(k_nodes<T>, dim3(cdiv(ctx->ns, kNodeBlock), nrhs), dim3(2 * kNodeBlock * kNodeLanes), 0,
+                     ctx->stream, static_cast<const cv_t<T> *>(ctx->m2s_part.p), ctx->ns, chunks,
+                     static_cast<const double2 *>(ctx->ct.R.p), static_cast<const double2 *>(ctx->ct.cq.p),
+                     static_cast<const double2 *>(ctx->ct.U64.p), 2 * ctx->p + 1, static_cast<double2 *>(spec),
+                     static_cast<cv_t<T> *>(f64 ? ctx->Up64.p : ctx->Up32.p));
   LAUNCH_CHECK(ctx);
   return MPSL_OK;
 }
 
 int launch_m2s(mpsl_ctx *ctx, int prec, const void *beta, void *spec, int nrhs) {
   if (ctx->somm.active) return launch_m2s_interp(ctx, prec, beta, spec, nrhs);
-  return prec == MPSL_FP64 ? launch_m2s_t<double>(ctx, beta, spec, nrhs)
-                           : launch_m2s_t<float>(ctx, beta, spec, nrhs);
+  if (prec == MPSL_FP64) {
+    const int rc = launch_m2s_t<double>(ctx, beta, nrhs);
+    return rc ? rc : launch_nodes_t<double>(ctx, spec, nrhs);
+  }
+  const int rc = launch_m2s_t<float>(ctx, beta, nrhs);
+  return rc ? rc : launch_nodes_t<float>(ctx, spec, nrhs);
+}
+
+int launch_m2s_coef(mpsl_ctx *ctx, int prec, const void *beta, int nrhs) {
+  if (ctx->somm.active) {
+    int rc = launch_m2s_interp(ctx, prec, beta, ctx->spec.p, nrhs);
+    if (!rc) rc = launch_reflect(ctx, ctx->spec.p, nullptr, ctx->sigma.p, nrhs);
+    return rc ? rc : launch_s2l_coef(ctx, ctx->sigma.p, nrhs);
+  }
+  if (prec == MPSL_FP64) {
+    const int rc = launch_m2s_t<double>(ctx, beta, nrhs);
+    return rc ? rc : launch_nodes_t<double>(ctx, nullptr, nrhs);
+  }
+  const int rc = launch_m2s_t<float>(ctx, beta, nrhs);
+  return rc ? rc : launch_nodes_t<float>(ctx, nullptr, nrhs);
 }
 
 int launch_reflect(mpsl_ctx *ctx, const void *spec, const double *src, void *sigma, int nrhs) {
@@ -1686,24 +1775,26 @@ int launch_s2l(mpsl_ctx *ctx, int prec, void *part, int chunks, int nrhs, int64_
 
 int launch_sum_parts(mpsl_ctx *ctx, int prec, const void *part, int chunks, void *alpha) {
   const int64_t len = ctx->n * static_cast<int64_t>(2 * ctx->p + 1);
+  const dim3 grid(cdiv(len * kSumLanes, 256));
   if (prec == MPSL_FP64)
-    hipLaunchKernelGGL(k_sum_parts<double>, dim3(cdiv(len, 256)), dim3(256), 0, ctx->stream,
-                       static_cast<const double2 *>(part), chunks, len, static_cast<double2 *>(alpha));
+    hipLaunchKernelGGL(k_sum_parts<double>, grid, dim3(256), 0, ctx->stream, static_cast<const double2 *>(part), chunks,
+                       len, static_cast<double2 *>(alpha));
   else
-    hipLaunchKernelGGL(k_sum_parts<float>, dim3(cdiv(len, 256)), dim3(256), 0, ctx->stream,
-                       static_cast<const float2 *>(part), chunks, len, static_cast<float2 *>(alpha));
+    hipLaunchKernelGGL(k_sum_parts<float>, grid, dim3(256), 0, ctx->stream, static_cast<const float2 *>(part), chunks,
+                       len, static_cast<float2 *>(alpha));
   LAUNCH_CHECK(ctx);
   return MPSL_OK;
 }
 
 template <typename T>
-static int launch_sapply_t(mpsl_ctx *ctx, const void *x, const void *alpha, void *y, int nrhs, int64_t astride) {
+static int launch_sapply_t(mpsl_ctx *ctx, const void *x, const void *alpha, int slots, void *y, int nrhs,
+                           int64_t astride) {
   const int n = static_cast<int>(ctx->n);
   const bool f64 = std::is_same<T, double>::value;
   const auto *S = static_cast<const cv_t<T> *>(f64 ? ctx->S64.p : ctx->S32.p);
   const auto *rot = static_cast<const cv_t<T> *>(f64 ? ctx->gt.rot64.p : ctx->gt.rot32.p);
   const dim3 grid(cdiv(n, 16), nrhs);
-  const dim3 block(kSapplyThreads);
+  const dim3 block(slots > 8 ? kSapplyThreads : 256);
   const auto *xx = static_cast<const cv_t<T> *>(x);
   const auto *aa = static_cast<const cv_t<T> *>(alpha);
   auto *yy = static_cast<cv_t<T> *>(y);
@@ -1713,7 +1804,7 @@ static int launch_sapply_t(mpsl_ctx *ctx, const void *x, const void *alpha, void
   const int nt = typed ? ctx->n_types : 1;
   switch (ctx->p) {
 #define X(PP) \
-  case PP: hipLaunchKernelGGL((k_sapply<T, PP>), grid, block, 0, ctx->stream, xx, aa, S, rot, n, yy, astride, ty, nt); break;
+  case PP: hipLaunchKernelGGL((k_sapply<T, PP>), grid, block, 0, ctx->stream, xx, aa, slots, S, rot, n, yy, astride, ty, nt); break;
     MPSL_P_CASES(X)
 #undef X
     default: return set_err(ctx, MPSL_EUNSUPPORTED, "expansion order outside 1..20");
@@ -1722,23 +1813,27 @@ static int launch_sapply_t(mpsl_ctx *ctx, const void *x, const void *alpha, void
   return MPSL_OK;
 }
 
-int launch_sapply(mpsl_ctx *ctx, int prec, const void *x, const void *alpha, void *y, int nrhs, int64_t astride) {
-  return prec == MPSL_FP64 ? launch_sapply_t<double>(ctx, x, alpha, y, nrhs, astride)
-                           : launch_sapply_t<float>(ctx, x, alpha, y, nrhs, astride);
-}
+// Bytes of partials that a tile block of k_sapply sums without help.
+constexpr size_t kSapplySumBytes = 64 * 1024;
 
-int launch_fold_parts(mpsl_ctx *ctx, int prec, void *part, int chunks, int nrhs, int64_t pstride) {
-  if (chunks <= 1) return MPSL_OK;
-  const int64_t len = ctx->n * static_cast<int64_t>(2 * ctx->p + 1);
-  const dim3 grid(cdiv(len, 256), nrhs);
-  if (prec == MPSL_FP64)
-    hipLaunchKernelGGL(k_fold_parts<double>, grid, dim3(256), 0, ctx->stream, static_cast<double2 *>(part), chunks,
-                       len, pstride);
-  else
-    hipLaunchKernelGGL(k_fold_parts<float>, grid, dim3(256), 0, ctx->stream, static_cast<float2 *>(part), chunks,
-                       len, pstride);
-  LAUNCH_CHECK(ctx);
-  return MPSL_OK;
+int launch_sapply(mpsl_ctx *ctx, int prec, const void *x, void *alpha, int slots, void *y, int nrhs, int64_t astride) {
+  // The tile blocks of k_sapply sum the partials themselves where they fill
+  // the chip or have little to sum; else a launch of its own spreads the sums
+  // over more compute units (203 particles, p = 16, FP32, 83 slots: 42.7 us per
+  // matvec with the extra launch, 49.2 us without; 1000, p = 12, FP64, 384
+  // slots: 207 and 249 us; 20000, p = 16, FP32, 16 slots: 1040 us without it,
+  // 1060 us with).
+  const size_t esz = prec == MPSL_FP64 ? sizeof(double2) : sizeof(float2);
+  const size_t tile = 16 * (2 * ctx->p + 1) * esz * slots;
+  if (slots > 1 && tile > kSapplySumBytes && static_cast<int64_t>(cdiv(ctx->n, 16)) * nrhs < ctx->n_cu) {
+    for (int r = 0; r < nrhs; ++r) {
+      char *a = static_cast<char *>(alpha) + r * astride * esz;
+      if (const int rc = launch_sum_parts(ctx, prec, a, slots, a)) return rc;
+    }
+    slots = 1;
+  }
+  return prec == MPSL_FP64 ? launch_sapply_t<double>(ctx, x, alpha, slots, y, nrhs, astride)
+                           : launch_sapply_t<float>(ctx, x, alpha, slots, y, nrhs, astride);
 }
 
 int launch_proj_fix(mpsl_ctx *ctx, void *h, const void *q, int k) {
