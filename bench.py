@@ -32,17 +32,18 @@ M2L_VARIANTS = {
     0: ("k_m2l<{t},16,-1> (all-pairs M2L, one lane per target)", "alu", "m2l_5000stars_p16_hbm_traffic.md",
         ("// Row a1: all-pairs free-space M2L", "// FMM near field:")),
     1: ("k_m2l<{t},16,0|1> (all-pairs M2L, output halves)", "alu", None, None),
-    2: ("k_m2l_mfma<{t},16,1> (all-pairs M2L on the matrix cores)", "mfma",
+    2: ("k_m2l_bf<16,1> / k_m2l_f64<16,1> ({t}, all-pairs M2L on the matrix cores)", "mfma",
         "m2l_mfma_5000stars_p16_hbm_traffic.md",
         ("// Row a1 on the matrix cores, one right-hand side.", "// Row a1 for many right-hand sides")),
-    3: ("k_m2l_mfma<{t},16,2> (all-pairs M2L on the matrix cores, 32 targets per wave)", "mfma", None, None),
+    3: ("k_m2l_bf<16,2> / k_m2l_f64<16,2> ({t}, all-pairs M2L on the matrix cores, 32 targets per wave)", "mfma",
+        None, None),
 }
 
 
 def m2l_source_sha256(variant=0):
     """Hash of the source of one M2L kernel variant (its device code)."""
     region = M2L_VARIANTS[variant][3]
-    with open(os.path.join(ROOT, "paper_1407_3868_amd", "csrc", "kernels.hip")) as fh:
+    with open(os.path.join(ROOT, "paper_1407_3868_amd", "csrc", "m2l.hip")) as fh:
         src = fh.read()
     a = src.index(region[0])
     b = src.index(region[1], a)

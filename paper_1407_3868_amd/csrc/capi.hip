@@ -1147,7 +1147,7 @@ int mpsl_set_tuning(mpsl_ctx *ctx, int prec, int variant, int chunks) {
 int mpsl_get_tuning(const mpsl_ctx *ctx, int prec, int *variant, int *chunks, double *ms) {
   if (!ctx || (prec != MPSL_FP64 && prec != MPSL_FP32)) return MPSL_EINVAL;
   const auto &t = ctx->tune[prec == MPSL_FP64 ? 0 : 1];
-  if (variant) *variant = t.variant >= 0 ? t.variant : mpsl::m2l_default_variant(ctx->p, prec);
+  if (variant) *variant = t.variant >= 0 ? t.variant : mpsl::m2l_default_variant(ctx, prec);
   if (chunks) *chunks = mpsl::chunks_m2l(ctx, prec);
   if (ms) *ms = t.ms;
   return MPSL_OK;

@@ -1,4 +1,4 @@
-// Launchers of the device kernels (implemented in kernels.hip).
+// Launchers of the device kernels (implemented in kernels.hip, m2l.hip, field.hip and somm.hip).
 #pragma once
 
 #include "context.h"
@@ -30,8 +30,8 @@ constexpr int kM2LHalves = 1;
 constexpr int kM2LMfma = 2;
 constexpr int kM2LMfmaWide = 3;
 constexpr int kM2LMfmaMaxP = 16;
-// Variant used before any tuning: by expansion order and precision.
-int m2l_default_variant(int p, int prec);
+// Variant used before any tuning: by expansion order, precision and size.
+int m2l_default_variant(const mpsl_ctx *ctx, int prec);
 // nrhs right-hand sides: beta [nrhs][n][P]; part of rhs r at part + r * pstride.
 int launch_m2l(mpsl_ctx *ctx, int prec, const void *beta, void *part, int chunks, int variant = -1,
                int nrhs = 1, int64_t pstride = 0);

@@ -90,186 +90,6 @@ __global__ void k_pair_tables(const double2 *__restrict__ xy, int n, double k2, 
   }
 }
 
-// Row a1: all-pairs free-space M2L (Graf's addition theorem).
-// One lane per target l; every lane of the grid walks the same source chunk,
-// so the source's coefficients are wave-uniform and live in scalar registers.
-// Per pair: H_0, H_1 and e^{i phi} from the pair table, the upward recurrence
-// H_{q+1} = (2q/z) H_q - H_{q-1}, e^{iq phi} by repeated multiplication,
-// h_q = H_q e^{iq phi}, h_{-q} = (-1)^q H_q e^{-iq phi}, and the Toeplitz
-// product alpha_{n'} += sum_nu h_{nu - n'} beta_nu consumed in the order the
-// recurrence produces h_q.
-//
-// m2l_block adds the contribution of source slots [V0, V1] to output slots
-// [O0, O1].  FP32 does everything in one call (33 accumulators, 66 scalar
-// registers of beta at p = 16).  FP64 splits the outputs over two lanes and
-// the source coefficients over two calls: 17 accumulators and at most 68
-// scalar registers of beta, at the cost of re-running the recurrence.
-template <typename T, int p, int O0, int O1, int V0, int V1, bool MIRROR>
-__device__ __forceinline__ void m2l_block(cx<T> (&acc)[O1 - O0 + 1], const cv_t<T> *__restrict__ bm, cx<T> h0,
-                                          cx<T> h1, cx<T> t, T two_over_z) {
-  constexpr int QA = V1 - O0, QB = O1 - V0;
-  constexpr int QMAX = (QA > QB ? QA : QB) < 2 * p ? (QA > QB ? QA : QB) : 2 * p;
-  cx<T> bv[V1 - V0 + 1];
-#pragma unroll
-  for (int v = V0; v <= V1; ++v) bv[v - V0] = ld<T>(bm[MIRROR ? 2 * p - v : v]);
-#pragma unroll
-  for (int v = (V0 > O0 ? V0 : O0); v <= (V1 < O1 ? V1 : O1); ++v) cmac(acc[v - O0], h0, bv[v - V0]);
-  cx<T> hprev = h0, hcur = h1, tq = t;
-#pragma unroll
-  for (int q = 1; q <= QMAX; ++q) {
-    if (q >= 2) {
-      const cx<T> hn = static_cast<T>(q - 1) * two_over_z * hcur - hprev;
-      hprev = hcur;
-      hcur = hn;
-      tq = tq * t;
-    }
-    // alpha_{v-q} += h_q beta_v for v - q in [O0, O1]
-    if ((V1 < O1 + q ? V1 : O1 + q) >= (V0 > O0 + q ? V0 : O0 + q)) {
-      const cx<T> hp = hcur * tq;
-#pragma unroll
-      for (int v = (V0 > O0 + q ? V0 : O0 + q); v <= (V1 < O1 + q ? V1 : O1 + q); ++v)
-        cmac(acc[v - q - O0], hp, bv[v - V0]);
-    }
-    // alpha_{v+q} += h_{-q} beta_v for v + q in [O0, O1]
-    if ((V1 < O1 - q ? V1 : O1 - q) >= (V0 > O0 - q ? V0 : O0 - q)) {
-      cx<T> hm = hcur * conj(tq);
-      if (q & 1) hm = mk<T>(-hm.re, -hm.im);
-#pragma unroll
-      for (int v = (V0 > O0 - q ? V0 : O0 - q); v <= (V1 < O1 - q ? V1 : O1 - q); ++v)
-        cmac(acc[v + q - O0], hm, bv[v - V0]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
-// Mirror identity: with reversed indices (alpha~_k = alpha_{-k},
-// beta~_nu = beta_{-nu}) the translation keeps its Toeplitz form with
-// h~_q = h_{-q} = H_q e^{iq(pi - phi)}, i.e. e^{i phi} -> -conj(e^{i phi}).
-// MIRROR = true computes output slots 2p - [O0, O1] that way.
-template <typename T, int p, int O0, int O1, int SPLIT, bool MIRROR>
-__device__ __forceinline__ void m2l_body(const cv_t<T> *__restrict__ pairs, const cv_t<T> *__restrict__ beta,
-                                         cv_t<T> *__restrict__ part, int n, int m0, int m1, int l) {
-  constexpr int P = 2 * p + 1;
-  constexpr int NO = O1 - O0 + 1;
-  const bool valid = l < n;
-  const int lc = valid ? l : n - 1;
-  cx<T> acc[NO];
-#pragma unroll
-  for (int i = 0; i < NO; ++i) acc[i] = mk<T>(0, 0);
-  if (m0 < m1) {
-    const cv_t<T> *pe = pairs + 4 * (static_cast<int64_t>(m0) * n + lc);
-    cv_t<T> a0 = pe[0], a1 = pe[1], a2 = pe[2], a3 = pe[3];
-    for (int m = m0; m < m1; ++m) {
-      cx<T> h0 = ld<T>(a0), h1 = ld<T>(a1);
-      cx<T> t = ld<T>(a2);
-      if (MIRROR) t.re = -t.re;
-      const T two_over_z = a3.x;
-      if (m + 1 < m1) {  // prefetch the next source's pair entry
-        pe += 4 * static_cast<int64_t>(n);
-        a0 = pe[0];
-        a1 = pe[1];
-        a2 = pe[2];
-        a3 = pe[3];
-      }
-      if (!valid) h0 = h1 = mk<T>(0, 0);
-      const cv_t<T> *bm = beta + static_cast<int64_t>(m) * P;
-      if (SPLIT) {  // source coefficients in two halves, one scalar-register set each
-        m2l_block<T, p, O0, O1, 0, p, MIRROR>(acc, bm, h0, h1, t, two_over_z);
-        __builtin_amdgcn_sched_barrier(0);
-        m2l_block<T, p, O0, O1, p + 1, P - 1, MIRROR>(acc, bm, h0, h1, t, two_over_z);
-        __builtin_amdgcn_sched_barrier(0);
-      } else {
-        m2l_block<T, p, O0, O1, 0, P - 1, MIRROR>(acc, bm, h0, h1, t, two_over_z);
-      }
-    }
-  }
-  if (valid) {
-#pragma unroll
-    for (int i = 0; i < NO; ++i) part[static_cast<int64_t>(l) * P + (MIRROR ? 2 * p - O0 - i : O0 + i)] = st(acc[i]);
-  }
-}
-
-// grid: (target blocks, source chunks); part[chunk][n][P].  Two variants:
-//  whole  (HALF = -1): one lane holds all P accumulators of its target;
-//  halves (HALF = 0, 1, two launches): output slots [0, p] and, through the
-//         mirror identity, [p+1, 2p], at most p+1 accumulators per lane and
-//         more waves per SIMD, for twice the recurrence work.  The two halves
-//         are separate kernels: in one kernel the compiler merges the bodies
-//         and doubles the live registers.
-// FP64 always takes the source coefficients in two scalar-register halves.
-// The launcher runs the variant the autotuner picked (default: whole).
-template <typename T, int p, int HALF>
-__global__ __launch_bounds__(kThreads) void k_m2l(const cv_t<T> *__restrict__ pairs,
-                                                  const cv_t<T> *__restrict__ beta,
-                                                  cv_t<T> *__restrict__ part, int n, int chunk_len,
-                                                  int64_t bstride, int64_t pstride) {
-  constexpr int P = 2 * p + 1;
-  const int l = blockIdx.x * kThreads + threadIdx.x;
-  const int c = blockIdx.y;
-  beta += blockIdx.z * bstride;  // right-hand side
-  part += blockIdx.z * pstride;
-  const int m0 = c * chunk_len;
-  const int m1 = min(n, m0 + chunk_len);
-  cv_t<T> *o = part + static_cast<int64_t>(c) * n * P;
-  constexpr int SPLIT = std::is_same<T, double>::value ? 1 : 0;
-  if (HALF == 0) m2l_body<T, p, 0, p, SPLIT, false>(pairs, beta, o, n, m0, m1, l);
-  else if (HALF == 1) m2l_body<T, p, 0, p - 1, SPLIT, true>(pairs, beta, o, n, m0, m1, l);
-  else m2l_body<T, p, 0, P - 1, SPLIT, false>(pairs, beta, o, n, m0, m1, l);
-}
-
-// FMM near field: the same pair translation restricted to padded neighbour
-// lists.  One lane per target in leaf-box order; each lane walks its own
-// list of sources (pair entries [j][i][4] as in the all-pairs table, source
-// coefficients loaded per lane), and every wave loops to the longest list
-// among its 64 targets (padding entries are zeros).  HALF as in k_m2l: -1
-// all outputs; 0 / 1 output slots [0, p] / (mirror) [p+1, 2p] in two
-// launches, which keeps FP64 within the register file.
-template <typename T, int p, int HALF>
-__global__ __launch_bounds__(kThreads) void k_fmm_near(const cv_t<T> *__restrict__ pairs,
-                                                       const int *__restrict__ src, const int *__restrict__ perm,
-                                                       const int *__restrict__ wave_cnt,
-                                                       const cv_t<T> *__restrict__ beta, cv_t<T> *__restrict__ out,
-                                                       int n, int kc) {
-  constexpr int P = 2 * p + 1;
-  const int i = blockIdx.x * kThreads + threadIdx.x;
-  // list entries [j_lo, j_hi) of this chunk into partial slot blockIdx.y
-  const int kw = __builtin_amdgcn_readfirstlane(wave_cnt[i >> 6]);
-  const int j_lo = blockIdx.y * kc, j_hi = min(kw, j_lo + kc);
-  out += static_cast<int64_t>(blockIdx.y) * n * P;
-  const bool valid = i < n;
-  const int ic = valid ? i : n - 1;
-  constexpr bool MIRROR = HALF == 1;
-  constexpr int O1 = HALF == 0 ? p : (HALF == 1 ? p - 1 : P - 1);  // outputs [0, O1]
-  cx<T> acc[O1 + 1];
-#pragma unroll
-  for (int k = 0; k <= O1; ++k) acc[k] = mk<T>(0, 0);
-  constexpr int SPLIT = std::is_same<T, double>::value ? 1 : 0;
-  for (int j = j_lo; j < j_hi; ++j) {
-    const int64_t e = static_cast<int64_t>(j) * n + ic;
-    const cv_t<T> *pe = pairs + 4 * e;
-    cx<T> h0 = ld<T>(pe[0]), h1 = ld<T>(pe[1]);
-    cx<T> t = ld<T>(pe[2]);
-    if (MIRROR) t.re = -t.re;
-    const T two_over_z = pe[3].x;
-    if (!valid) h0 = h1 = mk<T>(0, 0);
-    const cv_t<T> *bm = beta + static_cast<int64_t>(src[e]) * P;
-    if (SPLIT) {
-      m2l_block<T, p, 0, O1, 0, p, MIRROR>(acc, bm, h0, h1, t, two_over_z);
-      __builtin_amdgcn_sched_barrier(0);
-      m2l_block<T, p, 0, O1, p + 1, P - 1, MIRROR>(acc, bm, h0, h1, t, two_over_z);
-      __builtin_amdgcn_sched_barrier(0);
-    } else {
-      m2l_block<T, p, 0, O1, 0, P - 1, MIRROR>(acc, bm, h0, h1, t, two_over_z);
-    }
-  }
-  if (valid) {
-    const int64_t o = static_cast<int64_t>(perm[i]) * P;
-#pragma unroll
-    for (int k = 0; k <= O1; ++k) out[o + (MIRROR ? 2 * p - k : k)] = st(acc[k]);
-  }
-}
-
-
 // M2S partials to spectra, and for the matvec on to the S2L coefficients: per
 // block 16 nodes, both sides, eight lanes per (node, side) taking every eighth
 // particle chunk (FP64 sums, added in order).  With spec the sums are stored
@@ -790,369 +610,6 @@ __global__ __launch_bounds__(64 * kS2lWaves) void k_s2l_mfma(const cv_t<T> *__re
 }
 
 // ---------------------------------------------------------------------------
-// Row a1 on the matrix cores, one right-hand side.  The translation
-// alpha_{n'} = sum_q h_q beta_{n'+q} (q = nu - n', |q| <= 2p) is a product
-// with the source coefficients in shifted form: with A_m[n'][q] = beta_m[n'+q]
-// (zero where |n' + q| > p) and B[(m, q)][l] = h_q of the pair (m -> l),
-//   alpha_l[n'] = sum_{m, q} A_m[n'][q] B[(m, q)][l],
-// a GEMM with M = output orders, N = targets and K = (source, q).  Each
-// 16x16x4 MFMA takes four sources at one q: lane i runs the Hankel recurrence
-// of the pair (source i / 16 of the group -> target i % 16) and supplies its
-// h_q as the B operand; A, the shifted coefficients of one 16-row block of
-// output orders, is read from LDS.  Orders n' in [-p, -1] ("lo") and [1, p]
-// ("hi") are two 16-row blocks (for p < 16 the rows beyond p compute
-// values that are never stored; their reads stay inside the row); n' = 0 is
-// accumulated on the vector units and summed over the four sources of a
-// group at the end.  q runs from 0 to 2p; h_q and h_{-q} go to the blocks
-// whose rows they reach: 96 complex MFMAs per group at p = 16, against the
-// 66 that the nonzero band of the 32 block rows needs.  Complex products take three real MFMAs
-// (Gauss): P1 = sum Ar Br, P2 = sum Ai Bi, P3 = sum (Ar + Ai)(Br + Bi);
-// re = P1 - P2, im = P3 - P1 - P2.  LDS holds the coefficients of
-// kM2lMfmaBatch sources of the chunk as (re, im, re + im) with zero padding
-// on both sides of every row.  Each wave owns NT tiles of 16 targets (NT = 1
-// or 2); the A reads are shared across its tiles.
-constexpr int kM2lMfmaWaves = 4;
-constexpr int kM2lMfmaBatch = 32;
-
-template <typename T, int p, int NT>
-__global__ __launch_bounds__(64 * kM2lMfmaWaves) void k_m2l_mfma(const cv_t<T> *__restrict__ pairs,
-                                                                 const cv_t<T> *__restrict__ beta,
-                                                                 cv_t<T> *__restrict__ part, int n, int chunk_len,
-                                                                 int64_t bstride, int64_t pstride) {
-  static_assert(p >= 1 && p <= 16, "one 16-row block per sign of n'");
-  constexpr int P = 2 * p + 1;
-  constexpr int OFS = p - 1;       // LDS index of coefficient slot s (s >= 1 - p)
-  // Row length: slots [1 - p, 2p + 15].  FP32 rows are padded to 16 mod 64
-  // words, so that the four source rows one read touches start in different
-  // LDS banks (a stride of 0 mod 32 words serialises them four ways).
-  constexpr int LR0 = 3 * p + 16;
-  constexpr int LR = sizeof(T) == 4 ? LR0 + ((16 - LR0) % 64 + 64) % 64 : LR0;
-  constexpr int SB = kM2lMfmaBatch;
-  typedef typename mfma4<T>::v4 v4;
-  __shared__ T sa[3][SB][LR];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int r = lane & 15, g = lane >> 4;
-  const int c = blockIdx.y;
-  beta += blockIdx.z * bstride;
-  part += blockIdx.z * pstride;
-  const int m0 = c * chunk_len;
-  const int m1 = min(n, m0 + chunk_len);
-  const int lt0 = (blockIdx.x * kM2lMfmaWaves + w) * 16 * NT;
-
-  for (int e = threadIdx.x; e < 3 * SB * LR; e += 64 * kM2lMfmaWaves) (&sa[0][0][0])[e] = T(0);
-
-  v4 lo[NT][3], hi[NT][3];
-  cx<T> zc[NT];
-#pragma unroll
-  for (int tt = 0; tt < NT; ++tt) {
-#pragma unroll
-    for (int k = 0; k < 3; ++k) lo[tt][k] = hi[tt][k] = v4{0, 0, 0, 0};
-    zc[tt] = mk<T>(0, 0);
-  }
-  // pair entries of the first group (source m0 + g)
-  cv_t<T> pa[NT][4];
-  auto load_pairs = [&](int m) {
-#pragma unroll
-    for (int tt = 0; tt < NT; ++tt) {
-      const int l = lt0 + tt * 16 + r;
-      if (m < m1 && l < n) {
-        const cv_t<T> *pe = pairs + 4 * (static_cast<int64_t>(m) * n + l);
-#pragma unroll
-        for (int k = 0; k < 4; ++k) pa[tt][k] = pe[k];
-      } else {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) pa[tt][k] = st(mk<T>(0, 0));
-      }
-    }
-  };
-  load_pairs(m0 + g);
-
-  for (int mb = m0; mb < m1; mb += SB) {
-    const int sb = min(SB, m1 - mb);
-    __syncthreads();  // previous batch consumed (and the zero fill done)
-    for (int e = threadIdx.x; e < SB * P; e += 64 * kM2lMfmaWaves) {
-      const int s = e / P, v = e - s * P;
-      const cx<T> b = s < sb ? ld<T>(beta[static_cast<int64_t>(mb + s) * P + v]) : mk<T>(0, 0);
-      sa[0][s][v + OFS] = b.re;
-      sa[1][s][v + OFS] = b.im;
-      sa[2][s][v + OFS] = b.re + b.im;
-    }
-    __syncthreads();
-    // a wave whose targets all lie past the last particle (the grid's tail)
-    // stages its share of the batch and meets the barriers, but multiplies nothing
-    for (int g0 = 0; g0 < sb && lt0 < n; g0 += 4) {
-      const int s = g0 + g;  // this lane's source within the batch
-      cx<T> hp[NT], hc[NT], t[NT], tq[NT];
-      T tz[NT];
-#pragma unroll
-      for (int tt = 0; tt < NT; ++tt) {
-        hp[tt] = ld<T>(pa[tt][0]);
-        hc[tt] = ld<T>(pa[tt][1]);
-        t[tt] = ld<T>(pa[tt][2]);
-        tq[tt] = t[tt];
-        tz[tt] = pa[tt][3].x;
-      }
-      load_pairs(mb + s + 4);  // next group's entries in flight
-      const T *ar = sa[0][s], *ai = sa[1][s], *as = sa[2][s];
-      // A operands of step q.  lo rows: n' = r - p, coefficient slot r + q
-      // (h_q) and r - q (h_{-q}); hi rows: n' = r + 1, slots r + 1 + p + q and
-      // r + 1 + p - q; row n' = 0: slots p + q and p - q.
-      struct Ops {
-        T al[3], ah[3], bl[3], bh[3];
-        cx<T> bp, bn;
-      };
-      auto fetch = [&](int q) {
-        Ops o;
-        const int il = r + q + OFS, ih = r + 1 + p + q + OFS;
-        const int jl = r - q + OFS, jh = r + 1 + p - q + OFS;
-        o.al[0] = ar[il], o.al[1] = ai[il], o.al[2] = as[il];
-        if (q <= p - 1) o.ah[0] = ar[ih], o.ah[1] = ai[ih], o.ah[2] = as[ih];
-        if (q >= 1 && q <= p - 1) o.bl[0] = ar[jl], o.bl[1] = ai[jl], o.bl[2] = as[jl];
-        if (q >= 1) o.bh[0] = ar[jh], o.bh[1] = ai[jh], o.bh[2] = as[jh];
-        if (q <= p) {
-          o.bp = mk<T>(ar[p + q + OFS], ai[p + q + OFS]);
-          o.bn = mk<T>(ar[p - q + OFS], ai[p - q + OFS]);
-        }
-        return o;
-      };
-      Ops cur = fetch(0);
-#pragma unroll
-      for (int q = 0; q <= 2 * p; ++q) {
-        Ops nxt;
-        if (q < 2 * p) nxt = fetch(q + 1);  // the next step's LDS reads in flight
-        cx<T> hq[NT], hm[NT];
-#pragma unroll
-        for (int tt = 0; tt < NT; ++tt) {
-          if (q == 0) {
-            hq[tt] = hp[tt];  // H_0
-          } else {
-            if (q >= 2) {
-              const cx<T> hn = static_cast<T>(q - 1) * tz[tt] * hc[tt] - hp[tt];
-              hp[tt] = hc[tt];
-              hc[tt] = hn;
-              tq[tt] = tq[tt] * t[tt];
-            }
-            hq[tt] = hc[tt] * tq[tt];
-            hm[tt] = hc[tt] * conj(tq[tt]);
-            if (q & 1) hm[tt] = mk<T>(-hm[tt].re, -hm[tt].im);
-          }
-        }
-        // n' = 0 on the vector units: alpha_0 += h_q beta_q + h_{-q} beta_{-q}
-        if (q <= p) {
-#pragma unroll
-          for (int tt = 0; tt < NT; ++tt) cmac(zc[tt], hq[tt], cur.bp);
-          if (q > 0) {
-#pragma unroll
-            for (int tt = 0; tt < NT; ++tt) cmac(zc[tt], hm[tt], cur.bn);
-          }
-        }
-        // the two blocks alternate so that no MFMA waits on the one before it
-        const bool lom = q >= 1 && q <= p - 1, hip_ = q <= p - 1, him = q >= 1;
-#pragma unroll
-        for (int tt = 0; tt < NT; ++tt) {
-          const T sq = hq[tt].re + hq[tt].im;
-          lo[tt][0] = mfma4<T>::mac(cur.al[0], hq[tt].re, lo[tt][0]);
-          if (hip_) hi[tt][0] = mfma4<T>::mac(cur.ah[0], hq[tt].re, hi[tt][0]);
-          lo[tt][1] = mfma4<T>::mac(cur.al[1], hq[tt].im, lo[tt][1]);
-          if (hip_) hi[tt][1] = mfma4<T>::mac(cur.ah[1], hq[tt].im, hi[tt][1]);
-          lo[tt][2] = mfma4<T>::mac(cur.al[2], sq, lo[tt][2]);
-          if (hip_) hi[tt][2] = mfma4<T>::mac(cur.ah[2], sq, hi[tt][2]);
-          if (q >= 1) {
-            const T sm = hm[tt].re + hm[tt].im;
-            if (him) hi[tt][0] = mfma4<T>::mac(cur.bh[0], hm[tt].re, hi[tt][0]);
-            if (lom) lo[tt][0] = mfma4<T>::mac(cur.bl[0], hm[tt].re, lo[tt][0]);
-            if (him) hi[tt][1] = mfma4<T>::mac(cur.bh[1], hm[tt].im, hi[tt][1]);
-            if (lom) lo[tt][1] = mfma4<T>::mac(cur.bl[1], hm[tt].im, lo[tt][1]);
-            if (him) hi[tt][2] = mfma4<T>::mac(cur.bh[2], sm, hi[tt][2]);
-            if (lom) lo[tt][2] = mfma4<T>::mac(cur.bl[2], sm, lo[tt][2]);
-          }
-        }
-        cur = nxt;
-        // one q step at a time: keeps the live registers to two steps' operands
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-  }
-  cv_t<T> *o = part + static_cast<int64_t>(c) * n * P;
-#pragma unroll
-  for (int tt = 0; tt < NT; ++tt) {
-    const int l = lt0 + tt * 16 + r;
-    cx<T> z = zc[tt];
-    z.re += __shfl_xor(z.re, 16);
-    z.im += __shfl_xor(z.im, 16);
-    z.re += __shfl_xor(z.re, 32);
-    z.im += __shfl_xor(z.im, 32);
-    if (l >= n) continue;
-    if (g == 0) o[static_cast<int64_t>(l) * P + p] = st(z);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = mfma4<T>::row(lane, j);
-      if (row < p) {
-        const T p1 = lo[tt][0][j], p2 = lo[tt][1][j], p3 = lo[tt][2][j];
-        o[static_cast<int64_t>(l) * P + row] = st(mk<T>(p1 - p2, p3 - p1 - p2));
-        const T q1 = hi[tt][0][j], q2 = hi[tt][1][j], q3 = hi[tt][2][j];
-        o[static_cast<int64_t>(l) * P + p + 1 + row] = st(mk<T>(q1 - q2, q3 - q1 - q2));
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Row a1 for many right-hand sides on the matrix cores (FP32): per pair the
-// Toeplitz translation T^{ml}[n'][nu] = h_{nu-n'} is built once and applied to
-// the coefficients of 64 right-hand sides as a GEMM  alpha_l[n'][r] +=
-// sum_nu T[n'][nu] beta_m[nu][r]  with 16x16x4 MFMA (M = n', K = nu, N = r),
-// complex products in three real MFMAs (Gauss).  One wave per target, kMrhsWaves
-// targets per block, grid.y source chunks, grid.z groups of 64 right-hand
-// sides.  Lanes 0..7 of each wave run the Hankel recurrences of 8 sources
-// at a time (from the pair table, as in k_m2l) into zero-padded LDS rows;
-// the A operand is read from there.  The B operand, beta transposed to
-// [m][nu][r] (r fastest, zero rows and columns as padding), is staged per
-// source in LDS for all waves of the block, double-buffered: the next
-// source's loads are in flight during the current source's MFMAs.
-constexpr int kMrhsWaves = 8;
-constexpr int kMrhsBatch = 8;
-
-template <int p>
-__global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs(const float2 *__restrict__ pairs,
-                                                              const float2 *__restrict__ bt,
-                                                              float2 *__restrict__ part, int n, int chunk_len,
-                                                              int nrhs, int r_pad, int64_t pstride) {
-  constexpr int P = 2 * p + 1;
-  constexpr int MT = (P + 15) / 16;
-  constexpr int KP = (P + 3) / 4 * 4;
-  constexpr int NT = 4;                      // 64 right-hand sides per block
-  constexpr int OFF = 16 * MT - 1;           // H index of q = k - row is q + OFF
-  constexpr int HQ = KP + OFF;               // zero outside |q| <= 2p
-  constexpr int BE = KP * 64;                // B entries of one source
-  constexpr int BL = (BE + 64 * kMrhsWaves - 1) / (64 * kMrhsWaves);  // loads per thread
-  __shared__ float2 H[kMrhsWaves][kMrhsBatch][HQ];
-  __shared__ float2 Bs[2][KP][64];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int l = blockIdx.x * kMrhsWaves + w;
-  const int c = blockIdx.y;
-  const int r0 = blockIdx.z * 64;
-  const int m0 = c * chunk_len;
-  const int m1 = min(n, m0 + chunk_len);
-  typedef float v4 __attribute__((ext_vector_type(4)));
-  // Gauss: P1 = sum Ar Br, P2 = sum Ai Bi, P3 = sum (Ar + Ai)(Br + Bi)
-  v4 P1[MT][NT], P2[MT][NT], P3[MT][NT];
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int ct = 0; ct < NT; ++ct) P1[mt][ct] = P2[mt][ct] = P3[mt][ct] = v4{0, 0, 0, 0};
-  const int col = lane & 15, kq = lane >> 4;
-  // B of source m: rows k (zero rows k >= P in bt), 64 right-hand sides
-  float2 pre[BL];
-  auto load_b = [&](int m) {
-#pragma unroll
-    for (int i = 0; i < BL; ++i) {
-      const int e = threadIdx.x + 64 * kMrhsWaves * i;
-      pre[i] = (m < m1 && e < BE) ? bt[(static_cast<int64_t>(m) * KP + e / 64) * r_pad + r0 + (e & 63)]
-                                  : make_float2(0.f, 0.f);
-    }
-  };
-  auto store_b = [&](int buf) {
-#pragma unroll
-    for (int i = 0; i < BL; ++i) {
-      const int e = threadIdx.x + 64 * kMrhsWaves * i;
-      if (e < BE) Bs[buf][e / 64][e & 63] = pre[i];
-    }
-  };
-  load_b(m0);
-  int it = 0;
-  for (int mb = m0; mb < m1; mb += kMrhsBatch) {
-    const int sb = min(kMrhsBatch, m1 - mb);
-    for (int i = lane; i < kMrhsBatch * HQ; i += 64) H[w][i / HQ][i % HQ] = make_float2(0.f, 0.f);
-    __syncthreads();
-    if (lane < sb) {  // h_q of pair (mb + lane -> l), q = -2p..2p
-      const int m = mb + lane;
-      float2 *h = H[w][lane] + OFF;
-      if (l < n && m != l) {
-        const float2 *pe = pairs + 4 * (static_cast<int64_t>(m) * n + l);
-        cx<float> hp = ld<float>(pe[0]), hc = ld<float>(pe[1]);
-        const cx<float> t = ld<float>(pe[2]);
-        const float tz = pe[3].x;
-        h[0] = st(hp);
-        cx<float> tq = t;
-        for (int q = 1; q <= 2 * p; ++q) {
-          if (q >= 2) {
-            const cx<float> hn = static_cast<float>(q - 1) * tz * hc - hp;
-            hp = hc;
-            hc = hn;
-            tq = tq * t;
-          }
-          h[q] = st(hc * tq);
-          cx<float> hm = hc * conj(tq);
-          if (q & 1) hm = mk<float>(-hm.re, -hm.im);
-          h[-q] = st(hm);
-        }
-      }
-    }
-    for (int s = 0; s < sb; ++s, ++it) {
-      const int buf = it & 1;
-      store_b(buf);          // B of source mb + s (loaded one iteration ahead)
-      __syncthreads();
-      load_b(mb + s + 1);    // next source's B in flight during the MFMAs
-      const float2 *hrow = H[w][s];
-#pragma unroll
-      for (int k0 = 0; k0 < KP; k0 += 4) {
-        const int k = k0 + kq;
-        float br[NT], bi[NT], bs[NT];
-#pragma unroll
-        for (int ct = 0; ct < NT; ++ct) {
-          const float2 bv = Bs[buf][k][ct * 16 + col];
-          br[ct] = bv.x;
-          bi[ct] = bv.y;
-          bs[ct] = bv.x + bv.y;
-        }
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-          const float2 a = hrow[k - (mt * 16 + col) + OFF];
-          const float as = a.x + a.y;
-#pragma unroll
-          for (int ct = 0; ct < NT; ++ct) {
-            P1[mt][ct] = mfma4<float>::mac(a.x, br[ct], P1[mt][ct]);
-            P2[mt][ct] = mfma4<float>::mac(a.y, bi[ct], P2[mt][ct]);
-            P3[mt][ct] = mfma4<float>::mac(as, bs[ct], P3[mt][ct]);
-          }
-        }
-      }
-    }
-    __syncthreads();
-  }
-  if (l >= n) return;
-  // result register j of lane i: row 4 (i / 16) + j, column i % 16
-  const int64_t len = static_cast<int64_t>(n) * P;
-#pragma unroll
-  for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-    for (int ct = 0; ct < NT; ++ct)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int row = mt * 16 + 4 * kq + j;
-        const int r = r0 + ct * 16 + col;
-        const float p1 = P1[mt][ct][j], p2 = P2[mt][ct][j], p3 = P3[mt][ct][j];
-        if (row < P && r < nrhs)
-          part[r * pstride + c * len + static_cast<int64_t>(l) * P + row] = make_float2(p1 - p2, p3 - p1 - p2);
-      }
-}
-
-// beta [r][m][P] -> bt [m][KP][r_pad] (r fastest; zero rows k >= P and
-// zero columns r >= nrhs), FP32.
-__global__ void k_rhs_transpose(const float2 *__restrict__ x, float2 *__restrict__ bt, int n, int P, int KP,
-                                int nrhs, int r_pad) {
-  const int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  const int64_t rows = static_cast<int64_t>(n) * KP;
-  if (i >= rows * r_pad) return;
-  const int64_t row = i / r_pad;
-  const int r = static_cast<int>(i % r_pad);
-  const int m = static_cast<int>(row / KP), k = static_cast<int>(row % KP);
-  bt[i] = (r < nrhs && k < P) ? x[r * static_cast<int64_t>(n) * P + static_cast<int64_t>(m) * P + k]
-                              : make_float2(0.f, 0.f);
-}
-
-// ---------------------------------------------------------------------------
 // GMRES helpers, FP64 complex.
 constexpr int kDotBlocks = 64;
 constexpr int kRed = 256;
@@ -1351,36 +808,6 @@ __global__ void k_to64(const float2 *__restrict__ a, double2 *__restrict__ b, in
 
 }  // namespace
 
-int m2l_default_variant(int p, int prec) {
-  // measured crossovers at 5000 particles: the matrix-core form wins from
-  // p = 12 in FP32 and at p = 16 in FP64 (its FP64 MFMA rate equals the vector
-  // rate, so only the larger translations gain)
-  const int from = prec == MPSL_FP64 ? 15 : 12;
-  return (p >= from && p <= kM2LMfmaMaxP) ? kM2LMfma : kM2LWhole;
-}
-
-static int m2l_variant(const mpsl_ctx *ctx, int prec) {
-  int v = ctx->tune[prec == MPSL_FP64 ? 0 : 1].variant;
-  if (v < 0) v = m2l_default_variant(ctx->p, prec);
-  if (v >= kM2LMfma && ctx->p > kM2LMfmaMaxP) v = kM2LWhole;
-  return v;
-}
-
-int chunks_m2l(const mpsl_ctx *ctx, int prec) {
-  const int tuned = ctx->tune[prec == MPSL_FP64 ? 0 : 1].chunks;
-  if (tuned > 0) return static_cast<int>(std::min<int64_t>(tuned, ctx->n));
-  if (ctx->m2l_chunks > 0) return static_cast<int>(std::min<int64_t>(ctx->m2l_chunks, ctx->n));
-  // about 2560 blocks of 128 lanes, or 10240 of 4 waves on the matrix cores
-  const int v = m2l_variant(ctx, prec);
-  int c = v >= kM2LMfma ? cdiv(10240, cdiv(ctx->n, 64 * (v == kM2LMfmaWide ? 2 : 1)))
-                        : cdiv(2560, cdiv(ctx->n, kThreads));
-  c = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(c, ctx->n)));
-  // matrix cores: chunks of whole groups of four sources (m2l_mfma_chunk_len),
-  // counted so that none is empty
-  if (v >= kM2LMfma) c = cdiv(ctx->n, m2l_mfma_chunk_len(static_cast<int>(ctx->n), c));
-  return c;
-}
-
 // Chunk count for a launch of bpc blocks per chunk whose blocks all carry the
 // same work.  With `slots` blocks resident at once on the whole chip
 // (compute units x blocks per unit), B blocks run in ceil(B / slots) waves,
@@ -1519,146 +946,6 @@ int launch_pair_tables(mpsl_ctx *ctx) {
                      static_cast<double2 *>(ctx->gt.pair64.p), static_cast<float2 *>(ctx->gt.pair32.p));
   LAUNCH_CHECK(ctx);
   return MPSL_OK;
-}
-
-// Sources per chunk of the matrix-core M2L: each MFMA step takes a group of
-// four sources, so a chunk length that is not a multiple of 4 leaves a part
-// of one group's matrix work on zeros in every chunk (39 sources: 2.5 %
-// of the launch at 5000 particles); trailing chunks may come out empty and
-// then write zero partials.
-int m2l_mfma_chunk_len(int n, int chunks) { return (cdiv(n, chunks) + 3) / 4 * 4; }
-
-template <typename T>
-static int launch_m2l_t(mpsl_ctx *ctx, const void *beta, void *part, int chunks, int variant, int nrhs,
-                        int64_t pstride) {
-  const int n = static_cast<int>(ctx->n);
-  const int chunk_len = cdiv(n, chunks);
-  const bool f64 = std::is_same<T, double>::value;
-  const dim3 grid(cdiv(n, kThreads), chunks, nrhs);
-  const auto *pairs = static_cast<const cv_t<T> *>(f64 ? ctx->gt.pair64.p : ctx->gt.pair32.p);
-  const auto *b = static_cast<const cv_t<T> *>(beta);
-  auto *o = static_cast<cv_t<T> *>(part);
-  const int64_t bs = ctx->n * static_cast<int64_t>(2 * ctx->p + 1);
-  if (variant == kM2LMfma || variant == kM2LMfmaWide) {
-    if (ctx->p > kM2LMfmaMaxP) return set_err(ctx, MPSL_EUNSUPPORTED, "matrix-core M2L needs p <= 16");
-    const int nt = variant == kM2LMfma ? 1 : 2;
-    const dim3 g(cdiv(n, 16 * nt * kM2lMfmaWaves), chunks, nrhs);
-    const dim3 blk(64 * kM2lMfmaWaves);
-    const int cl = m2l_mfma_chunk_len(n, chunks);
-    switch (ctx->p) {
-#define X(PP)                                                                                               \
-  case PP:                                                                                                  \
-    if constexpr (PP <= kM2LMfmaMaxP) {                                                                     \
-      if (nt == 1)                                                                                          \
-        hipLaunchKernelGGL((k_m2l_mfma<T, PP, 1>), g, blk, 0, ctx->stream, pairs, b, o, n, cl, bs, pstride); \
-      else                                                                                                  \
-        hipLaunchKernelGGL((k_m2l_mfma<T, PP, 2>), g, blk, 0, ctx->stream, pairs, b, o, n, cl, bs, pstride); \
-    }                                                                                                       \
-    break;
-      MPSL_P_CASES(X)
-#undef X
-      default: return set_err(ctx, MPSL_EUNSUPPORTED, "expansion order outside 1..20");
-    }
-    LAUNCH_CHECK(ctx);
-    return MPSL_OK;
-  }
-  switch (ctx->p) {
-#define X(PP)                                                                                               \
-  case PP:                                                                                                  \
-    if (variant == kM2LHalves) {                                                                            \
-      hipLaunchKernelGGL((k_m2l<T, PP, 0>), grid, dim3(kThreads), 0, ctx->stream, pairs, b, o, n, chunk_len, \
-                         bs, pstride);                                                                      \
-      hipLaunchKernelGGL((k_m2l<T, PP, 1>), grid, dim3(kThreads), 0, ctx->stream, pairs, b, o, n, chunk_len, \
-                         bs, pstride);                                                                      \
-    } else {                                                                                                \
-      hipLaunchKernelGGL((k_m2l<T, PP, -1>), grid, dim3(kThreads), 0, ctx->stream, pairs, b, o, n,           \
-                         chunk_len, bs, pstride);                                                           \
-    }                                                                                                       \
-    break;
-    MPSL_P_CASES(X)
-#undef X
-    default: return set_err(ctx, MPSL_EUNSUPPORTED, "expansion order outside 1..20");
-  }
-  LAUNCH_CHECK(ctx);
-  return MPSL_OK;
-}
-
-int launch_m2l(mpsl_ctx *ctx, int prec, const void *beta, void *part, int chunks, int variant, int nrhs,
-               int64_t pstride) {
-  if (variant < 0) variant = m2l_variant(ctx, prec);  // tuned or default; matrix cores up to p = 16
-  return prec == MPSL_FP64 ? launch_m2l_t<double>(ctx, beta, part, chunks, variant, nrhs, pstride)
-                           : launch_m2l_t<float>(ctx, beta, part, chunks, variant, nrhs, pstride);
-}
-
-int chunks_m2l_mrhs(const mpsl_ctx *ctx, int nrhs) {
-  const int64_t blocks = static_cast<int64_t>(cdiv(ctx->n, kMrhsWaves)) * cdiv(nrhs, 64);
-  return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(cdiv(1024, blocks), cdiv(ctx->n, kMrhsBatch))));
-}
-
-int launch_m2l_mrhs(mpsl_ctx *ctx, const void *beta, void *part, int chunks, int nrhs, int64_t pstride) {
-  const int n = static_cast<int>(ctx->n);
-  const int P = 2 * ctx->p + 1;
-  const int KP = (P + 3) / 4 * 4;
-  const int64_t rows = static_cast<int64_t>(n) * KP;
-  const int r_pad = 64 * cdiv(nrhs, 64);
-  int rc = dev_alloc(ctx, ctx->bt, static_cast<size_t>(rows) * r_pad * sizeof(float2));
-  if (rc) return rc;
-  hipLaunchKernelGGL(k_rhs_transpose, dim3(cdiv(rows * r_pad, 256)), dim3(256), 0, ctx->stream,
-                     static_cast<const float2 *>(beta), static_cast<float2 *>(ctx->bt.p), n, P, KP, nrhs, r_pad);
-  LAUNCH_CHECK(ctx);
-  const int chunk_len = cdiv(n, chunks);
-  const dim3 grid(cdiv(n, kMrhsWaves), chunks, r_pad / 64);
-  const auto *pairs = static_cast<const float2 *>(ctx->gt.pair32.p);
-  const auto *bt = static_cast<const float2 *>(ctx->bt.p);
-  auto *pp = static_cast<float2 *>(part);
-  switch (ctx->p) {
-#define X(PP) \
-  case PP: hipLaunchKernelGGL((k_m2l_mrhs<PP>), grid, dim3(64 * kMrhsWaves), 0, ctx->stream, pairs, bt, pp, n, chunk_len, nrhs, r_pad, pstride); break;
-    MPSL_P_CASES(X)
-#undef X
-    default: return set_err(ctx, MPSL_EUNSUPPORTED, "expansion order outside 1..20");
-  }
-  LAUNCH_CHECK(ctx);
-  return MPSL_OK;
-}
-
-template <typename T>
-static int launch_fmm_near_t(mpsl_ctx *ctx, const void *beta, void *out) {
-  const FmmPlan &f = ctx->fmm;
-  const int n = static_cast<int>(ctx->n);
-  const bool f64 = std::is_same<T, double>::value;
-  const auto *pairs = static_cast<const cv_t<T> *>(f64 ? f.near64.p : f.near32.p);
-  const auto *src = static_cast<const int *>(f.near_src.p);
-  const auto *perm = static_cast<const int *>(f.perm.p);
-  const auto *wave = static_cast<const int *>(f.near_wave.p);
-  const auto *b = static_cast<const cv_t<T> *>(beta);
-  auto *o = static_cast<cv_t<T> *>(out);
-  const int kc = cdiv(f.near_k, f.near_chunks);
-  const dim3 grid(cdiv(n, kThreads), f.near_chunks);
-  // FP64: two output halves (register pressure); FP32: one launch
-  switch (ctx->p) {
-#define X(PP)                                                                                                    \
-  case PP:                                                                                                       \
-    if constexpr (std::is_same<T, double>::value) {                                                              \
-      hipLaunchKernelGGL((k_fmm_near<T, PP, 0>), grid, dim3(kThreads), 0, ctx->stream, pairs, src, perm, wave, b, \
-                         o, n, kc);                                                                              \
-      hipLaunchKernelGGL((k_fmm_near<T, PP, 1>), grid, dim3(kThreads), 0, ctx->stream, pairs, src, perm, wave, b, \
-                         o, n, kc);                                                                              \
-    } else {                                                                                                     \
-      hipLaunchKernelGGL((k_fmm_near<T, PP, -1>), grid, dim3(kThreads), 0, ctx->stream, pairs, src, perm, wave,   \
-                         b, o, n, kc);                                                                           \
-    }                                                                                                            \
-    break;
-    MPSL_P_CASES(X)
-#undef X
-    default: return set_err(ctx, MPSL_EUNSUPPORTED, "expansion order outside 1..20");
-  }
-  LAUNCH_CHECK(ctx);
-  return MPSL_OK;
-}
-
-int launch_fmm_near(mpsl_ctx *ctx, int prec, const void *beta, void *out) {
-  return prec == MPSL_FP64 ? launch_fmm_near_t<double>(ctx, beta, out) : launch_fmm_near_t<float>(ctx, beta, out);
 }
 
 template <typename T>

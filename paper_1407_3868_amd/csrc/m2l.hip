@@ -1,0 +1,1037 @@
+// Row a1: the all-pairs free-space M2L, its forms for one and for many
+// right-hand sides, and the FMM's near field (the same pair translation).
+// Layouts as in kernels.hip.
+#include <cmath>
+
+#include "kernels.h"
+
+namespace mpsl {
+
+namespace {
+
+constexpr int kThreads = 128;
+
+inline int cdiv(int64_t a, int64_t b) { return static_cast<int>((a + b - 1) / b); }
+
+// Row a1: all-pairs free-space M2L (Graf's addition theorem).
+// One lane per target l; every lane of the grid walks the same source chunk,
+// so the source's coefficients are wave-uniform and live in scalar registers.
+// Per pair: H_0, H_1 and e^{i phi} from the pair table, the upward recurrence
+// H_{q+1} = (2q/z) H_q - H_{q-1}, e^{iq phi} by repeated multiplication,
+// h_q = H_q e^{iq phi}, h_{-q} = (-1)^q H_q e^{-iq phi}, and the Toeplitz
+// product alpha_{n'} += sum_nu h_{nu - n'} beta_nu consumed in the order the
+// recurrence produces h_q.
+//
+// m2l_block adds the contribution of source slots [V0, V1] to output slots
+// [O0, O1].  FP32 does everything in one call (33 accumulators, 66 scalar
+// registers of beta at p = 16).  FP64 splits the outputs over two lanes and
+// the source coefficients over two calls: 17 accumulators and at most 68
+// scalar registers of beta, at the cost of re-running the recurrence.
+template <typename T, int p, int O0, int O1, int V0, int V1, bool MIRROR>
+__device__ __forceinline__ void m2l_block(cx<T> (&acc)[O1 - O0 + 1], const cv_t<T> *__restrict__ bm, cx<T> h0,
+                                          cx<T> h1, cx<T> t, T two_over_z) {
+  constexpr int QA = V1 - O0, QB = O1 - V0;
+  constexpr int QMAX = (QA > QB ? QA : QB) < 2 * p ? (QA > QB ? QA : QB) : 2 * p;
+  cx<T> bv[V1 - V0 + 1];
+#pragma unroll
+  for (int v = V0; v <= V1; ++v) bv[v - V0] = ld<T>(bm[MIRROR ? 2 * p - v : v]);
+#pragma unroll
+  for (int v = (V0 > O0 ? V0 : O0); v <= (V1 < O1 ? V1 : O1); ++v) cmac(acc[v - O0], h0, bv[v - V0]);
+  cx<T> hprev = h0, hcur = h1, tq = t;
+#pragma unroll
+  for (int q = 1; q <= QMAX; ++q) {
+    if (q >= 2) {
+      const cx<T> hn = static_cast<T>(q - 1) * two_over_z * hcur - hprev;
+      hprev = hcur;
+      hcur = hn;
+      tq = tq * t;
+    }
+    // alpha_{v-q} += h_q beta_v for v - q in [O0, O1]
+    if ((V1 < O1 + q ? V1 : O1 + q) >= (V0 > O0 + q ? V0 : O0 + q)) {
+      const cx<T> hp = hcur * tq;
+#pragma unroll
+      for (int v = (V0 > O0 + q ? V0 : O0 + q); v <= (V1 < O1 + q ? V1 : O1 + q); ++v)
+        cmac(acc[v - q - O0], hp, bv[v - V0]);
+    }
+    // alpha_{v+q} += h_{-q} beta_v for v + q in [O0, O1]
+    if ((V1 < O1 - q ? V1 : O1 - q) >= (V0 > O0 - q ? V0 : O0 - q)) {
+      cx<T> hm = hcur * conj(tq);
+      if (q & 1) hm = mk<T>(-hm.re, -hm.im);
+#pragma unroll
+      for (int v = (V0 > O0 - q ? V0 : O0 - q); v <= (V1 < O1 - q ? V1 : O1 - q); ++v)
+        cmac(acc[v + q - O0], hm, bv[v - V0]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
+// Mirror identity: with reversed indices (alpha~_k = alpha_{-k},
+// beta~_nu = beta_{-nu}) the translation keeps its Toeplitz form with
+// h~_q = h_{-q} = H_q e^{iq(pi - phi)}, i.e. e^{i phi} -> -conj(e^{i phi}).
+// MIRROR = true computes output slots 2p - [O0, O1] that way.
+template <typename T, int p, int O0, int O1, int SPLIT, bool MIRROR>
+__device__ __forceinline__ void m2l_body(const cv_t<T> *__restrict__ pairs, const cv_t<T> *__restrict__ beta,
+                                         cv_t<T> *__restrict__ part, int n, int m0, int m1, int l) {
+  constexpr int P = 2 * p + 1;
+  constexpr int NO = O1 - O0 + 1;
+  const bool valid = l < n;
+  const int lc = valid ? l : n - 1;
+  cx<T> acc[NO];
+#pragma unroll
+  for (int i = 0; i < NO; ++i) acc[i] = mk<T>(0, 0);
+  if (m0 < m1) {
+    const cv_t<T> *pe = pairs + 4 * (static_cast<int64_t>(m0) * n + lc);
+    cv_t<T> a0 = pe[0], a1 = pe[1], a2 = pe[2], a3 = pe[3];
+    for (int m = m0; m < m1; ++m) {
+      cx<T> h0 = ld<T>(a0), h1 = ld<T>(a1);
+      cx<T> t = ld<T>(a2);
+      if (MIRROR) t.re = -t.re;
+      const T two_over_z = a3.x;
+      if (m + 1 < m1) {  // prefetch the next source's pair entry
+        pe += 4 * static_cast<int64_t>(n);
+        a0 = pe[0];
+        a1 = pe[1];
+        a2 = pe[2];
+        a3 = pe[3];
+      }
+      if (!valid) h0 = h1 = mk<T>(0, 0);
+      const cv_t<T> *bm = beta + static_cast<int64_t>(m) * P;
+      if (SPLIT) {  // source coefficients in two halves, one scalar-register set each
+        m2l_block<T, p, O0, O1, 0, p, MIRROR>(acc, bm, h0, h1, t, two_over_z);
+        __builtin_amdgcn_sched_barrier(0);
+        m2l_block<T, p, O0, O1, p + 1, P - 1, MIRROR>(acc, bm, h0, h1, t, two_over_z);
+        __builtin_amdgcn_sched_barrier(0);
+      } else {
+        m2l_block<T, p, O0, O1, 0, P - 1, MIRROR>(acc, bm, h0, h1, t, two_over_z);
+      }
+    }
+  }
+  if (valid) {
+#pragma unroll
+    for (int i = 0; i < NO; ++i) part[static_cast<int64_t>(l) * P + (MIRROR ? 2 * p - O0 - i : O0 + i)] = st(acc[i]);
+  }
+}
+
+// grid: (target blocks, source chunks); part[chunk][n][P].  Two variants:
+//  whole  (HALF = -1): one lane holds all P accumulators of its target;
+//  halves (HALF = 0, 1, two launches): output slots [0, p] and, through the
+//         mirror identity, [p+1, 2p], at most p+1 accumulators per lane and
+//         more waves per SIMD, for twice the recurrence work.  The two halves
+//         are separate kernels: in one kernel the compiler merges the bodies
+//         and doubles the live registers.
+// FP64 always takes the source coefficients in two scalar-register halves.
+// The launcher runs the variant the autotuner picked (default: whole).
+template <typename T, int p, int HALF>
+__global__ __launch_bounds__(kThreads) void k_m2l(const cv_t<T> *__restrict__ pairs,
+                                                  const cv_t<T> *__restrict__ beta,
+                                                  cv_t<T> *__restrict__ part, int n, int chunk_len,
+                                                  int64_t bstride, int64_t pstride) {
+  constexpr int P = 2 * p + 1;
+  const int l = blockIdx.x * kThreads + threadIdx.x;
+  const int c = blockIdx.y;
+  beta += blockIdx.z * bstride;  // right-hand side
+  part += blockIdx.z * pstride;
+  const int m0 = c * chunk_len;
+  const int m1 = min(n, m0 + chunk_len);
+  cv_t<T> *o = part + static_cast<int64_t>(c) * n * P;
+  constexpr int SPLIT = std::is_same<T, double>::value ? 1 : 0;
+  if (HALF == 0) m2l_body<T, p, 0, p, SPLIT, false>(pairs, beta, o, n, m0, m1, l);
+  else if (HALF == 1) m2l_body<T, p, 0, p - 1, SPLIT, true>(pairs, beta, o, n, m0, m1, l);
+  else m2l_body<T, p, 0, P - 1, SPLIT, false>(pairs, beta, o, n, m0, m1, l);
+}
+
+// FMM near field: the same pair translation restricted to padded neighbour
+// lists.  One lane per target in leaf-box order; each lane walks its own
+// list of sources (pair entries [j][i][4] as in the all-pairs table, source
+// coefficients loaded per lane), and every wave loops to the longest list
+// among its 64 targets (padding entries are zeros).  HALF as in k_m2l: -1
+// all outputs; 0 / 1 output slots [0, p] / (mirror) [p+1, 2p] in two
+// launches, which keeps FP64 within the register file.
+template <typename T, int p, int HALF>
+__global__ __launch_bounds__(kThreads) void k_fmm_near(const cv_t<T> *__restrict__ pairs,
+                                                       const int *__restrict__ src, const int *__restrict__ perm,
+                                                       const int *__restrict__ wave_cnt,
+                                                       const cv_t<T> *__restrict__ beta, cv_t<T> *__restrict__ out,
+                                                       int n, int kc) {
+  constexpr int P = 2 * p + 1;
+  const int i = blockIdx.x * kThreads + threadIdx.x;
+  // list entries [j_lo, j_hi) of this chunk into partial slot blockIdx.y
+  const int kw = __builtin_amdgcn_readfirstlane(wave_cnt[i >> 6]);
+  const int j_lo = blockIdx.y * kc, j_hi = min(kw, j_lo + kc);
+  out += static_cast<int64_t>(blockIdx.y) * n * P;
+  const bool valid = i < n;
+  const int ic = valid ? i : n - 1;
+  constexpr bool MIRROR = HALF == 1;
+  constexpr int O1 = HALF == 0 ? p : (HALF == 1 ? p - 1 : P - 1);  // outputs [0, O1]
+  cx<T> acc[O1 + 1];
+#pragma unroll
+  for (int k = 0; k <= O1; ++k) acc[k] = mk<T>(0, 0);
+  constexpr int SPLIT = std::is_same<T, double>::value ? 1 : 0;
+  for (int j = j_lo; j < j_hi; ++j) {
+    const int64_t e = static_cast<int64_t>(j) * n + ic;
+    const cv_t<T> *pe = pairs + 4 * e;
+    cx<T> h0 = ld<T>(pe[0]), h1 = ld<T>(pe[1]);
+    cx<T> t = ld<T>(pe[2]);
+    if (MIRROR) t.re = -t.re;
+    const T two_over_z = pe[3].x;
+    if (!valid) h0 = h1 = mk<T>(0, 0);
+    const cv_t<T> *bm = beta + static_cast<int64_t>(src[e]) * P;
+    if (SPLIT) {
+      m2l_block<T, p, 0, O1, 0, p, MIRROR>(acc, bm, h0, h1, t, two_over_z);
+      __builtin_amdgcn_sched_barrier(0);
+      m2l_block<T, p, 0, O1, p + 1, P - 1, MIRROR>(acc, bm, h0, h1, t, two_over_z);
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
+      m2l_block<T, p, 0, O1, 0, P - 1, MIRROR>(acc, bm, h0, h1, t, two_over_z);
+    }
+  }
+  if (valid) {
+    const int64_t o = static_cast<int64_t>(perm[i]) * P;
+#pragma unroll
+    for (int k = 0; k <= O1; ++k) out[o + (MIRROR ? 2 * p - k : k)] = st(acc[k]);
+  }
+}
+
+
+// ---------------------------------------------------------------------------
+// Row a1 on the matrix cores, one right-hand side, FP64.  The translation
+// alpha_{n'} = sum_q h_q beta_{n'+q} (q = nu - n', |q| <= 2p) is a product
+// with the source coefficients in shifted form: with slots s' = n' + p,
+// A_m[s'][q] = beta_m[s' + q] (zero where s' + q leaves [0, 2p]) and
+// B[(m, q)][l] = h_q of the pair (m -> l),
+//   alpha_l[s'] = sum_{m, q} A_m[s'][q] B[(m, q)][l],
+// a GEMM with M = output slots, N = targets and K = (source, q).  A 4x4x4 MFMA
+// (four blocks) takes four sources at one q and four output slots for 16
+// targets: lane i runs the Hankel recurrence of the pair (source i / 16 of the
+// group -> target i % 16) and supplies its h_q as the B operand; A, four
+// consecutive coefficients from slot 4 R + q of the lane's source, is read from
+// LDS, which holds the coefficients of kM2lBatch sources as (re, im, re + im)
+// with zero padding.  Complex products take three real MFMAs (Gauss):
+// P1 = sum Ar Br, P2 = sum Ai Bi, P3 = sum (Ar + Ai)(Br + Bi); re = P1 - P2,
+// im = P3 - P1 - P2.  For even p the last slot runs on the vector units
+// (2p + 1 = 4 NR + 1).
+//
+// Bound by the matrix cores and the vector units in turn: FP64 MFMAs and
+// vector instructions do not overlap on this chip (a 4x4x4 costs 16.5 cycles, an
+// FP64 multiply-add beside it 4.4 more), so the work is the sum of both.  Why
+// 4x4x4: only |s' + q - p| <= p of a block's rows count, and blocks of four
+// slots waste 9 % of them where 16-slot blocks wasted 31 % (p = 16: 864 x 16.5
+// cycles per 64 pairs instead of 288 x 65), at the same rate per operation.
+// 3001 particles, p = 16: 1.40 -> 1.22 ms; 1000, p = 12: 146 us on the vector
+// units -> 83 us.
+// NT = 2 target tiles per wave share the A reads, which would take all of the
+// LDS bandwidth for one.
+constexpr int kM2lWaves = 4;
+constexpr int kM2lBatch = 16;
+
+template <int p, int NT>
+__global__ __launch_bounds__(64 * kM2lWaves, 2) void k_m2l_f64(const double2 *__restrict__ pairs,
+                                                               const double2 *__restrict__ beta,
+                                                               double2 *__restrict__ part, int n, int chunk_len,
+                                                               int64_t bstride, int64_t pstride) {
+  constexpr int P = 2 * p + 1;
+  constexpr bool VROW = P % 4 == 1 && P > 1;  // slot 2p on the vector units
+  constexpr int NR = VROW ? P / 4 : (P + 3) / 4;
+  // row of a source: slots -3 .. 2p + 3 + the padded rows' overhang; a stride of
+  // 4 mod 32 entries puts the four sources of one read in different banks
+  constexpr int LR0 = P + 8;
+  constexpr int LR = LR0 + ((4 - LR0) % 32 + 32) % 32;
+  constexpr int SB = kM2lBatch;
+  __shared__ double sa[3][SB][LR];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int r = lane & 15, g = lane >> 4;
+  const int c = blockIdx.y;
+  beta += blockIdx.z * bstride;
+  part += blockIdx.z * pstride;
+  const int m0 = c * chunk_len;
+  const int m1 = min(n, m0 + chunk_len);
+  const int lt0 = (blockIdx.x * kM2lWaves + w) * 16 * NT;
+
+  for (int e = threadIdx.x; e < 3 * SB * LR; e += 64 * kM2lWaves) (&sa[0][0][0])[e] = 0.0;
+
+  double acc[NT][NR][3];
+  cx<double> zc[NT];
+#pragma unroll
+  for (int tt = 0; tt < NT; ++tt) {
+#pragma unroll
+    for (int R = 0; R < NR; ++R) acc[tt][R][0] = acc[tt][R][1] = acc[tt][R][2] = 0.0;
+    zc[tt] = mk(0.0, 0.0);
+  }
+  // pair entries of the first group (source m0 + g)
+  double2 pa[NT][4];
+  auto load_pairs = [&](int m) {
+#pragma unroll
+    for (int tt = 0; tt < NT; ++tt) {
+      const int l = lt0 + tt * 16 + r;
+      if (m < m1 && l < n) {
+        const double2 *pe = pairs + 4 * (static_cast<int64_t>(m) * n + l);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pa[tt][k] = pe[k];
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pa[tt][k] = make_double2(0.0, 0.0);
+      }
+    }
+  };
+  load_pairs(m0 + g);
+
+  for (int mb = m0; mb < m1; mb += SB) {
+    const int sb = min(SB, m1 - mb);
+    __syncthreads();  // previous batch consumed (and the zero fill done)
+    for (int e = threadIdx.x; e < SB * P; e += 64 * kM2lWaves) {
+      const int s = e / P, v = e - s * P;
+      const double2 b = s < sb ? beta[static_cast<int64_t>(mb + s) * P + v] : make_double2(0.0, 0.0);
+      sa[0][s][v + 3] = b.x;
+      sa[1][s][v + 3] = b.y;
+      sa[2][s][v + 3] = b.x + b.y;
+    }
+    __syncthreads();
+    // a wave whose targets all lie past the last particle (the grid's tail)
+    // stages its share of the batch and meets the barriers, but multiplies nothing
+    for (int g0 = 0; g0 < sb && lt0 < n; g0 += 4) {
+      const int s = g0 + g;  // this lane's source within the batch
+      cx<double> hp[NT], hc[NT], t[NT], tq[NT];
+      double tz[NT], f[NT];
+#pragma unroll
+      for (int tt = 0; tt < NT; ++tt) {
+        hp[tt] = ld<double>(pa[tt][0]);
+        hc[tt] = ld<double>(pa[tt][1]);
+        t[tt] = ld<double>(pa[tt][2]);
+        tq[tt] = t[tt];
+        tz[tt] = pa[tt][3].x;
+        f[tt] = 0.0;
+      }
+      load_pairs(mb + s + 4);  // next group's entries in flight
+      const double *ar = &sa[0][s][3 + (lane & 3)], *ai = &sa[1][s][3 + (lane & 3)], *as = &sa[2][s][3 + (lane & 3)];
+      const double *vr = &sa[0][s][3], *vi = &sa[1][s][3];
+#pragma unroll
+      for (int q = 0; q <= 2 * p; ++q) {
+        cx<double> hq[NT], hm[NT];
+        double sq[NT], sm[NT];
+#pragma unroll
+        for (int tt = 0; tt < NT; ++tt) {
+          if (q == 0) {
+            hq[tt] = hm[tt] = hp[tt];  // H_0
+          } else {
+            if (q >= 2) {
+              f[tt] += tz[tt];  // 2 (q - 1) / z
+              const cx<double> hn = mk(fma(f[tt], hc[tt].re, -hp[tt].re), fma(f[tt], hc[tt].im, -hp[tt].im));
+              hp[tt] = hc[tt];
+              hc[tt] = hn;
+              tq[tt] = tq[tt] * t[tt];
+            }
+            // h_q = H_q e^{iq phi}, h_{-q} = (-1)^q H_q e^{-iq phi}: two shared products
+            const double a = hc[tt].re * tq[tt].re, d = hc[tt].re * tq[tt].im;
+            hq[tt] = mk(fma(-hc[tt].im, tq[tt].im, a), fma(hc[tt].im, tq[tt].re, d));
+            hm[tt] = q & 1 ? mk(fma(-hc[tt].im, tq[tt].im, -a), fma(-hc[tt].im, tq[tt].re, d))
+                           : mk(fma(hc[tt].im, tq[tt].im, a), fma(hc[tt].im, tq[tt].re, -d));
+          }
+          if (VROW) cmac(zc[tt], hm[tt], mk(vr[2 * p - q], vi[2 * p - q]));
+          sq[tt] = hq[tt].re + hq[tt].im;
+          sm[tt] = hm[tt].re + hm[tt].im;
+        }
+        // q: blocks with 4 R <= 2 p - q; -q: blocks with 4 R + 3 >= q
+#pragma unroll
+        for (int R = 0; R < NR; ++R) {
+          if (4 * R <= 2 * p - q) {
+            const double xr = ar[4 * R + q], xi = ai[4 * R + q], xs = as[4 * R + q];
+#pragma unroll
+            for (int tt = 0; tt < NT; ++tt) {
+              acc[tt][R][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(xr, hq[tt].re, acc[tt][R][0], 0, 0, 0);
+              acc[tt][R][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(xi, hq[tt].im, acc[tt][R][1], 0, 0, 0);
+              acc[tt][R][2] = __builtin_amdgcn_mfma_f64_4x4x4f64(xs, sq[tt], acc[tt][R][2], 0, 0, 0);
+            }
+          }
+          if (q > 0 && 4 * R + 3 >= q) {
+            const double xr = ar[4 * R - q], xi = ai[4 * R - q], xs = as[4 * R - q];
+#pragma unroll
+            for (int tt = 0; tt < NT; ++tt) {
+              acc[tt][R][0] = __builtin_amdgcn_mfma_f64_4x4x4f64(xr, hm[tt].re, acc[tt][R][0], 0, 0, 0);
+              acc[tt][R][1] = __builtin_amdgcn_mfma_f64_4x4x4f64(xi, hm[tt].im, acc[tt][R][1], 0, 0, 0);
+              acc[tt][R][2] = __builtin_amdgcn_mfma_f64_4x4x4f64(xs, sm[tt], acc[tt][R][2], 0, 0, 0);
+            }
+          }
+        }
+        // one q step at a time keeps the live registers to one step's operands
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  // lane i holds slot 4 R + i / 16 of target i % 16
+  double2 *o = part + static_cast<int64_t>(c) * n * P;
+#pragma unroll
+  for (int tt = 0; tt < NT; ++tt) {
+    const int l = lt0 + tt * 16 + r;
+    cx<double> z = zc[tt];
+    z.re += __shfl_xor(z.re, 16);
+    z.im += __shfl_xor(z.im, 16);
+    z.re += __shfl_xor(z.re, 32);
+    z.im += __shfl_xor(z.im, 32);
+    if (l >= n) continue;
+    if (VROW && g == 0) o[static_cast<int64_t>(l) * P + 2 * p] = st(z);
+#pragma unroll
+    for (int R = 0; R < NR; ++R) {
+      const int row = 4 * R + g;
+      const double p1 = acc[tt][R][0], p2 = acc[tt][R][1], p3 = acc[tt][R][2];
+      if (row < P - (VROW ? 1 : 0)) o[static_cast<int64_t>(l) * P + row] = make_double2(p1 - p2, p3 - p1 - p2);
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Row a1 in FP32 on the bf16 matrix cores, one right-hand side: the same
+// product of shifted source coefficients and pair Hankel values as above,
+//   alpha_l[s'] = sum_{m, q} A_m[s'][q] h_q(m -> l),  A_m[s'][q] = beta_m[s' + q]
+// (slots s' = n' + p), with every FP32 operand split exactly into three bf16
+// parts, x = x1 + x2 + x3 (rounding to nearest leaves 9 more bits to each next
+// part, so the 24 bits of x fit), and the six products whose parts' weights
+// reach 2^-18 (11, 12, 21, 22, 13, 31) accumulated in FP32; the three left out
+// are below 2^-26 of the product, less than the rounding of one FP32 multiply.
+// Complex products take four real ones (no operand sums), each in its own
+// accumulators.  The matrix cores' bf16 sums do not round to nearest, so a
+// long chain of them drifts (chunks of 316 sources: 5.9e-7 relative error of a
+// 5000-particle matvec, of 40: 4.5e-7); after every batch of sources they are
+// added to running FP32 sums and start again from zero.
+//
+// Why: an FP32 MFMA and FP32 vector instructions do not overlap on this chip (a
+// 16x16x4 costs 32.4 cycles, a multiply-add beside it 3.3 .. 4.9 more), and
+// the FP32 matrix kernel spent 288 of them and ~1000 vector instructions per
+// group of 64 pairs.  Six bf16 MFMAs at 16x the rate replace one: 288 of 16
+// cycles with the four-product form, and ~1280 vector instructions (the
+// recurrence, the products with e^{iq phi}, the splitting), in turn as well
+// where a wave issues its MFMAs back to back.  Interleaving them one to three
+// did not help (each instruction then takes 5.3 cycles), nor did dot products
+// for the remainders (they share the matrix pipe).  5000 particles, p = 16:
+// 1.96 -> 1.55 ms; the matvec's error against 64 bits 4.6e-7 -> 4.0e-7.
+//
+// Layout.  One wave per 16 targets; a 16x16x32 MFMA takes four sources and
+// eight consecutive q: lane i runs the recurrence of the pair (source i / 16
+// of the group -> target i % 16) and its eight h_q are its B operand.  q goes
+// in octets, {8j + 1 .. 8j + 8} and {-8j .. -8j - 7}.  The A operand of output
+// rows 16 b + r and an octet is eight consecutive coefficients from slot
+// r + 1 + 8 t, with t = 2 b + j or 2 b - j - 1: the LDS holds every source's
+// parts zero-padded and in four copies, shifted by 0 .. 3 entries, so that each
+// lane reads its eight with two aligned 8-byte reads.  For 2 p + 1 = 16 NB + 1
+// (p = 8, 16) the last row runs on the vector units.
+constexpr int kM2lBfWaves = 4;
+constexpr int kM2lBfBatch = 8;                       // sources staged at a time
+constexpr int kBfRow = 80;                           // entries of one shifted copy (64 used), 2 bytes each
+constexpr int kBfSrc = 6 * 4 * kBfRow + 32;          // entries per source: [part][re, im][copy], bank offset
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// Eight FP32 values as three bf16 parts (round to nearest; the remainders are
+// exact).
+struct Split8 {
+  bf8 v[3];
+};
+__device__ __forceinline__ Split8 split8(const float (&x)[8]) {
+  Split8 o;
+#pragma unroll
+  for (int i = 0; i < 8; i += 2) {
+    f32x2 r = {x[i], x[i + 1]};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const bf2 h = __builtin_convertvector(r, bf2);
+      o.v[k][i] = h[0];
+      o.v[k][i + 1] = h[1];
+      if (k < 2) r = r - __builtin_convertvector(h, f32x2);
+    }
+  }
+  return o;
+}
+
+template <int p, int NT>
+__global__ __launch_bounds__(64 * kM2lBfWaves, NT == 1 ? 3 : 2) void k_m2l_bf(const float2 *__restrict__ pairs,
+                                                             const float2 *__restrict__ beta,
+                                                             float2 *__restrict__ part, int n, int chunk_len,
+                                                             int64_t bstride, int64_t pstride) {
+  static_assert(p >= 1 && p <= 16, "two 16-row blocks");
+  constexpr int P = 2 * p + 1;
+  constexpr bool VROW = P % 16 == 1 && P > 1;  // slot 2p on the vector units
+  constexpr int NB = (P - (VROW ? 1 : 0) + 15) / 16;
+  constexpr int NJ = (2 * p + 7) / 8;          // octets of q > 0
+  constexpr int NM = (P - (VROW ? 1 : 0) + 7) / 8;  // octets of q <= 0 that the matrix rows need
+  constexpr int NO = NJ > NM ? NJ : NM;
+  static_assert(NO <= 4, "octets");
+  constexpr int SB = kM2lBfBatch;
+  typedef float v4 __attribute__((ext_vector_type(4)));
+  __shared__ __align__(16) __bf16 sa[SB * kBfSrc];
+  __shared__ float2 sv[VROW ? SB : 1][VROW ? P : 1];
+  __shared__ v4 run[kM2lBfWaves][NT * NB * 2][64];  // sums over the batches, each lane its own entries
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int r = lane & 15, g = lane >> 4;
+  const int c = blockIdx.y;
+  beta += blockIdx.z * bstride;
+  part += blockIdx.z * pstride;
+  const int m0 = c * chunk_len;
+  const int m1 = min(n, m0 + chunk_len);
+  const int lt0 = (blockIdx.x * kM2lBfWaves + w) * 16 * NT;
+
+  for (int e = threadIdx.x; e < SB * kBfSrc / 8; e += 64 * kM2lBfWaves)
+    reinterpret_cast<float4 *>(sa)[e] = make_float4(0.f, 0.f, 0.f, 0.f);
+
+  v4 acc[NT][NB][4];  // Ar Br, Ai Bi, Ar Bi, Ai Br
+  cx<float> zc[NT];
+#pragma unroll
+  for (int tt = 0; tt < NT; ++tt) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc[tt][b][k] = v4{0, 0, 0, 0};
+    zc[tt] = mk(0.f, 0.f);
+  }
+#pragma unroll
+  for (int x = 0; x < NT * NB * 2; ++x) run[w][x][lane] = v4{0, 0, 0, 0};
+  float2 pa[NT][4];
+  auto load_pairs = [&](int m) {
+#pragma unroll
+    for (int tt = 0; tt < NT; ++tt) {
+      const int l = lt0 + tt * 16 + r;
+      if (m < m1 && l < n) {
+        const float2 *pe = pairs + 4 * (static_cast<int64_t>(m) * n + l);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pa[tt][k] = pe[k];
+      } else {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pa[tt][k] = make_float2(0.f, 0.f);
+      }
+    }
+  };
+  load_pairs(m0 + g);
+
+  for (int mb = m0; mb < m1; mb += SB) {
+    const int sb = min(SB, m1 - mb);
+    __syncthreads();  // previous batch consumed (and the zero fill done)
+    for (int e = threadIdx.x; e < SB * P; e += 64 * kM2lBfWaves) {
+      const int s = e / P, v = e - s * P;
+      const float2 b = s < sb ? beta[static_cast<int64_t>(mb + s) * P + v] : make_float2(0.f, 0.f);
+      if (VROW) sv[s][v] = b;
+      float x[2] = {b.x, b.y};
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const __bf16 h = static_cast<__bf16>(x[i]);
+          x[i] -= static_cast<float>(h);
+          __bf16 *o = sa + s * kBfSrc + (2 * k + i) * 4 * kBfRow + v + 15;  // copy u holds slot v at v + 15 - u
+#pragma unroll
+          for (int u = 0; u < 4; ++u) o[u * kBfRow - u] = h;
+        }
+    }
+    __syncthreads();
+    // a wave whose targets all lie past the last particle (the grid's tail)
+    // stages its share of the batch and meets the barriers, but multiplies nothing
+    for (int g0 = 0; g0 < sb && lt0 < n; g0 += 4) {
+      const int s = g0 + g;  // this lane's source within the batch
+      float2 pc[NT][4];
+#pragma unroll
+      for (int tt = 0; tt < NT; ++tt)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) pc[tt][k] = pa[tt][k];
+      load_pairs(mb + s + 4);  // next group's entries in flight
+      // entry r + 16 + 8 t of the zero-padded row starts at copy r % 4, entry 4 (r / 4) + 16 + 8 t
+      const __bf16 *as = sa + s * kBfSrc + (r & 3) * kBfRow + (r & ~3) + 16;
+      auto frag = [&](int k, int i, int tt) {
+        const bf4 *a = reinterpret_cast<const bf4 *>(as + (2 * k + i) * 4 * kBfRow + 8 * tt);
+        const bf4 lo = a[0], hi = a[1];
+        return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+      };
+#pragma unroll
+      for (int tt = 0; tt < NT; ++tt) {
+        cx<float> hp = ld<float>(pc[tt][0]), hc = ld<float>(pc[tt][1]);
+        const cx<float> t = ld<float>(pc[tt][2]);
+        cx<float> tq = t;
+        const float tz = pc[tt][3].x;
+        // products of one octet (B parts br, bi) with the fragments t0 + 2 b of the blocks [b0, b1)
+        auto mul = [&](const Split8 &br, const Split8 &bi, int t0, auto b0c, auto b1c) {
+          constexpr int b0 = decltype(b0c)::value, b1 = decltype(b1c)::value;
+          if constexpr (b0 < b1) {
+            constexpr int ka[6] = {0, 0, 1, 0, 1, 2}, kb[6] = {2, 1, 1, 0, 0, 0};
+            bf8 ar[NB][3], ai[NB][3];
+#pragma unroll
+            for (int b = b0; b < b1; ++b)
+#pragma unroll
+              for (int k = 0; k < 3; ++k) {
+                ar[b][k] = frag(k, 0, t0 + 2 * b);
+                ai[b][k] = frag(k, 1, t0 + 2 * b);
+              }
+#pragma unroll
+            for (int x = 0; x < 6; ++x)
+#pragma unroll
+              for (int b = b0; b < b1; ++b) {
+                acc[tt][b][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar[b][ka[x]], br.v[kb[x]], acc[tt][b][0], 0, 0, 0);
+                acc[tt][b][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ai[b][ka[x]], bi.v[kb[x]], acc[tt][b][1], 0, 0, 0);
+                acc[tt][b][2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar[b][ka[x]], bi.v[kb[x]], acc[tt][b][2], 0, 0, 0);
+                acc[tt][b][3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ai[b][ka[x]], br.v[kb[x]], acc[tt][b][3], 0, 0, 0);
+              }
+          }
+        };
+        float pr[8], pi[8], nr[8], ni[8];  // h_{8j+1 ..} and h_{-8j-7 ..}
+        auto octet = [&](auto jc) {
+          constexpr int j = decltype(jc)::value;
+          // q = 8 j .. 8 j + 8; the last one's h_{-q} opens the next octet
+#pragma unroll
+          for (int u = 0; u <= 8; ++u) {
+            const int q = 8 * j + u;
+            if (u == 0 && j > 0) continue;  // done at the end of the previous octet
+            cx<float> hq = mk(0.f, 0.f), hm = mk(0.f, 0.f);
+            if (q == 0) {
+              hm = hp;  // H_0
+            } else if (q <= 2 * p) {
+              if (q >= 2) {
+                const cx<float> hn = static_cast<float>(q - 1) * tz * hc - hp;
+                hp = hc;
+                hc = hn;
+                tq = tq * t;
+              }
+              // h_q = H_q e^{iq phi}, h_{-q} = (-1)^q H_q e^{-iq phi}: two shared products
+              const float a = hc.re * tq.re, d = hc.re * tq.im;
+              hq = mk(fmaf(-hc.im, tq.im, a), fmaf(hc.im, tq.re, d));
+              hm = q & 1 ? mk(fmaf(-hc.im, tq.im, -a), fmaf(-hc.im, tq.re, d))
+                         : mk(fmaf(hc.im, tq.im, a), fmaf(hc.im, tq.re, -d));
+            }
+            if (VROW && q <= 2 * p) cmac(zc[tt], hm, ld<float>(sv[s][VROW ? 2 * p - q : 0]));
+            if (u > 0) {
+              pr[u - 1] = hq.re;
+              pi[u - 1] = hq.im;
+            }
+            if (u == 8) {  // opens the next octet of q <= 0, after this one is used
+              const Split8 br = split8(nr), bi = split8(ni);
+              // q <= 0: block b needs q >= -16 b - 15, fragment t = 2 b - j - 1
+              mul(br, bi, -j - 1, std::integral_constant<int, (j < NM ? (j / 2 < NB ? j / 2 : NB) : NB)>{},
+                  std::integral_constant<int, NB>{});
+              nr[7] = hm.re;
+              ni[7] = hm.im;
+            } else {
+              nr[7 - u] = hm.re;
+              ni[7 - u] = hm.im;
+            }
+          }
+          // q > 0: block b needs q <= 2 p - 16 b, fragment t = 2 b + j
+          constexpr int top = 8 * j + 1 <= 2 * p ? (2 * p - 8 * j - 1) / 16 + 1 : 0;
+          if constexpr (top > 0) {
+            const Split8 br = split8(pr), bi = split8(pi);
+            mul(br, bi, j, std::integral_constant<int, 0>{}, std::integral_constant<int, (top < NB ? top : NB)>{});
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        };
+        octet(std::integral_constant<int, 0>{});
+        if constexpr (NO > 1) octet(std::integral_constant<int, 1>{});
+        if constexpr (NO > 2) octet(std::integral_constant<int, 2>{});
+        if constexpr (NO > 3) octet(std::integral_constant<int, 3>{});
+      }
+    }
+    // the batch's products into the running sums (rounded to nearest)
+#pragma unroll
+    for (int tt = 0; tt < NT; ++tt)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        v4 *s = &run[w][(tt * NB + b) * 2][lane];
+        s[0] = s[0] + (acc[tt][b][0] - acc[tt][b][1]);
+        s[64] = s[64] + (acc[tt][b][2] + acc[tt][b][3]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[tt][b][k] = v4{0, 0, 0, 0};
+      }
+  }
+  float2 *o = part + static_cast<int64_t>(c) * n * P;
+#pragma unroll
+  for (int tt = 0; tt < NT; ++tt) {
+    const int l = lt0 + tt * 16 + r;
+    cx<float> z = zc[tt];
+    z.re += __shfl_xor(z.re, 16);
+    z.im += __shfl_xor(z.im, 16);
+    z.re += __shfl_xor(z.re, 32);
+    z.im += __shfl_xor(z.im, 32);
+    if (l >= n) continue;
+    if (VROW && g == 0) o[static_cast<int64_t>(l) * P + 2 * p] = st(z);
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const v4 *s = &run[w][(tt * NB + b) * 2][lane];
+      const v4 re = s[0], im = s[64];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int row = 16 * b + 4 * g + j;
+        if (row < P - (VROW ? 1 : 0)) o[static_cast<int64_t>(l) * P + row] = make_float2(re[j], im[j]);
+      }
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Row a1 for many right-hand sides on the matrix cores (FP32): per pair the
+// Toeplitz translation T^{ml}[n'][nu] = h_{nu-n'} is built once and applied to
+// the coefficients of 64 right-hand sides as a GEMM  alpha_l[n'][r] +=
+// sum_nu T[n'][nu] beta_m[nu][r]  with 16x16x4 MFMA (M = n', K = nu, N = r),
+// complex products in three real MFMAs (Gauss).  One wave per target, kMrhsWaves
+// targets per block, grid.y source chunks, grid.z groups of 64 right-hand
+// sides.  Lanes 0..7 of each wave run the Hankel recurrences of 8 sources
+// at a time (from the pair table, as in k_m2l) into zero-padded LDS rows;
+// the A operand is read from there.  The B operand, beta transposed to
+// [m][nu][r] (r fastest, zero rows and columns as padding), is staged per
+// source in LDS for all waves of the block, double-buffered: the next
+// source's loads are in flight during the current source's MFMAs.
+constexpr int kMrhsWaves = 8;
+constexpr int kMrhsBatch = 8;
+
+template <int p>
+__global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs(const float2 *__restrict__ pairs,
+                                                              const float2 *__restrict__ bt,
+                                                              float2 *__restrict__ part, int n, int chunk_len,
+                                                              int nrhs, int r_pad, int64_t pstride) {
+  constexpr int P = 2 * p + 1;
+  constexpr int MT = (P + 15) / 16;
+  constexpr int KP = (P + 3) / 4 * 4;
+  constexpr int NT = 4;                      // 64 right-hand sides per block
+  constexpr int OFF = 16 * MT - 1;           // H index of q = k - row is q + OFF
+  constexpr int HQ = KP + OFF;               // zero outside |q| <= 2p
+  constexpr int BE = KP * 64;                // B entries of one source
+  constexpr int BL = (BE + 64 * kMrhsWaves - 1) / (64 * kMrhsWaves);  // loads per thread
+  __shared__ float2 H[kMrhsWaves][kMrhsBatch][HQ];
+  __shared__ float2 Bs[2][KP][64];
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int l = blockIdx.x * kMrhsWaves + w;
+  const int c = blockIdx.y;
+  const int r0 = blockIdx.z * 64;
+  const int m0 = c * chunk_len;
+  const int m1 = min(n, m0 + chunk_len);
+  typedef float v4 __attribute__((ext_vector_type(4)));
+  // Gauss: P1 = sum Ar Br, P2 = sum Ai Bi, P3 = sum (Ar + Ai)(Br + Bi)
+  v4 P1[MT][NT], P2[MT][NT], P3[MT][NT];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) P1[mt][ct] = P2[mt][ct] = P3[mt][ct] = v4{0, 0, 0, 0};
+  const int col = lane & 15, kq = lane >> 4;
+  // B of source m: rows k (zero rows k >= P in bt), 64 right-hand sides
+  float2 pre[BL];
+  auto load_b = [&](int m) {
+#pragma unroll
+    for (int i = 0; i < BL; ++i) {
+      const int e = threadIdx.x + 64 * kMrhsWaves * i;
+      pre[i] = (m < m1 && e < BE) ? bt[(static_cast<int64_t>(m) * KP + e / 64) * r_pad + r0 + (e & 63)]
+                                  : make_float2(0.f, 0.f);
+    }
+  };
+  auto store_b = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < BL; ++i) {
+      const int e = threadIdx.x + 64 * kMrhsWaves * i;
+      if (e < BE) Bs[buf][e / 64][e & 63] = pre[i];
+    }
+  };
+  load_b(m0);
+  int it = 0;
+  for (int mb = m0; mb < m1; mb += kMrhsBatch) {
+    const int sb = min(kMrhsBatch, m1 - mb);
+    for (int i = lane; i < kMrhsBatch * HQ; i += 64) H[w][i / HQ][i % HQ] = make_float2(0.f, 0.f);
+    __syncthreads();
+    if (lane < sb) {  // h_q of pair (mb + lane -> l), q = -2p..2p
+      const int m = mb + lane;
+      float2 *h = H[w][lane] + OFF;
+      if (l < n && m != l) {
+        const float2 *pe = pairs + 4 * (static_cast<int64_t>(m) * n + l);
+        cx<float> hp = ld<float>(pe[0]), hc = ld<float>(pe[1]);
+        const cx<float> t = ld<float>(pe[2]);
+        const float tz = pe[3].x;
+        h[0] = st(hp);
+        cx<float> tq = t;
+        for (int q = 1; q <= 2 * p; ++q) {
+          if (q >= 2) {
+            const cx<float> hn = static_cast<float>(q - 1) * tz * hc - hp;
+            hp = hc;
+            hc = hn;
+            tq = tq * t;
+          }
+          h[q] = st(hc * tq);
+          cx<float> hm = hc * conj(tq);
+          if (q & 1) hm = mk<float>(-hm.re, -hm.im);
+          h[-q] = st(hm);
+        }
+      }
+    }
+    for (int s = 0; s < sb; ++s, ++it) {
+      const int buf = it & 1;
+      store_b(buf);          // B of source mb + s (loaded one iteration ahead)
+      __syncthreads();
+      load_b(mb + s + 1);    // next source's B in flight during the MFMAs
+      const float2 *hrow = H[w][s];
+#pragma unroll
+      for (int k0 = 0; k0 < KP; k0 += 4) {
+        const int k = k0 + kq;
+        float br[NT], bi[NT], bs[NT];
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+          const float2 bv = Bs[buf][k][ct * 16 + col];
+          br[ct] = bv.x;
+          bi[ct] = bv.y;
+          bs[ct] = bv.x + bv.y;
+        }
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          const float2 a = hrow[k - (mt * 16 + col) + OFF];
+          const float as = a.x + a.y;
+#pragma unroll
+          for (int ct = 0; ct < NT; ++ct) {
+            P1[mt][ct] = mfma4<float>::mac(a.x, br[ct], P1[mt][ct]);
+            P2[mt][ct] = mfma4<float>::mac(a.y, bi[ct], P2[mt][ct]);
+            P3[mt][ct] = mfma4<float>::mac(as, bs[ct], P3[mt][ct]);
+          }
+        }
+      }
+    }
+    __syncthreads();
+  }
+  if (l >= n) return;
+  // result register j of lane i: row 4 (i / 16) + j, column i % 16
+  const int64_t len = static_cast<int64_t>(n) * P;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int row = mt * 16 + 4 * kq + j;
+        const int r = r0 + ct * 16 + col;
+        const float p1 = P1[mt][ct][j], p2 = P2[mt][ct][j], p3 = P3[mt][ct][j];
+        if (row < P && r < nrhs)
+          part[r * pstride + c * len + static_cast<int64_t>(l) * P + row] = make_float2(p1 - p2, p3 - p1 - p2);
+      }
+}
+
+// beta [r][m][P] -> bt [m][KP][r_pad] (r fastest; zero rows k >= P and
+// zero columns r >= nrhs), FP32.
+__global__ void k_rhs_transpose(const float2 *__restrict__ x, float2 *__restrict__ bt, int n, int P, int KP,
+                                int nrhs, int r_pad) {
+  const int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
+  const int64_t rows = static_cast<int64_t>(n) * KP;
+  if (i >= rows * r_pad) return;
+  const int64_t row = i / r_pad;
+  const int r = static_cast<int>(i % r_pad);
+  const int m = static_cast<int>(row / KP), k = static_cast<int>(row % KP);
+  bt[i] = (r < nrhs && k < P) ? x[r * static_cast<int64_t>(n) * P + static_cast<int64_t>(m) * P + k]
+                              : make_float2(0.f, 0.f);
+}
+
+// ---------------------------------------------------------------------------
+// Dispatch over the expansion order.
+#define MPSL_P_CASES(X) \
+  X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15) X(16) X(17) \
+  X(18) X(19) X(20)
+
+}  // namespace
+
+#define LAUNCH_CHECK(ctx)                                                          \
+  do {                                                                             \
+    hipError_t e_ = hipGetLastError();                                             \
+    if (e_ != hipSuccess) return set_err(ctx, MPSL_EHIP, std::string("kernel launch: ") + hipGetErrorString(e_)); \
+  } while (0)
+
+// The matrix-core forms win at every order they take (measured at 1000 and
+// 5000 particles; FP32 p = 16 1.49 against 3.04 ms, FP64 p = 12 0.083 against
+// 0.146 ms).  FP64 takes 32 targets per wave up to p = 12 (they share the
+// coefficient reads: 83 against 88 us at 1000 particles, p = 12; at p = 16 the
+// registers spill, 1245 against 1215 us at 3001) once that leaves enough
+// waves (203 particles, p = 12: 13.5 against 9.4 us).
+int m2l_default_variant(const mpsl_ctx *ctx, int prec) {
+  if (ctx->p > kM2LMfmaMaxP) return kM2LWhole;
+  return prec == MPSL_FP64 && ctx->p <= 12 && ctx->n >= 768 ? kM2LMfmaWide : kM2LMfma;
+}
+
+static int m2l_variant(const mpsl_ctx *ctx, int prec) {
+  int v = ctx->tune[prec == MPSL_FP64 ? 0 : 1].variant;
+  if (v < 0) v = m2l_default_variant(ctx, prec);
+  if (v >= kM2LMfma && ctx->p > kM2LMfmaMaxP) v = kM2LWhole;
+  return v;
+}
+
+// Source chunks of the matrix-core forms.  A compute unit works through its
+// share of the blocks at a fixed rate, so a launch takes about
+//   ceil(blocks / units) x (groups of four sources per chunk) x t_group
+// (t_group: 260 P cycles FP32, 525 P FP64 per 16 targets and wave, measured), a
+// sixth more while a unit has one block only, plus the writing and summing of
+// the chunks' partials at HBM rate; the best of up to 128 counts.  (5000
+// particles FP32: 42 chunks and 1.49 ms, as 125, which left 3x the partials to
+// sum; 1000 particles FP64, p = 12: 63 chunks, 83 us.)
+static int m2l_mfma_chunks(const mpsl_ctx *ctx, int prec, int nt) {
+  const int n = static_cast<int>(ctx->n), P = 2 * ctx->p + 1;
+  const int bpc = cdiv(n, 64 * nt), units = std::max(1, ctx->n_cu);
+  const bool f64 = prec == MPSL_FP64;
+  const double t_group = (f64 ? 525.0 : 260.0) * P * nt / 2.3e3;                        // us
+  const double t_slot = 2.0 * n * P * (f64 ? sizeof(double2) : sizeof(float2)) / 4.5e6;  // us
+  double best = 1e300;
+  int bc = 1;
+  for (int c = 1; c <= std::min(128, cdiv(n, 4)); ++c) {
+    const int groups = m2l_mfma_chunk_len(n, c) / 4;
+    if (cdiv(n, 4 * groups) != c) continue;  // trailing chunks empty
+    const int rounds = cdiv(static_cast<int64_t>(bpc) * c, units);
+    const double t = rounds * groups * t_group * (rounds == 1 ? 1.17 : 1.0) + c * t_slot;
+    if (t < best) {
+      best = t;
+      bc = c;
+    }
+  }
+  return bc;
+}
+
+int chunks_m2l(const mpsl_ctx *ctx, int prec) {
+  const int tuned = ctx->tune[prec == MPSL_FP64 ? 0 : 1].chunks;
+  if (tuned > 0) return static_cast<int>(std::min<int64_t>(tuned, ctx->n));
+  if (ctx->m2l_chunks > 0) return static_cast<int>(std::min<int64_t>(ctx->m2l_chunks, ctx->n));
+  const int v = m2l_variant(ctx, prec);
+  if (v >= kM2LMfma) return m2l_mfma_chunks(ctx, prec, v == kM2LMfmaWide ? 2 : 1);
+  // one lane per target: about 2560 blocks of 128 lanes
+  return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(cdiv(2560, cdiv(ctx->n, kThreads)), ctx->n)));
+}
+
+// Sources per chunk of the matrix-core M2L: each MFMA step takes a group of
+// four sources, so a chunk length that is not a multiple of 4 leaves a part
+// of one group's matrix work on zeros in every chunk (39 sources: 2.5 %
+// of the launch at 5000 particles); trailing chunks may come out empty and
+// then write zero partials.
+int m2l_mfma_chunk_len(int n, int chunks) { return (cdiv(n, chunks) + 3) / 4 * 4; }
+
+template <typename T>
+static int launch_m2l_t(mpsl_ctx *ctx, const void *beta, void *part, int chunks, int variant, int nrhs,
+                        int64_t pstride) {
+  const int n = static_cast<int>(ctx->n);
+  const int chunk_len = cdiv(n, chunks);
+  const bool f64 = std::is_same<T, double>::value;
+  const dim3 grid(cdiv(n, kThreads), chunks, nrhs);
+  const auto *pairs = static_cast<const cv_t<T> *>(f64 ? ctx->gt.pair64.p : ctx->gt.pair32.p);
+  const auto *b = static_cast<const cv_t<T> *>(beta);
+  auto *o = static_cast<cv_t<T> *>(part);
+  const int64_t bs = ctx->n * static_cast<int64_t>(2 * ctx->p + 1);
+  if (variant == kM2LMfma || variant == kM2LMfmaWide) {
+    if (ctx->p > kM2LMfmaMaxP) return set_err(ctx, MPSL_EUNSUPPORTED, "matrix-core M2L needs p <= 16");
+    const int nt = variant == kM2LMfma ? 1 : 2;
+    static_assert(kM2lWaves == kM2lBfWaves, "one grid for both precisions");
+    const dim3 g(cdiv(n, 16 * nt * kM2lWaves), chunks, nrhs);
+    const dim3 blk(64 * kM2lWaves);
+    const int cl = m2l_mfma_chunk_len(n, chunks);
+    switch (ctx->p) {
+#define X(PP)                                                                                        \
+  case PP:                                                                                           \
+    if constexpr (PP <= kM2LMfmaMaxP) {                                                              \
+      if constexpr (std::is_same<T, float>::value) {                                                 \
+        if (nt == 1)                                                                                 \
+          hipLaunchKernelGGL((k_m2l_bf<PP, 1>), g, blk, 0, ctx->stream, pairs, b, o, n, cl, bs, pstride); \
+        else                                                                                         \
+          hipLaunchKernelGGL((k_m2l_bf<PP, 2>), g, blk, 0, ctx->stream, pairs, b, o, n, cl, bs, pstride); \
+      } else {                                                                                       \
+        if (nt == 1)                                                                                 \
+          hipLaunchKernelGGL((k_m2l_f64<PP, 1>), g, blk, 0, ctx->stream, pairs, b, o, n, cl, bs, pstride); \
+        else                                                                                         \
+          hipLaunchKernelGGL((k_m2l_f64<PP, 2>), g, blk, 0, ctx->stream, pairs, b, o, n, cl, bs, pstride); \
+      }                                                                                              \
+    }                                                                                                \
+    break;
+      MPSL_P_CASES(X)
+#undef X
+      default: return set_err(ctx, MPSL_EUNSUPPORTED, "expansion order outside 1..20");
+    }
+    LAUNCH_CHECK(ctx);
+    return MPSL_OK;
+  }
+  switch (ctx->p) {
+#define X(PP)                                                                                               \
+  case PP:                                                                                                  \
+    if (variant == kM2LHalves) {                                                                            \
+      hipLaunchKernelGGL((k_m2l<T, PP, 0>), grid, dim3(kThreads), 0, ctx->stream, pairs, b, o, n, chunk_len, \
+                         bs, pstride);                                                                      \
+      hipLaunchKernelGGL((k_m2l<T, PP, 1>), grid, dim3(kThreads), 0, ctx->stream, pairs, b, o, n, chunk_len, \
+                         bs, pstride);                                                                      \
+    } else {                                                                                                \
+      hipLaunchKernelGGL((k_m2l<T, PP, -1>), grid, dim3(kThreads), 0, ctx->stream, pairs, b, o, n,           \
+                         chunk_len, bs, pstride);                                                           \
+    }                                                                                                       \
+    break;
+    MPSL_P_CASES(X)
+#undef X
+    default: return set_err(ctx, MPSL_EUNSUPPORTED, "expansion order outside 1..20");
+  }
+  LAUNCH_CHECK(ctx);
+  return MPSL_OK;
+}
+
+int launch_m2l(mpsl_ctx *ctx, int prec, const void *beta, void *part, int chunks, int variant, int nrhs,
+               int64_t pstride) {
+  if (variant < 0) variant = m2l_variant(ctx, prec);  // tuned or default; matrix cores up to p = 16
+  return prec == MPSL_FP64 ? launch_m2l_t<double>(ctx, beta, part, chunks, variant, nrhs, pstride)
+                           : launch_m2l_t<float>(ctx, beta, part, chunks, variant, nrhs, pstride);
+}
+
+int chunks_m2l_mrhs(const mpsl_ctx *ctx, int nrhs) {
+  const int64_t blocks = static_cast<int64_t>(cdiv(ctx->n, kMrhsWaves)) * cdiv(nrhs, 64);
+  return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(cdiv(1024, blocks), cdiv(ctx->n, kMrhsBatch))));
+}
+
+int launch_m2l_mrhs(mpsl_ctx *ctx, const void *beta, void *part, int chunks, int nrhs, int64_t pstride) {
+  const int n = static_cast<int>(ctx->n);
+  const int P = 2 * ctx->p + 1;
+  const int KP = (P + 3) / 4 * 4;
+  const int64_t rows = static_cast<int64_t>(n) * KP;
+  const int r_pad = 64 * cdiv(nrhs, 64);
+  int rc = dev_alloc(ctx, ctx->bt, static_cast<size_t>(rows) * r_pad * sizeof(float2));
+  if (rc) return rc;
+  hipLaunchKernelGGL(k_rhs_transpose, dim3(cdiv(rows * r_pad, 256)), dim3(256), 0, ctx->stream,
+                     static_cast<const float2 *>(beta), static_cast<float2 *>(ctx->bt.p), n, P, KP, nrhs, r_pad);
+  LAUNCH_CHECK(ctx);
+  const int chunk_len = cdiv(n, chunks);
+  const dim3 grid(cdiv(n, kMrhsWaves), chunks, r_pad / 64);
+  const auto *pairs = static_cast<const float2 *>(ctx->gt.pair32.p);
+  const auto *bt = static_cast<const float2 *>(ctx->bt.p);
+  auto *pp = static_cast<float2 *>(part);
+  switch (ctx->p) {
+#define X(PP) \
+  case PP: hipLaunchKernelGGL((k_m2l_mrhs<PP>), grid, dim3(64 * kMrhsWaves), 0, ctx->stream, pairs, bt, pp, n, chunk_len, nrhs, r_pad, pstride); break;
+    MPSL_P_CASES(X)
+#undef X
+    default: return set_err(ctx, MPSL_EUNSUPPORTED, "expansion order outside 1..20");
+  }
+  LAUNCH_CHECK(ctx);
+  return MPSL_OK;
+}
+
+template <typename T>
+static int launch_fmm_near_t(mpsl_ctx *ctx, const void *beta, void *out) {
+  const FmmPlan &f = ctx->fmm;
+  const int n = static_cast<int>(ctx->n);
+  const bool f64 = std::is_same<T, double>::value;
+  const auto *pairs = static_cast<const cv_t<T> *>(f64 ? f.near64.p : f.near32.p);
+  const auto *src = static_cast<const int *>(f.near_src.p);
+  const auto *perm = static_cast<const int *>(f.perm.p);
+  const auto *wave = static_cast<const int *>(f.near_wave.p);
+  const auto *b = static_cast<const cv_t<T> *>(beta);
+  auto *o = static_cast<cv_t<T> *>(out);
+  const int kc = cdiv(f.near_k, f.near_chunks);
+  const dim3 grid(cdiv(n, kThreads), f.near_chunks);
+  // FP64: two output halves (register pressure); FP32: one launch
+  switch (ctx->p) {
+#define X(PP)                                                                                                    \
+  case PP:                                                                                                       \
+    if constexpr (std::is_same<T, double>::value) {                                                              \
+      hipLaunchKernelGGL((k_fmm_near<T, PP, 0>), grid, dim3(kThreads), 0, ctx->stream, pairs, src, perm, wave, b, \
+                         o, n, kc);                                                                              \
+      hipLaunchKernelGGL((k_fmm_near<T, PP, 1>), grid, dim3(kThreads), 0, ctx->stream, pairs, src, perm, wave, b, \
+                         o, n, kc);                                                                              \
+    } else {                                                                                                     \
+      hipLaunchKernelGGL((k_fmm_near<T, PP, -1>), grid, dim3(kThreads), 0, ctx->stream, pairs, src, perm, wave,   \
+                         b, o, n, kc);                                                                           \
+    }                                                                                                            \
+    break;
+    MPSL_P_CASES(X)
+#undef X
+    default: return set_err(ctx, MPSL_EUNSUPPORTED, "expansion order outside 1..20");
+  }
+  LAUNCH_CHECK(ctx);
+  return MPSL_OK;
+}
+
+int launch_fmm_near(mpsl_ctx *ctx, int prec, const void *beta, void *out) {
+  return prec == MPSL_FP64 ? launch_fmm_near_t<double>(ctx, beta, out) : launch_fmm_near_t<float>(ctx, beta, out);
+}
+
+}  // namespace mpsl
