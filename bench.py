@@ -34,7 +34,7 @@ M2L_VARIANTS = {
     1: ("k_m2l<{t},16,0|1> (all-pairs M2L, output halves)", "alu", None, None),
     2: ("k_m2l_bf<16,1> / k_m2l_f64<16,1> ({t}, all-pairs M2L on the matrix cores)", "mfma",
         "m2l_mfma_5000stars_p16_hbm_traffic.md",
-        ("// Row a1 on the matrix cores, one right-hand side.", "// Row a1 for many right-hand sides")),
+        ("// Row a1 on the matrix cores, one right-hand side", "// Row a1 for many right-hand sides")),
     3: ("k_m2l_bf<16,2> / k_m2l_f64<16,2> ({t}, all-pairs M2L on the matrix cores, 32 targets per wave)", "mfma",
         None, None),
 }
