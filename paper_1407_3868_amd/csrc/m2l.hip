@@ -421,6 +421,7 @@ typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // Eight FP32 values as three bf16 parts (round to nearest; the remainders are
 // exact).
@@ -801,6 +802,218 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs(const float2 *__re
       }
 }
 
+// ---------------------------------------------------------------------------
+// Row a1 for many right-hand sides on the bf16 matrix cores (FP32 operands in
+// three exact bf16 parts and the six largest products of parts, as in
+// k_m2l_bf), for 16 < 2p + 1 <= 32: per pair one 16x16x32 MFMA step covers all
+// source orders.  alpha_l[n'][r] += sum_nu T[n'][nu] beta_m[nu][r] with
+// T[n'][nu] = h_{nu - n'} (M = n' in two 16-row blocks, K = nu, N = r in four
+// 16-column tiles); complex products in four real ones, re and im in one
+// accumulator each (the imaginary part of T negated in registers).
+//
+// One wave per target, kMrhsWaves targets per block, grid.y source chunks,
+// grid.z groups of 64 right-hand sides.  Lanes 0..7 run the Hankel recurrences
+// of 8 sources at a time into FP32 rows; per source each lane splits one h_q
+// and stores its parts in four copies, shifted by 0 .. 3 entries, from which
+// the A operand (eight consecutive q, ending at a lane's row) is read with
+// aligned 8-byte reads.  B, split once per call (k_rhs_split), is staged per
+// source for all waves of the block, double-buffered.  The matrix cores' bf16
+// sums do not round to nearest, so they are added to the chunk's partial slot
+// after every kMrhsFlush sources and start again from zero.
+//
+// Bound by the matrix cores: 192 MFMAs of 16 cycles per pair and 64 right-hand
+// sides, where the FP32 form below needs 3 MT KP NT / 4 = 168 of 32.4 (p = 12).
+// 64 right-hand sides, 2000 particles, p = 12: 10.9 -> 7.9 ms (MFMAs 65 % of the
+// cycles), the batch's error against 64 bits 1.3e-6 -> 1.0e-6.
+constexpr int kMrhsFlush = 32;
+
+template <int p>
+__global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *__restrict__ pairs,
+                                                                 const __bf16 *__restrict__ bt,
+                                                                 float2 *__restrict__ part, int n, int chunk_len,
+                                                                 int nrhs, int r_pad, int64_t pstride) {
+  constexpr int P = 2 * p + 1;
+  static_assert(P > 16 && P <= 32, "two row blocks, one K step");
+  constexpr int MT = 2, NT = 4;
+  constexpr int OFF = 31;                    // row entry of h_q is q + OFF
+  constexpr int PR = 6 * 64 * 32;            // B entries of one source
+  constexpr int BL = PR / 8 / (64 * kMrhsWaves);  // 16-byte loads per thread
+  static_assert(BL * 8 * 64 * kMrhsWaves == PR, "whole loads");
+  typedef float v4 __attribute__((ext_vector_type(4)));
+  __shared__ float2 H[kMrhsWaves][kMrhsBatch][65];
+  __shared__ __align__(16) __bf16 Hs[2][kMrhsWaves][6][4][kBfRow];
+  __shared__ __align__(16) __bf16 Bs[2][PR];  // [part, re / im][nu / 8][r][nu % 8]: a read's 16 columns are contiguous
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int l = blockIdx.x * kMrhsWaves + w;
+  const int c = blockIdx.y;
+  const int r0 = blockIdx.z * 64;
+  const int m0 = c * chunk_len;
+  const int m1 = min(n, m0 + chunk_len);
+  const int col = lane & 15, kq = lane >> 4;
+  v4 acc[MT][NT][2];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) acc[mt][ct][0] = acc[mt][ct][1] = v4{0, 0, 0, 0};
+  u32x4 pre[BL];
+  auto load_b = [&](int m) {
+    const int64_t mc = min(m, n - 1);  // past the chunk: loaded, never used
+#pragma unroll
+    for (int i = 0; i < BL; ++i) {
+      const int e = threadIdx.x + 64 * kMrhsWaves * i;  // 16-byte piece: (array, nu / 8) e / 64, right-hand side e % 64
+      pre[i] = *reinterpret_cast<const u32x4 *>(bt + ((mc * 24 + e / 64) * r_pad + r0 + e % 64) * 8);
+    }
+  };
+  auto store_b = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < BL; ++i) *reinterpret_cast<u32x4 *>(&Bs[buf][8 * (threadIdx.x + 64 * kMrhsWaves * i)]) = pre[i];
+  };
+  // sums of the sources since the last flush into the chunk's slot
+  const int64_t len = static_cast<int64_t>(n) * P;
+  bool first = true;
+  auto flush = [&]() {
+    if (l < n) {
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+          const int r = r0 + ct * 16 + col;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const int row = mt * 16 + 4 * kq + j;
+            if (row < P && r < nrhs) {
+              float2 *o = part + r * pstride + c * len + static_cast<int64_t>(l) * P + row;
+              float2 v = make_float2(acc[mt][ct][0][j], acc[mt][ct][1][j]);
+              if (!first) {
+                const float2 u = *o;
+                v.x += u.x;
+                v.y += u.y;
+              }
+              *o = v;
+            }
+          }
+          acc[mt][ct][0] = acc[mt][ct][1] = v4{0, 0, 0, 0};
+        }
+    }
+    first = false;
+  };
+  load_b(m0);
+  int it = 0;
+  for (int mb = m0; mb < m1; mb += kMrhsBatch) {
+    const int sb = min(kMrhsBatch, m1 - mb);
+    // each wave fills its own rows (one wave's LDS accesses stay in order)
+    for (int i = lane; i < kMrhsBatch * 64; i += 64) H[w][i / 64][i % 64] = make_float2(0.f, 0.f);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    if (lane < sb) {  // h_q of pair (mb + lane -> l), q = -2p..2p
+      const int m = mb + lane;
+      float2 *h = H[w][lane] + OFF;
+      if (l < n && m != l) {
+        const float2 *pe = pairs + 4 * (static_cast<int64_t>(m) * n + l);
+        cx<float> hp = ld<float>(pe[0]), hc = ld<float>(pe[1]);
+        const cx<float> t = ld<float>(pe[2]);
+        const float tz = pe[3].x;
+        h[0] = st(hp);
+        cx<float> tq = t;
+        for (int q = 1; q <= 2 * p; ++q) {
+          if (q >= 2) {
+            const cx<float> hn = static_cast<float>(q - 1) * tz * hc - hp;
+            hp = hc;
+            hc = hn;
+            tq = tq * t;
+          }
+          h[q] = st(hc * tq);
+          cx<float> hm = hc * conj(tq);
+          if (q & 1) hm = mk<float>(-hm.re, -hm.im);
+          h[-q] = st(hm);
+        }
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    // parts of the h of source s of the batch: copy u holds entry x at x + 3 - u
+    auto split_h = [&](int s, int buf) {
+      const float2 h = H[w][s][lane];
+      float x[2] = {h.x, h.y};
+#pragma unroll
+      for (int k = 0; k < 3; ++k)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const __bf16 b = static_cast<__bf16>(x[i]);
+          x[i] -= static_cast<float>(b);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) Hs[buf][w][2 * k + i][u][lane + 3 - u] = b;
+        }
+    };
+    split_h(0, it & 1);
+    if (it == 0) store_b(0);
+    for (int s = 0; s < sb; ++s, ++it) {
+      const int buf = it & 1;
+      __syncthreads();       // B and the parts of h of this source stored
+      load_b(mb + s + 1);    // the next source's, beside the MFMAs
+      if (s + 1 < sb) split_h(s + 1, buf ^ 1);
+      const __bf16 *bs = Bs[buf] + (kq * 64 + col) * 8;
+      bf8 ar[MT][3], ai[MT][3], an[MT][3];
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) {
+        // h_{nu - n'} for nu = 8 kq + 0 .. 7, n' = 16 mt + col: entries from x0
+        const int x0 = 8 * kq - 16 * mt - col + OFF + 3;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          const bf4 *a = reinterpret_cast<const bf4 *>(&Hs[buf][w][2 * k][x0 & 3][x0 & ~3]);
+          const bf4 *b = reinterpret_cast<const bf4 *>(&Hs[buf][w][2 * k + 1][x0 & 3][x0 & ~3]);
+          ar[mt][k] = __builtin_shufflevector(a[0], a[1], 0, 1, 2, 3, 4, 5, 6, 7);
+          ai[mt][k] = __builtin_shufflevector(b[0], b[1], 0, 1, 2, 3, 4, 5, 6, 7);
+          an[mt][k] = __builtin_bit_cast(bf8, __builtin_bit_cast(u32x4, ai[mt][k]) ^ 0x80008000u);
+        }
+      }
+#pragma unroll
+      for (int ct = 0; ct < NT; ++ct) {
+        bf8 br[3], bi[3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+          br[k] = *reinterpret_cast<const bf8 *>(bs + (2 * k) * 64 * 32 + ct * 16 * 8);
+          bi[k] = *reinterpret_cast<const bf8 *>(bs + (2 * k + 1) * 64 * 32 + ct * 16 * 8);
+        }
+        constexpr int ka[6] = {0, 0, 1, 0, 1, 2}, kb[6] = {2, 1, 1, 0, 0, 0};
+#pragma unroll
+        for (int x = 0; x < 6; ++x) {
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+            acc[mt][ct][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar[mt][ka[x]], br[kb[x]], acc[mt][ct][0], 0, 0, 0);
+            acc[mt][ct][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar[mt][ka[x]], bi[kb[x]], acc[mt][ct][1], 0, 0, 0);
+          }
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+            acc[mt][ct][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(an[mt][ka[x]], bi[kb[x]], acc[mt][ct][0], 0, 0, 0);
+            acc[mt][ct][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ai[mt][ka[x]], br[kb[x]], acc[mt][ct][1], 0, 0, 0);
+          }
+        }
+      }
+      store_b(buf ^ 1);  // last read two sources ago
+      if ((it + 1) % kMrhsFlush == 0) flush();
+    }
+  }
+  if (it % kMrhsFlush != 0 || first) flush();
+}
+
+// beta [r][m][P] -> bt [m][part, re / im][nu / 8][r_pad][nu % 8]: three bf16
+// parts of every coefficient, zeros for nu >= P and r >= nrhs.
+__global__ void k_rhs_split(const float2 *__restrict__ x, __bf16 *__restrict__ bt, int n, int P, int nrhs, int r_pad) {
+  const int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
+  if (i >= static_cast<int64_t>(n) * r_pad * 32) return;
+  const int k = static_cast<int>(i % 32), r = static_cast<int>(i / 32 % r_pad);
+  const int64_t m = i / 32 / r_pad;
+  const float2 v = (r < nrhs && k < P) ? x[(r * static_cast<int64_t>(n) + m) * P + k] : make_float2(0.f, 0.f);
+  float b[2] = {v.x, v.y};
+#pragma unroll
+  for (int u = 0; u < 3; ++u)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const __bf16 h = static_cast<__bf16>(b[j]);
+      b[j] -= static_cast<float>(h);
+      bt[(((m * 6 + 2 * u + j) * 4 + k / 8) * r_pad + r) * 8 + k % 8] = h;
+    }
+}
+
 // beta [r][m][P] -> bt [m][KP][r_pad] (r fastest; zero rows k >= P and
 // zero columns r >= nrhs), FP32.
 __global__ void k_rhs_transpose(const float2 *__restrict__ x, float2 *__restrict__ bt, int n, int P, int KP,
@@ -963,9 +1176,20 @@ int launch_m2l(mpsl_ctx *ctx, int prec, const void *beta, void *part, int chunks
                            : launch_m2l_t<float>(ctx, beta, part, chunks, variant, nrhs, pstride);
 }
 
+// Source chunks: one block of either form runs per compute unit at a time, all
+// with the same work, so of the counts up to about 1024 blocks' worth the
+// smallest whose blocks fill their last round within 3 % of the best (2000
+// particles, 64 right-hand sides: 250 blocks, one chunk).
 int chunks_m2l_mrhs(const mpsl_ctx *ctx, int nrhs) {
   const int64_t blocks = static_cast<int64_t>(cdiv(ctx->n, kMrhsWaves)) * cdiv(nrhs, 64);
-  return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(cdiv(1024, blocks), cdiv(ctx->n, kMrhsBatch))));
+  const int hi = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(cdiv(1024, blocks), cdiv(ctx->n, kMrhsBatch))));
+  const int units = std::max(1, ctx->n_cu);
+  auto cost = [&](int c) { return static_cast<double>(cdiv(blocks * c, units)) / c; };
+  double best = 1e300;
+  for (int c = 1; c <= hi; ++c) best = std::min(best, cost(c));
+  for (int c = 1; c <= hi; ++c)
+    if (cost(c) <= 1.03 * best) return c;
+  return hi;
 }
 
 int launch_m2l_mrhs(mpsl_ctx *ctx, const void *beta, void *part, int chunks, int nrhs, int64_t pstride) {
@@ -974,6 +1198,37 @@ int launch_m2l_mrhs(mpsl_ctx *ctx, const void *beta, void *part, int chunks, int
   const int KP = (P + 3) / 4 * 4;
   const int64_t rows = static_cast<int64_t>(n) * KP;
   const int r_pad = 64 * cdiv(nrhs, 64);
+  // bf16 parts where one K step holds all orders (p = 8 .. 15; at p = 16 the
+  // 33 orders would pad to 64), unless the context's memory budget has no room
+  // for them: then, and else, the FP32 form
+  const size_t parts = static_cast<size_t>(n) * r_pad * 6 * 32 * sizeof(__bf16);
+  bool split = P > 16 && P <= 32 && parts < ctx->bt_refused;
+  if (split && parts > ctx->bt.bytes) {
+    split = ctx->hbm_budget == 0 || ctx->hbm_used - ctx->bt.bytes + parts <= ctx->hbm_budget;
+    if (split && dev_alloc(ctx, ctx->bt, parts) != MPSL_OK) {
+      split = false;
+      ctx->bt_refused = parts;  // not tried again: a later call may be under capture
+    }
+  }
+  if (split) {
+    auto *bt = static_cast<__bf16 *>(ctx->bt.p);
+    hipLaunchKernelGGL(k_rhs_split, dim3(cdiv(static_cast<int64_t>(n) * r_pad * 32, 256)), dim3(256), 0, ctx->stream,
+                       static_cast<const float2 *>(beta), bt, n, P, nrhs, r_pad);
+    LAUNCH_CHECK(ctx);
+    const dim3 grid(cdiv(n, kMrhsWaves), chunks, r_pad / 64);
+    switch (ctx->p) {
+#define X(PP)                                                                                                  \
+  case PP:                                                                                                     \
+    hipLaunchKernelGGL(k_m2l_mrhs_bf<PP>, grid, dim3(64 * kMrhsWaves), 0, ctx->stream,                         \
+                       static_cast<const float2 *>(ctx->gt.pair32.p), bt, static_cast<float2 *>(part), n,      \
+                       cdiv(n, chunks), nrhs, r_pad, pstride);                                                 \
+    break;
+      X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15)
+#undef X
+    }
+    LAUNCH_CHECK(ctx);
+    return MPSL_OK;
+  }
   int rc = dev_alloc(ctx, ctx->bt, static_cast<size_t>(rows) * r_pad * sizeof(float2));
   if (rc) return rc;
   hipLaunchKernelGGL(k_rhs_transpose, dim3(cdiv(rows * r_pad, 256)), dim3(256), 0, ctx->stream,

@@ -12,7 +12,7 @@ orders would show).
 import numpy as np
 import pytest
 
-from gpu_common import coeff_vector, gpu_context, make_workload, rel_err
+from gpu_common import coeff_vector, gpu_context, make_workload, oracle_problem, rel_err
 from oracle import operators as oops
 
 pytestmark = pytest.mark.gpu
@@ -51,3 +51,26 @@ def test_fp32_long_chunk(variant):
     ref = _m2l(ctx, 0, x)
     ctx.set_tuning(1, variant, 1)
     assert rel_err(_m2l(ctx, 1, x), ref) < 2e-6
+
+
+@pytest.mark.parametrize("p", [7, 8, 9, 12, 15, 16])
+@pytest.mark.parametrize("n,nrhs", [(5, 16), (70, 65), (700, 17)])
+def test_many_rhs(p, n, nrhs):
+    # one K step (p = 8 .. 15) and the FP32 form beside it; a ragged last group
+    # of right-hand sides; chunks longer than the interval between two flushes
+    import torch
+    wl = make_workload("c2" if n > 70 else "s70p8", n=n)
+    wl.p = p
+    ctx = gpu_context(wl)
+    X = np.stack([coeff_vector(wl, 80 + r) for r in range(3)])[np.arange(nrhs) % 3]
+    y = {}
+    for prec, dt in ((0, np.complex128), (1, np.complex64)):
+        xd = torch.from_numpy(X.astype(dt)).cuda()
+        yd = torch.full_like(xd, float("nan"))
+        ctx.set_stream(torch.cuda.current_stream().cuda_stream)
+        ctx.apply_batch_dev(prec, nrhs, xd, yd)
+        torch.cuda.synchronize()
+        y[prec] = yd.cpu().numpy()
+    assert rel_err(y[0][0], oracle_problem(wl).matvec(X[0])) < 1e-11 if n <= 70 else True
+    for r in range(nrhs):
+        assert rel_err(y[1][r], y[0][r]) < 2e-5
