@@ -818,15 +818,13 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs(const float2 *__re
 // the A operand (eight consecutive q, ending at a lane's row) is read with
 // aligned 8-byte reads.  B, split once per call (k_rhs_split), is staged per
 // source for all waves of the block, double-buffered.  The matrix cores' bf16
-// sums do not round to nearest, so they are added to the chunk's partial slot
-// after every kMrhsFlush sources and start again from zero.
+// sums do not round to nearest, so they are added to running FP32 sums after
+// every batch of 8 sources and start again from zero.
 //
 // Bound by the matrix cores: 192 MFMAs of 16 cycles per pair and 64 right-hand
 // sides, where the FP32 form below needs 3 MT KP NT / 4 = 168 of 32.4 (p = 12).
 // 64 right-hand sides, 2000 particles, p = 12: 10.9 -> 7.9 ms (MFMAs 65 % of the
 // cycles), the batch's error against 64 bits 1.3e-6 -> 1.0e-6.
-constexpr int kMrhsFlush = 32;
-
 template <int p>
 __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *__restrict__ pairs,
                                                                  const __bf16 *__restrict__ bt,
@@ -868,34 +866,22 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *_
 #pragma unroll
     for (int i = 0; i < BL; ++i) *reinterpret_cast<u32x4 *>(&Bs[buf][8 * (threadIdx.x + 64 * kMrhsWaves * i)]) = pre[i];
   };
-  // sums of the sources since the last flush into the chunk's slot
-  const int64_t len = static_cast<int64_t>(n) * P;
-  bool first = true;
+  // sums of the sources since the last flush into the running ones
+  v4 run[MT][NT][2];
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) run[mt][ct][0] = run[mt][ct][1] = v4{0, 0, 0, 0};
   auto flush = [&]() {
-    if (l < n) {
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int ct = 0; ct < NT; ++ct) {
-          const int r = r0 + ct * 16 + col;
+      for (int ct = 0; ct < NT; ++ct)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const int row = mt * 16 + 4 * kq + j;
-            if (row < P && r < nrhs) {
-              float2 *o = part + r * pstride + c * len + static_cast<int64_t>(l) * P + row;
-              float2 v = make_float2(acc[mt][ct][0][j], acc[mt][ct][1][j]);
-              if (!first) {
-                const float2 u = *o;
-                v.x += u.x;
-                v.y += u.y;
-              }
-              *o = v;
-            }
-          }
-          acc[mt][ct][0] = acc[mt][ct][1] = v4{0, 0, 0, 0};
+        for (int i = 0; i < 2; ++i) {
+          run[mt][ct][i] += acc[mt][ct][i];
+          acc[mt][ct][i] = v4{0, 0, 0, 0};
         }
-    }
-    first = false;
   };
   load_b(m0);
   int it = 0;
@@ -989,10 +975,22 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *_
         }
       }
       store_b(buf ^ 1);  // last read two sources ago
-      if ((it + 1) % kMrhsFlush == 0) flush();
     }
+    flush();
   }
-  if (it % kMrhsFlush != 0 || first) flush();
+  if (l >= n) return;
+  const int64_t len = static_cast<int64_t>(n) * P;
+#pragma unroll
+  for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int row = mt * 16 + 4 * kq + j, r = r0 + ct * 16 + col;
+        if (row < P && r < nrhs)
+          part[r * pstride + c * len + static_cast<int64_t>(l) * P + row] =
+              make_float2(run[mt][ct][0][j], run[mt][ct][1][j]);
+      }
 }
 
 // beta [r][m][P] -> bt [m][part, re / im][nu / 8][r_pad][nu % 8]: three bf16
