@@ -383,6 +383,14 @@ template <int P> struct OrderSplit {
 };
 
 constexpr int kM2sWaves = 4;
+// Steps of the M2S and S2L products whose operands are in flight.  In FP64 they
+// read an entry of 16 bytes per particle, node and side from HBM, and one step
+// ahead left the matrix cores waiting (1000 particles, 25216 nodes, p = 12: M2S
+// 336 us, S2L 349 us, 2.3 TB/s; two steps 274 and 298, four 265 and 281).  In
+// FP32 one step ahead is enough, and loading past the end of a chunk costs
+// more than it gives (20000 particles, 1024 nodes, p = 16: S2L 123 us with one
+// step, fetched only where there is one, 143 with two).
+template <typename T> constexpr int gemm_depth() { return sizeof(T) == 8 ? 4 : 1; }
 template <typename T, int p>
 __global__ __launch_bounds__(64 * kM2sWaves) void k_m2s_mfma(const cv_t<T> *__restrict__ E,
                                                              const cv_t<T> *__restrict__ beta,
@@ -413,7 +421,8 @@ __global__ __launch_bounds__(64 * kM2sWaves) void k_m2s_mfma(const cv_t<T> *__re
   for (int v = 0; v < (NV > 0 ? NV : 1); ++v) vr[v] = mk<T>(0, 0);
   if (m0 < m1) {
     // operands of particle group mb (loads clamped into range, zeros selected
-    // past the chunk), the next group fetched while the current one multiplies
+    // past the chunk), those of the next gemm_depth groups in flight while the
+    // current one multiplies
     struct Ops {
       cv_t<T> a, b[NT], bv[NV > 0 ? NV : 1];
     };
@@ -425,23 +434,28 @@ __global__ __launch_bounds__(64 * kM2sWaves) void k_m2s_mfma(const cv_t<T> *__re
 #pragma unroll
       for (int v = 0; v < NV; ++v) o.bv[v] = beta[static_cast<int64_t>(mc) * P + 16 * NT + v];
     };
-    Ops nx;
-    fetch(m0, nx);
-    for (int mb = m0; mb < m1; mb += 4) {
-      const Ops cu = nx;
-      if (mb + 4 < m1) fetch(mb + 4, nx);
-      const bool mv = mb + kr < m1;
-      const T zr = mv ? cu.a.x : T(0), zi = mv ? cu.a.y : T(0), zs = zr + zi;
+    constexpr int U = gemm_depth<T>();
+    Ops nx[U];
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const bool cv = t * 16 + (lane & 15) < P;  // padded tile (long remainders only)
-        const T br = cv ? cu.b[t].x : T(0), bi = cv ? cu.b[t].y : T(0);
-        P1[t] = mfma4<T>::mac(zr, br, P1[t]);
-        P2[t] = mfma4<T>::mac(zi, bi, P2[t]);
-        P3[t] = mfma4<T>::mac(zs, br + bi, P3[t]);
+    for (int u = 0; u < U; ++u) fetch(m0 + 4 * u, nx[u]);
+    for (int mb = m0; mb < m1; mb += 4 * U) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const Ops cu = nx[u];
+        if (U > 1 || mb + 4 < m1) fetch(mb + 4 * (U + u), nx[u]);
+        const bool mv = mb + 4 * u + kr < m1;
+        const T zr = mv ? cu.a.x : T(0), zi = mv ? cu.a.y : T(0), zs = zr + zi;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const bool cv = t * 16 + (lane & 15) < P;  // padded tile (long remainders only)
+          const T br = cv ? cu.b[t].x : T(0), bi = cv ? cu.b[t].y : T(0);
+          P1[t] = mfma4<T>::mac(zr, br, P1[t]);
+          P2[t] = mfma4<T>::mac(zi, bi, P2[t]);
+          P3[t] = mfma4<T>::mac(zs, br + bi, P3[t]);
+        }
+#pragma unroll
+        for (int v = 0; v < NV; ++v) cmac(vr[v], mk<T>(zr, zi), ld<T>(cu.bv[v]));
       }
-#pragma unroll
-      for (int v = 0; v < NV; ++v) cmac(vr[v], mk<T>(zr, zi), ld<T>(cu.bv[v]));
     }
   }
   // vector-unit orders: sum over the four particles of each node (lane
@@ -533,7 +547,8 @@ __global__ __launch_bounds__(64 * kS2lWaves) void k_s2l_mfma(const cv_t<T> *__re
   }
   if (q0 < q1) {
     // operands of node group qb (loads clamped into range, zeros selected
-    // outside it), the next group fetched while the current one multiplies
+    // outside it), those of the next gemm_depth groups in flight while the
+    // current one multiplies
     struct Ops {
       cv_t<T> a[MT], b[NT], bv[NV > 0 ? NV : 1];
     };
@@ -549,39 +564,43 @@ __global__ __launch_bounds__(64 * kS2lWaves) void k_s2l_mfma(const cv_t<T> *__re
 #pragma unroll
       for (int v = 0; v < NV; ++v) o.bv[v] = u[16 * NT + v];
     };
-    Ops nx;
-    fetch(0, q0, nx);
-    for (int side = 0, qb = q0; side < 2;) {
-      const Ops cu = nx;
-      const bool qv = qb + kr < q1;
-      int ns_side = side, ns_qb = qb + 4;
-      if (ns_qb >= q1) {
-        ns_side = side + 1;
-        ns_qb = q0;
-      }
-      if (ns_side < 2) fetch(ns_side, ns_qb, nx);
-      T br[NT], bi[NT], bs[NT];
+    constexpr int U = gemm_depth<T>();
+    const int half = (q1 - q0 + 3) / 4;  // steps per side
+    Ops nx[U];
+    auto fetch_step = [&](int i, Ops &o) {
+      const int side = i >= half ? 1 : 0;
+      fetch(side, q0 + 4 * (i - side * half), o);
+    };
 #pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const bool cv = qv && (t * 16 + (lane & 15)) < P;
-        br[t] = cv ? cu.b[t].x : T(0);
-        bi[t] = cv ? cu.b[t].y : T(0);
-        bs[t] = br[t] + bi[t];
-      }
+    for (int u = 0; u < U; ++u) fetch_step(u, nx[u]);
+    for (int i = 0; i < 2 * half; i += U) {
 #pragma unroll
-      for (int m = 0; m < MT; ++m) {
-        const T zr = (qv && lv[m]) ? cu.a[m].x : T(0), zi = (qv && lv[m]) ? cu.a[m].y : T(0), zs = zr + zi;
+      for (int u = 0; u < U; ++u) {
+        const Ops cu = nx[u];
+        if (U > 1 || i + 1 < 2 * half) fetch_step(i + u + U, nx[u]);
+        const int x = i + u >= half ? i + u - half : i + u;
+        const bool qv = i + u < 2 * half && q0 + 4 * x + kr < q1;
+        T br[NT], bi[NT], bs[NT];
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-          P1[m][t] = mfma4<T>::mac(zr, br[t], P1[m][t]);
-          P2[m][t] = mfma4<T>::mac(zi, bi[t], P2[m][t]);
-          P3[m][t] = mfma4<T>::mac(zs, bs[t], P3[m][t]);
+          const bool cv = qv && (t * 16 + (lane & 15)) < P;
+          br[t] = cv ? cu.b[t].x : T(0);
+          bi[t] = cv ? cu.b[t].y : T(0);
+          bs[t] = br[t] + bi[t];
         }
 #pragma unroll
-        for (int v = 0; v < NV; ++v) cmac(vr[m][v], mk<T>(zr, zi), ld<T>(cu.bv[v]));
+        for (int m = 0; m < MT; ++m) {
+          const T zr = (qv && lv[m]) ? cu.a[m].x : T(0), zi = (qv && lv[m]) ? cu.a[m].y : T(0), zs = zr + zi;
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            P1[m][t] = mfma4<T>::mac(zr, br[t], P1[m][t]);
+            P2[m][t] = mfma4<T>::mac(zi, bi[t], P2[m][t]);
+            P3[m][t] = mfma4<T>::mac(zs, bs[t], P3[m][t]);
+          }
+#pragma unroll
+          for (int v = 0; v < NV; ++v) cmac(vr[m][v], mk<T>(zr, zi), ld<T>(cu.bv[v]));
+        }
       }
-      side = ns_side;
-      qb = ns_qb;
     }
   }
   cv_t<T> *o = part + static_cast<int64_t>(c) * n * P;
