@@ -76,6 +76,12 @@ __device__ inline void sincos_quarter(double r, double &s, double &c) {
   c = 1.0 - r2 * pc;
 }
 
+// x with its sign bit flipped where s = 2^31 (s = 0: unchanged).
+__device__ inline float flip_sign(float x, unsigned s) { return __uint_as_float(__float_as_uint(x) ^ s); }
+__device__ inline double flip_sign(double x, unsigned s) {
+  return __hiloint2double(static_cast<int>(static_cast<unsigned>(__double2hiint(x)) ^ s), __double2loint(x));
+}
+
 // e^{a + i b} in the matvec precision.  The phase b (up to |lambda| times the
 // strip width) is reduced in FP64 to r = b - k pi/2, |r| <= pi/4, with a
 // two-term pi/2 (Cody and Waite); sin and cos of r come from the series
@@ -85,16 +91,29 @@ __device__ inline void sincos_quarter(double r, double &s, double &c) {
 // same instructions.
 template <typename T> __device__ inline cx<T> cexpT(double a, double b) {
   constexpr double kHalfPiHi = 1.5707963267948966, kHalfPiLo = 6.123233995736766e-17;
-  const double k = rint(b * 0.6366197723675814);
+  constexpr double kRound = 6755399441055744.0;  // 1.5 2^52: the sum's low bits are the nearest integer
+  const double km = fma(b, 0.6366197723675814, kRound), k = km - kRound;
   const double r = fma(-k, kHalfPiLo, fma(-k, kHalfPiHi, b));
   T sr, cr;
   sincos_quarter(static_cast<T>(r), sr, cr);
-  const int qd = static_cast<int>(static_cast<long long>(k) & 3);
-  const T sn = qd == 0 ? sr : qd == 1 ? cr : qd == 2 ? -sr : -cr;
-  const T cs = qd == 0 ? cr : qd == 1 ? -sr : qd == 2 ? -cr : sr;
+  const unsigned qd = static_cast<unsigned>(__double2loint(km));
+  const T sn = flip_sign((qd & 1) ? cr : sr, (qd & 2) << 30);
+  const T cs = flip_sign((qd & 1) ? sr : cr, ((qd + 1) & 2) << 30);
   const T e = exp(static_cast<T>(a));
   return {e * cs, e * sn};
 }
+
+// Orders on the matrix cores and on the vector units: full 16-order tiles go
+// to the MFMAs; a remainder of one or two orders (p = 16: 33 = 2 x 16 + 1,
+// p = 8: 17 = 16 + 1) is accumulated on the vector units instead of a tile of
+// which it would fill at most 2/16; a longer remainder gets a padded tile.
+template <int P> struct OrderSplit {
+  static constexpr int NF = P / 16;
+  static constexpr int REM = P - 16 * NF;
+  static constexpr bool VALU_REM = REM > 0 && REM <= 2;
+  static constexpr int NT = VALU_REM ? NF : (P + 15) / 16;  // MFMA tiles
+  static constexpr int NV = VALU_REM ? REM : 0;             // vector-unit orders, slots 16 NT ..
+};
 
 // One 16x16x4 matrix-core multiply-accumulate in precision T, D = A B + C.
 // Operand layout (both precisions): lane i supplies A[i % 16][i / 16] and

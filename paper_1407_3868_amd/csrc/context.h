@@ -72,7 +72,7 @@ struct FmmStage {
 // on the vertical segment are kept as their own coarse nodes.
 struct SommPlan {
   bool active = false;
-  int nT = 0, nc = 0, nint = 0, ndir = 0, nfb = 0;
+  int nT = 0, nrow = 0, nc = 0, nint = 0, ndir = 0, nfb = 0;
   double tile_w = 0.0, tile_h = 0.0, L_I = 0.0, d_dir = 0.0;
   DBuf perm;        // int32[n]: particles ordered by tile
   DBuf tstart;      // int32[nT + 1]
@@ -87,7 +87,8 @@ struct SommPlan {
   DBuf dir;         // int32[ndir][2]: contour node and coarse node of each direct node
   DBuf G;           // work [nrhs][2][nT][nc] in the matvec precision
   DBuf fblk;        // M2S interval-node blocks: (interval, first node)
-  DBuf trow;        // int32[nT]: tiles in row-major order (by y, then x)
+  DBuf trow;        // int32[nrow][2]: tiles in row-major order (by y, then x) and their steps, in groups of four
+  DBuf tgrp;        // double2[nrow / 4]: centre of each group's first tile
   DBuf Fx;          // double2[ns]: e^{i lam_q w}, the factor between horizontally adjacent tiles
   DBuf Bp;          // S2L node-chunk partials [chunk][nrhs][2][nT][24 nint] in the matvec precision
   const void *sigma = nullptr;  // S2L densities recorded by the coefficient step

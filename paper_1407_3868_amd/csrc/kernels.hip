@@ -369,19 +369,6 @@ __global__ __launch_bounds__(kSapplyThreads) void k_sapply(const cv_t<T> *__rest
 // B[i / 16][i % 16] = beta of that particle and order.  Complex products take
 // three real MFMAs (Gauss: P1 = sum Ar Br, P2 = sum Ai Bi, P3 = sum (Ar + Ai)
 // (Br + Bi); re = P1 - P2, im = P3 - P1 - P2).
-//
-// Orders on the matrix cores and on the vector units: full 16-order tiles go
-// to the MFMAs; a remainder of one or two orders (p = 16: 33 = 2 x 16 + 1,
-// p = 8: 17 = 16 + 1) is accumulated on the vector units instead of a tile of
-// which it would fill at most 2/16; a longer remainder gets a padded tile.
-template <int P> struct OrderSplit {
-  static constexpr int NF = P / 16;
-  static constexpr int REM = P - 16 * NF;
-  static constexpr bool VALU_REM = REM > 0 && REM <= 2;
-  static constexpr int NT = VALU_REM ? NF : (P + 15) / 16;  // MFMA tiles
-  static constexpr int NV = VALU_REM ? REM : 0;             // vector-unit orders, slots 16 NT ..
-};
-
 constexpr int kM2sWaves = 4;
 // Steps of the M2S and S2L products whose operands are in flight.  In FP64 they
 // read an entry of 16 bytes per particle, node and side from HBM, and one step
