@@ -73,10 +73,15 @@ int launch_dotc_multi(mpsl_ctx *ctx, const void *V, int64_t ld, int k, const voi
                       void *h_out, const int32_t *skip = nullptr, int v_prec = MPSL_FP64);
 int launch_gemv_sub(mpsl_ctx *ctx, const void *V, int64_t ld, int k, const void *h, void *w,
                     int64_t len, const int32_t *skip = nullptr, int v_prec = MPSL_FP64);
+// The same, and nrm = ||w||^2 (with skip set: w and nrm stay as they are).  With
+// flag, *flag = ||w||^2 >= eta2 times the real part of before.  Needs
+// gemv_norm_scratch_bytes(len) of ctx->scal.
+size_t gemv_norm_scratch_bytes(int64_t len);
+int launch_gemv_norm(mpsl_ctx *ctx, const void *V, int64_t ld, int k, const void *h, void *w, int64_t len, void *nrm,
+                     const int32_t *skip, int v_prec, const void *before = nullptr, double eta2 = 0.0,
+                     int32_t *flag = nullptr);
 // v32 = s src, rounded to complex64.
 int launch_scale_to_fp32(mpsl_ctx *ctx, void *v32, int64_t len, double s, const void *src);
-// skip = ||after||^2 >= eta2 ||before||^2 (both the real part of a dot product).
-int launch_reorth_flag(mpsl_ctx *ctx, const void *before, const void *after, double eta2, int32_t *skip);
 int launch_scale(mpsl_ctx *ctx, void *v, int64_t len, double s, const void *src);
 // h[i] -= q[i] (q^H h) for i < k (one block): the projection onto span(W)
 // in V coordinates used when a GMRES cycle recycles the first cycle's space.

@@ -680,49 +680,92 @@ __global__ __launch_bounds__(kRed) void k_dotc_part(const TV *__restrict__ V, in
   }
 }
 
-__global__ void k_dotc_final(const double2 *__restrict__ part, int k, int nb, double2 *__restrict__ h,
-                             const int32_t *__restrict__ skip) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
+// Sums of the partials, one wave per value (one lane per value took its 64
+// loads one after another: 5.9 us).
+__global__ __launch_bounds__(256) void k_dotc_final(const double2 *__restrict__ part, int k, int nb,
+                                                    double2 *__restrict__ h, const int32_t *__restrict__ skip) {
+  const int j = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (j >= k) return;
-  if (skip && *skip) {
-    h[j] = make_double2(0.0, 0.0);
-    return;
-  }
+  const bool off = skip && *skip;
   double re = 0.0, im = 0.0;
-  for (int b = 0; b < nb; ++b) {
-    re += part[j * nb + b].x;
-    im += part[j * nb + b].y;
+  if (!off)
+    for (int b = lane; b < nb; b += 64) {
+      const double2 v = part[j * nb + b];
+      re += v.x;
+      im += v.y;
+    }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    re += __shfl_xor(re, o);
+    im += __shfl_xor(im, o);
   }
-  h[j] = make_double2(re, im);
+  if (lane == 0) h[j] = make_double2(re, im);
 }
 
+// w -= V h; with sq also the block's share of ||w||^2 (w is at hand: a dot
+// product of its own read it back in two launches of 5.4 and 1.6 us).
 template <typename TV>
-__global__ void k_gemv_sub(const TV *__restrict__ V, int64_t ld_v, int k,
-                           const double2 *__restrict__ h, double2 *__restrict__ w, int64_t len,
-                           const int32_t *__restrict__ skip) {
+__global__ __launch_bounds__(kRed) void k_gemv_sub(const TV *__restrict__ V, int64_t ld_v, int k,
+                                                   const double2 *__restrict__ h, double2 *__restrict__ w,
+                                                   int64_t len, double *__restrict__ sq,
+                                                   const int32_t *__restrict__ skip) {
+  if (skip && *skip) return;  // the whole grid
   const int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (i >= len || (skip && *skip)) return;
-  cx<double> acc = ld<double>(w[i]);
-  int j = 0;
-  for (; j + 8 <= k; j += 8) {  // eight loads in flight per lane
-    TV a[8];
+  double n2 = 0.0;
+  if (i < len) {
+    cx<double> acc = ld<double>(w[i]);
+    int j = 0;
+    for (; j + 8 <= k; j += 8) {  // eight loads in flight per lane
+      TV a[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) a[u] = V[(j + u) * ld_v + i];
+      for (int u = 0; u < 8; ++u) a[u] = V[(j + u) * ld_v + i];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) acc = acc - mk<double>(a[u].x, a[u].y) * ld<double>(h[j + u]);
+      for (int u = 0; u < 8; ++u) acc = acc - mk<double>(a[u].x, a[u].y) * ld<double>(h[j + u]);
+    }
+    for (; j < k; ++j) {
+      const TV a = V[j * ld_v + i];
+      acc = acc - mk<double>(a.x, a.y) * ld<double>(h[j]);
+    }
+    w[i] = st(acc);
+    n2 = acc.re * acc.re + acc.im * acc.im;
   }
-  for (; j < k; ++j) {
-    const TV a = V[j * ld_v + i];
-    acc = acc - mk<double>(a.x, a.y) * ld<double>(h[j]);
+  if (!sq) return;
+  __shared__ double red[kRed / 64];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = n2;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = red[0];
+#pragma unroll
+    for (int v = 1; v < kRed / 64; ++v) s += red[v];
+    sq[blockIdx.x] = s;
   }
-  w[i] = st(acc);
 }
 
-// Second Gram-Schmidt pass only when the first cancelled much of the vector
-// (Daniel, Gragg, Kaufman and Stewart): skip = ||w after||^2 >= eta2 ||w before||^2.
-__global__ void k_reorth_flag(const double2 *__restrict__ before, const double2 *__restrict__ after, double eta2,
-                              int32_t *__restrict__ skip) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) skip[0] = after->x >= eta2 * before->x ? 1 : 0;
+// nrm = ||w||^2 from the shares of k_gemv_sub (skip: the pass was not needed and
+// nrm stays).  With flag, whether the second Gram-Schmidt pass is needed, which
+// is when the first cancelled much of the vector (Daniel, Gragg, Kaufman and
+// Stewart): flag = ||w after||^2 >= eta2 ||w before||^2.
+__global__ __launch_bounds__(kRed) void k_norm_final(const double *__restrict__ sq, int nb,
+                                                     double2 *__restrict__ nrm, const int32_t *__restrict__ skip,
+                                                     const double2 *__restrict__ before, double eta2,
+                                                     int32_t *__restrict__ flag) {
+  if (skip && *skip) return;
+  __shared__ double red[kRed / 64];
+  double n2 = 0.0;
+  for (int b = threadIdx.x; b < nb; b += kRed) n2 += sq[b];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = n2;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double s = red[0];
+#pragma unroll
+    for (int v = 1; v < kRed / 64; ++v) s += red[v];
+    nrm[0] = make_double2(s, 0.0);
+    if (flag) flag[0] = s >= eta2 * before->x ? 1 : 0;
+  }
 }
 
 __global__ __launch_bounds__(kRed) void k_proj_fix(double2 *__restrict__ h, const double2 *__restrict__ q, int k) {
@@ -1151,22 +1194,41 @@ int launch_dotc_multi(mpsl_ctx *ctx, const void *V, int64_t ld_v, int k, const v
     hipLaunchKernelGGL(k_dotc_part<double2>, grid, dim3(kRed), 0, ctx->stream, static_cast<const double2 *>(V), ld_v,
                        k, static_cast<const double2 *>(w), len, scr, skip);
   LAUNCH_CHECK(ctx);
-  hipLaunchKernelGGL(k_dotc_final, dim3(cdiv(k, 256)), dim3(256), 0, ctx->stream, scr, k, kDotBlocks,
+  hipLaunchKernelGGL(k_dotc_final, dim3(cdiv(k, 4)), dim3(256), 0, ctx->stream, scr, k, kDotBlocks,
                      static_cast<double2 *>(h_out), skip);
+  LAUNCH_CHECK(ctx);
+  return MPSL_OK;
+}
+
+static int gemv_sub(mpsl_ctx *ctx, const void *V, int64_t ld_v, int k, const void *h, void *w, int64_t len,
+                    double *sq, const int32_t *skip, int v_prec) {
+  const dim3 grid(cdiv(len, kRed));
+  if (v_prec == MPSL_FP32)
+    hipLaunchKernelGGL(k_gemv_sub<float2>, grid, dim3(kRed), 0, ctx->stream, static_cast<const float2 *>(V), ld_v, k,
+                       static_cast<const double2 *>(h), static_cast<double2 *>(w), len, sq, skip);
+  else
+    hipLaunchKernelGGL(k_gemv_sub<double2>, grid, dim3(kRed), 0, ctx->stream, static_cast<const double2 *>(V), ld_v,
+                       k, static_cast<const double2 *>(h), static_cast<double2 *>(w), len, sq, skip);
   LAUNCH_CHECK(ctx);
   return MPSL_OK;
 }
 
 int launch_gemv_sub(mpsl_ctx *ctx, const void *V, int64_t ld_v, int k, const void *h, void *w, int64_t len,
                     const int32_t *skip, int v_prec) {
-  if (v_prec == MPSL_FP32)
-    hipLaunchKernelGGL(k_gemv_sub<float2>, dim3(cdiv(len, 256)), dim3(256), 0, ctx->stream,
-                       static_cast<const float2 *>(V), ld_v, k, static_cast<const double2 *>(h),
-                       static_cast<double2 *>(w), len, skip);
-  else
-    hipLaunchKernelGGL(k_gemv_sub<double2>, dim3(cdiv(len, 256)), dim3(256), 0, ctx->stream,
-                       static_cast<const double2 *>(V), ld_v, k, static_cast<const double2 *>(h),
-                       static_cast<double2 *>(w), len, skip);
+  return gemv_sub(ctx, V, ld_v, k, h, w, len, nullptr, skip, v_prec);
+}
+
+size_t gemv_norm_scratch_bytes(int64_t len) { return static_cast<size_t>(cdiv(len, kRed)) * sizeof(double); }
+
+int launch_gemv_norm(mpsl_ctx *ctx, const void *V, int64_t ld_v, int k, const void *h, void *w, int64_t len,
+                     void *nrm, const int32_t *skip, int v_prec, const void *before, double eta2, int32_t *flag) {
+  if (ctx->scal.bytes < gemv_norm_scratch_bytes(len))
+    return set_err(ctx, MPSL_EINVAL, "reduction scratch too small for the norm");
+  auto *sq = static_cast<double *>(ctx->scal.p);
+  const int rc = gemv_sub(ctx, V, ld_v, k, h, w, len, sq, skip, v_prec);
+  if (rc) return rc;
+  hipLaunchKernelGGL(k_norm_final, dim3(1), dim3(kRed), 0, ctx->stream, sq, cdiv(len, kRed),
+                     static_cast<double2 *>(nrm), skip, static_cast<const double2 *>(before), eta2, flag);
   LAUNCH_CHECK(ctx);
   return MPSL_OK;
 }
@@ -1174,13 +1236,6 @@ int launch_gemv_sub(mpsl_ctx *ctx, const void *V, int64_t ld_v, int k, const voi
 int launch_scale_to_fp32(mpsl_ctx *ctx, void *v32, int64_t len, double s, const void *src) {
   hipLaunchKernelGGL(k_scale_to32, dim3(cdiv(len, 256)), dim3(256), 0, ctx->stream, static_cast<float2 *>(v32),
                      static_cast<const double2 *>(src), len, s);
-  LAUNCH_CHECK(ctx);
-  return MPSL_OK;
-}
-
-int launch_reorth_flag(mpsl_ctx *ctx, const void *before, const void *after, double eta2, int32_t *skip) {
-  hipLaunchKernelGGL(k_reorth_flag, dim3(1), dim3(64), 0, ctx->stream, static_cast<const double2 *>(before),
-                     static_cast<const double2 *>(after), eta2, skip);
   LAUNCH_CHECK(ctx);
   return MPSL_OK;
 }

@@ -42,7 +42,7 @@ int SolveSM::init(mpsl_ctx *ctx, const mpsl_opts &o, const void *b_dev) {
                                          std::to_string(kMaxKrylov));
   const size_t c = sizeof(double2);
   // the Arnoldi dot products reduce m + 1 rows of partial sums at once
-  int rc = dev_alloc(ctx, ctx->scal, dotc_scratch_bytes(m_ + 2));
+  int rc = dev_alloc(ctx, ctx->scal, std::max(dotc_scratch_bytes(m_ + 2), gemv_norm_scratch_bytes(len_)));
   if (rc) return rc;
   vp_ = o_.precision == MPSL_FP32 ? MPSL_FP32 : MPSL_FP64;
   const size_t vb = vp_ == MPSL_FP32 ? sizeof(float2) : sizeof(double2);
@@ -210,15 +210,10 @@ int SolveSM::launch() {
       return rc;
     }
     if (k0_ > 0 && (rc = launch_proj_fix(ctx, h_, q_, k0_ + 1))) return rc;
-    if ((rc = launch_gemv_sub(ctx, V_, len_, nb, h_, vn, len_, nullptr, vp_)) ||
-        (rc = launch_dotc_multi(ctx, vn, 0, 1, vn, len_, nrm_)) ||
-        (rc = launch_reorth_flag(ctx, h_ + nb, nrm_, 0.5, skip_)))
-      return rc;
+    if ((rc = launch_gemv_norm(ctx, V_, len_, nb, h_, vn, len_, nrm_, nullptr, vp_, h_ + nb, 0.5, skip_))) return rc;
     if ((rc = launch_dotc_multi(ctx, V_, len_, nb, vn, len_, h2_, skip_, vp_))) return rc;
     if (k0_ > 0 && (rc = launch_proj_fix(ctx, h2_, q_, k0_ + 1))) return rc;
-    if ((rc = launch_gemv_sub(ctx, V_, len_, nb, h2_, vn, len_, skip_, vp_)) ||
-        (rc = launch_dotc_multi(ctx, vn, 0, 1, vn, len_, nrm_)))
-      return rc;
+    if ((rc = launch_gemv_norm(ctx, V_, len_, nb, h2_, vn, len_, nrm_, skip_, vp_))) return rc;
     MPSL_HIP_TRY(ctx, hipMemcpyAsync(hh_ + 3 * (m_ + 2) + 1, skip_, sizeof(int32_t), hipMemcpyDeviceToHost,
                                      ctx->stream));
     MPSL_HIP_TRY(ctx, hipMemcpyAsync(hh_, h_, nb * c, hipMemcpyDeviceToHost, ctx->stream));
