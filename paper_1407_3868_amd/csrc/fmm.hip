@@ -254,52 +254,87 @@ double near_cost(const Grid &g, int64_t n, int Pp) {
 // Device kernels.
 
 // P2M: one block per leaf box, one lane per output slot of the box multipole.
+// The parts of kb particles' table rows that the block's slots reach (wl
+// entries each) and their coefficients are staged in LDS with all loads in
+// flight.  Bound by the latency of that staging, one or two rounds per box:
+// read row by row from L2, with a barrier pair per particle, 20000 particles
+// at p = 16 took 87 us in FP32, now @P.
 template <typename T>
 __global__ void k_fmm_p2m(const cv_t<T> *__restrict__ beta, const int *__restrict__ perm,
-                          const int *__restrict__ start, const cv_t<T> *__restrict__ tab, int P, int P0,
-                          cv_t<T> *__restrict__ mout) {
-  __shared__ cx<T> bs[2 * kMaxP + 1];
+                          const int *__restrict__ start, const cv_t<T> *__restrict__ tab, int P, int P0, int kb,
+                          int wl, cv_t<T> *__restrict__ mout) {
+  extern __shared__ __align__(16) unsigned char p2m_smem[];
   const int b = blockIdx.x;
   const int i0 = start[b], i1 = start[b + 1];
   if (i0 == i1) return;
   const int tl = P0 + P - 1;
-  const int nrounds = cdiv(P0, blockDim.x);
-  for (int r = 0; r < nrounds; ++r) {
-    const int jo = r * blockDim.x + threadIdx.x;
+  cv_t<T> *Rs = reinterpret_cast<cv_t<T> *>(p2m_smem);  // [kb][wl]
+  cv_t<T> *bs = Rs + kb * wl;                           // [kb][P]
+  for (int o0 = 0; o0 < P0; o0 += blockDim.x) {
+    const int jo = o0 + threadIdx.x;
+    const int lo = max(0, P0 - o0 - static_cast<int>(blockDim.x));  // first entry of the rows reached
+    const int wn = P0 - o0 + P - 1 - lo;                            // entries reached, <= wl
     cx<T> acc = mk<T>(0, 0);
-    for (int i = i0; i < i1; ++i) {
-      __syncthreads();
-      if (threadIdx.x < P) bs[threadIdx.x] = ld<T>(beta[static_cast<int64_t>(perm[i]) * P + threadIdx.x]);
+    for (int ib = i0; ib < i1; ib += kb) {
+      const int nb = min(kb, i1 - ib);
+      __syncthreads();  // the previous particles consumed
+      const cv_t<T> *src = tab + static_cast<int64_t>(ib) * tl + lo;
+#pragma unroll 4
+      for (int e = threadIdx.x; e < nb * wn; e += blockDim.x) {
+        const int i = e / wn, x = e - i * wn;
+        Rs[i * wl + x] = src[static_cast<int64_t>(i) * tl + x];
+      }
+      for (int e = threadIdx.x; e < nb * P; e += blockDim.x)
+        bs[e] = beta[static_cast<int64_t>(perm[ib + e / P]) * P + e % P];
       __syncthreads();
       if (jo < P0) {
-        const cv_t<T> *row = tab + static_cast<int64_t>(i) * tl + (P0 - 1) - jo;
-        for (int j = 0; j < P; ++j) cmac(acc, ld<T>(row[j]), bs[j]);
+        for (int i = 0; i < nb; ++i) {
+          const cv_t<T> *row = Rs + i * wl + (P0 - 1) - jo - lo;
+#pragma unroll 4
+          for (int j = 0; j < P; ++j) cmac(acc, ld<T>(row[j]), ld<T>(bs[i * P + j]));
+        }
       }
     }
     if (jo < P0) mout[static_cast<int64_t>(b) * P0 + jo] = st(acc);
   }
 }
 
-// L2P: one block per leaf box; lanes over (particle, output slot).
+// L2P: one block per leaf box, one lane per (particle, output slot) of kb
+// particles (kb P <= the block's lanes), input slots in windows of jw with
+// their share of the table rows staged in LDS as in P2M (39 us -> @L there).
 template <typename T>
 __global__ void k_fmm_l2p(const cv_t<T> *__restrict__ lin, const int *__restrict__ perm,
-                          const int *__restrict__ start, const cv_t<T> *__restrict__ tab, int P, int P0,
-                          cv_t<T> *__restrict__ out) {
+                          const int *__restrict__ start, const cv_t<T> *__restrict__ tab, int P, int P0, int kb,
+                          int jw, cv_t<T> *__restrict__ out) {
   extern __shared__ __align__(16) unsigned char l2p_smem[];
-  cx<T> *Ls = reinterpret_cast<cx<T> *>(l2p_smem);
   const int b = blockIdx.x;
   const int i0 = start[b], i1 = start[b + 1];
   if (i0 == i1) return;
-  for (int j = threadIdx.x; j < P0; j += blockDim.x) Ls[j] = ld<T>(lin[static_cast<int64_t>(b) * P0 + j]);
-  __syncthreads();
-  const int tl = P0 + P - 1;
-  const int tot = (i1 - i0) * P;
-  for (int t = threadIdx.x; t < tot; t += blockDim.x) {
-    const int i = i0 + t / P, jo = t % P;
-    const cv_t<T> *row = tab + static_cast<int64_t>(i) * tl + (P - 1) - jo;
+  const int tl = P0 + P - 1, wl = jw + P - 1;
+  cv_t<T> *Ls = reinterpret_cast<cv_t<T> *>(l2p_smem);  // [jw]
+  cv_t<T> *Rs = Ls + jw;                                // [kb][wl]
+  const int li = threadIdx.x / P, jo = threadIdx.x - li * P;
+  for (int ib = i0; ib < i1; ib += kb) {
+    const int nb = min(kb, i1 - ib);
     cx<T> acc = mk<T>(0, 0);
-    for (int j = 0; j < P0; ++j) cmac(acc, ld<T>(row[j]), Ls[j]);
-    out[static_cast<int64_t>(perm[i]) * P + jo] = st(acc);
+    for (int j0 = 0; j0 < P0; j0 += jw) {
+      const int jn = min(jw, P0 - j0), wn = jn + P - 1;
+      __syncthreads();  // the previous window consumed
+      for (int j = threadIdx.x; j < jn; j += blockDim.x) Ls[j] = lin[static_cast<int64_t>(b) * P0 + j0 + j];
+      const cv_t<T> *src = tab + static_cast<int64_t>(ib) * tl + j0;
+#pragma unroll 4
+      for (int e = threadIdx.x; e < nb * wn; e += blockDim.x) {
+        const int i = e / wn, x = e - i * wn;
+        Rs[i * wl + x] = src[static_cast<int64_t>(i) * tl + x];
+      }
+      __syncthreads();
+      if (li < nb) {
+        const cv_t<T> *row = Rs + li * wl + (P - 1) - jo;
+#pragma unroll 4
+        for (int j = 0; j < jn; ++j) cmac(acc, ld<T>(row[j]), ld<T>(Ls[j]));
+      }
+    }
+    if (li < nb) out[static_cast<int64_t>(perm[ib + li]) * P + jo] = st(acc);
   }
 }
 
@@ -1057,9 +1092,17 @@ int fmm_apply_t(mpsl_ctx *ctx, int pi, const void *beta, void *part) {
   const cv_t<T> *b = static_cast<const cv_t<T> *>(beta);
   cv_t<T> *xb = static_cast<cv_t<T> *>(f.xb.p);
   const cv_t<T> *tab = static_cast<const cv_t<T> *>(f.tab[pi].p);
+  // particles staged at once: one round for a typical box of 8 to 10 (P2M), as
+  // many as the block has lanes for (L2P), within 32 KiB of LDS
   const int bs = std::min(256, cdiv(P0, 64) * 64);
-  hipLaunchKernelGGL(k_fmm_p2m<T>, dim3(nb0), dim3(bs), 0, ctx->stream, b, static_cast<const int *>(f.perm.p),
-                     static_cast<const int *>(f.start.p), tab + f.p2m_off[pi], P, P0, xb + f.lv[0].moff[pi]);
+  const int wl = std::min(P0, bs) + P - 1, jw = std::min(P0, 256);
+  const int esz = sizeof(cv_t<T>);
+  const int kb = std::max(1, std::min(10, 32768 / ((wl + P) * esz)));
+  const int kl = std::max(1, std::min(256 / P, 32768 / ((jw + P - 1) * esz)));
+  const size_t lds_p = static_cast<size_t>(kb) * (wl + P) * esz;
+  const size_t lds_l = (static_cast<size_t>(kl) * (jw + P - 1) + jw) * esz;
+  hipLaunchKernelGGL(k_fmm_p2m<T>, dim3(nb0), dim3(bs), lds_p, ctx->stream, b, static_cast<const int *>(f.perm.p),
+                     static_cast<const int *>(f.start.p), tab + f.p2m_off[pi], P, P0, kb, wl, xb + f.lv[0].moff[pi]);
   MPSL_HIP_TRY(ctx, hipGetLastError());
   int rc;
   for (const auto &st : f.up[pi])
@@ -1068,9 +1111,9 @@ int fmm_apply_t(mpsl_ctx *ctx, int pi, const void *beta, void *part) {
     if ((rc = launch_stage<T>(ctx, pi, st))) return rc;
   const int64_t len = ctx->n * static_cast<int64_t>(P);
   cv_t<T> *far = static_cast<cv_t<T> *>(part) + f.near_chunks * len;
-  hipLaunchKernelGGL(k_fmm_l2p<T>, dim3(nb0), dim3(256), P0 * sizeof(cx<T>), ctx->stream,
+  hipLaunchKernelGGL(k_fmm_l2p<T>, dim3(nb0), dim3(256), lds_l, ctx->stream,
                      static_cast<const cv_t<T> *>(xb + f.lv[0].loff[pi]), static_cast<const int *>(f.perm.p),
-                     static_cast<const int *>(f.start.p), tab + f.l2p_off[pi], P, P0, far);
+                     static_cast<const int *>(f.start.p), tab + f.l2p_off[pi], P, P0, kl, jw, far);
   MPSL_HIP_TRY(ctx, hipGetLastError());
   return launch_fmm_near(ctx, pi == 0 ? MPSL_FP64 : MPSL_FP32, beta, part);
 }
