@@ -258,7 +258,7 @@ double near_cost(const Grid &g, int64_t n, int Pp) {
 // entries each) and their coefficients are staged in LDS with all loads in
 // flight.  Bound by the latency of that staging, one or two rounds per box:
 // read row by row from L2, with a barrier pair per particle, 20000 particles
-// at p = 16 took 87 us in FP32, now @P.
+// at p = 16 took 87 us in FP32, now 36.
 template <typename T>
 __global__ void k_fmm_p2m(const cv_t<T> *__restrict__ beta, const int *__restrict__ perm,
                           const int *__restrict__ start, const cv_t<T> *__restrict__ tab, int P, int P0, int kb,
@@ -301,7 +301,7 @@ __global__ void k_fmm_p2m(const cv_t<T> *__restrict__ beta, const int *__restric
 
 // L2P: one block per leaf box, one lane per (particle, output slot) of kb
 // particles (kb P <= the block's lanes), input slots in windows of jw with
-// their share of the table rows staged in LDS as in P2M (39 us -> @L there).
+// their share of the table rows staged in LDS as in P2M (39 us -> 31 there).
 template <typename T>
 __global__ void k_fmm_l2p(const cv_t<T> *__restrict__ lin, const int *__restrict__ perm,
                           const int *__restrict__ start, const cv_t<T> *__restrict__ tab, int P, int P0, int kb,

@@ -84,7 +84,7 @@ class SolveSM {
   double2 *h_ = nullptr, *h2_ = nullptr, *nrm_ = nullptr;
   float2 *x32_ = nullptr, *y32_ = nullptr;
   // pinned host staging
-  double2 *hh_ = nullptr;  // pinned: h, h2 (m + 2 each), norm, y (m + 1), second-pass flag
+  double2 *hh_ = nullptr;  // pinned: second-pass flag, norm, h, h2 (m + 2 each), y (m + 1)
   // host Hessenberg state
   std::vector<zc> H_, cs_, sn_, gv_;
   int j_ = 0;

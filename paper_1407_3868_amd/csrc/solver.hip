@@ -63,16 +63,18 @@ int SolveSM::init(mpsl_ctx *ctx, const mpsl_opts &o, const void *b_dev) {
   xs_ = reinterpret_cast<double2 *>(take(len_ * c));
   b_ = reinterpret_cast<double2 *>(take(len_ * c));
   d_ = reinterpret_cast<double2 *>(take(len_ * c));
-  h_ = reinterpret_cast<double2 *>(take((m_ + 2) * c));
-  h2_ = reinterpret_cast<double2 *>(take((m_ + 2) * c));
-  nrm_ = reinterpret_cast<double2 *>(take((m_ + 2) * c));
+  // what the host reads after an Arnoldi step, in the order of hh_: one copy
+  auto *step = reinterpret_cast<double2 *>(take((2 * static_cast<size_t>(m_ + 2) + 2) * c));
+  skip_ = reinterpret_cast<int32_t *>(step);
+  nrm_ = step + 1;
+  h_ = step + 2;
+  h2_ = h_ + (m_ + 2);
   q_ = reinterpret_cast<double2 *>(take((m_ + 2) * c));
-  skip_ = reinterpret_cast<int32_t *>(take(256));
   x32_ = reinterpret_cast<float2 *>(take(len_ * sizeof(float2)));
   y32_ = reinterpret_cast<float2 *>(take(len_ * sizeof(float2)));
   if (hh_) (void)hipHostFree(hh_);
   hh_ = nullptr;
-  // pinned staging: h (m+2), h2 (m+2), norm (1), y (m+1), second-pass flag (1)
+  // pinned staging: second-pass flag (1), norm (1), h (m+2), h2 (m+2), y (m+1)
   if (hipHostMalloc(reinterpret_cast<void **>(&hh_), (3 * static_cast<size_t>(m_ + 2) + 2) * c) != hipSuccess) {
     hh_ = nullptr;
     return set_err(ctx, MPSL_ENOMEM, "pinned host allocation failed");
@@ -94,9 +96,9 @@ int SolveSM::init(mpsl_ctx *ctx, const mpsl_opts &o, const void *b_dev) {
   MPSL_HIP_TRY(ctx, hipMemsetAsync(xs_, 0, len_ * c, ctx->stream));
   if ((rc = launch_scale(ctx, r_, len_, 1.0, b_))) return rc;
   if ((rc = launch_dotc_multi(ctx, b_, 0, 1, b_, len_, nrm_))) return rc;
-  MPSL_HIP_TRY(ctx, hipMemcpyAsync(hh_ + 2 * (m_ + 2), nrm_, c, hipMemcpyDeviceToHost, ctx->stream));
+  MPSL_HIP_TRY(ctx, hipMemcpyAsync(hh_ + 1, nrm_, c, hipMemcpyDeviceToHost, ctx->stream));
   MPSL_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-  bn_ = std::sqrt(std::max(hh_[2 * (m_ + 2)].x, 0.0));
+  bn_ = std::sqrt(std::max(hh_[1].x, 0.0));
   if (!std::isfinite(bn_)) return set_err(ctx, MPSL_ENUMERIC, "non-finite right-hand side");
   if (bn_ == 0.0) {
     status_ = kConverged;
@@ -145,17 +147,17 @@ int SolveSM::begin_inner() {
           (rc = launch_proj_fix(ctx, h_, q_, k0_ + 1)) ||
           (rc = launch_gemv_sub(ctx, V_, len_, k0_ + 1, h_, r_, len_, nullptr, vp_)))
         return rc;
-      MPSL_HIP_TRY(ctx, hipMemcpyAsync(hh_, h_, (k0_ + 1) * c, hipMemcpyDeviceToHost, ctx->stream));
+      MPSL_HIP_TRY(ctx, hipMemcpyAsync(hh_ + 2, h_, (k0_ + 1) * c, hipMemcpyDeviceToHost, ctx->stream));
       MPSL_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
       std::vector<zc> sv(k0_ + 1);
-      for (int i = 0; i <= k0_; ++i) sv[i] = zc(hh_[i].x, hh_[i].y);
+      for (int i = 0; i <= k0_; ++i) sv[i] = zc(hh_[2 + i].x, hh_[2 + i].y);
       const std::vector<zc> f = w_coords(sv);
       for (int i = 0; i < k0_; ++i) yC_[i] += f[i];
     }
     if ((rc = launch_dotc_multi(ctx, r_, 0, 1, r_, len_, nrm_))) return rc;
-    MPSL_HIP_TRY(ctx, hipMemcpyAsync(hh_ + 2 * (m_ + 2), nrm_, c, hipMemcpyDeviceToHost, ctx->stream));
+    MPSL_HIP_TRY(ctx, hipMemcpyAsync(hh_ + 1, nrm_, c, hipMemcpyDeviceToHost, ctx->stream));
     MPSL_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-    rn = std::sqrt(std::max(hh_[2 * (m_ + 2)].x, 0.0));
+    rn = std::sqrt(std::max(hh_[1].x, 0.0));
   }
   H_.assign(static_cast<size_t>(m_ + 1) * m_, zc(0.0, 0.0));
   cs_.assign(m_, zc(0.0, 0.0));
@@ -214,17 +216,14 @@ int SolveSM::launch() {
     if ((rc = launch_dotc_multi(ctx, V_, len_, nb, vn, len_, h2_, skip_, vp_))) return rc;
     if (k0_ > 0 && (rc = launch_proj_fix(ctx, h2_, q_, k0_ + 1))) return rc;
     if ((rc = launch_gemv_norm(ctx, V_, len_, nb, h2_, vn, len_, nrm_, skip_, vp_))) return rc;
-    MPSL_HIP_TRY(ctx, hipMemcpyAsync(hh_ + 3 * (m_ + 2) + 1, skip_, sizeof(int32_t), hipMemcpyDeviceToHost,
+    MPSL_HIP_TRY(ctx, hipMemcpyAsync(hh_, skip_, (2 + static_cast<size_t>(m_ + 2) + nb) * c, hipMemcpyDeviceToHost,
                                      ctx->stream));
-    MPSL_HIP_TRY(ctx, hipMemcpyAsync(hh_, h_, nb * c, hipMemcpyDeviceToHost, ctx->stream));
-    MPSL_HIP_TRY(ctx, hipMemcpyAsync(hh_ + (m_ + 2), h2_, nb * c, hipMemcpyDeviceToHost, ctx->stream));
-  } else {
-    if ((rc = matvec(ctx, MPSL_FP64, xs_, w_)) || (rc = launch_scale(ctx, r_, len_, 1.0, b_)) ||
-        (rc = launch_axpy_c(ctx, r_, w_, len_, -1.0, 0.0)) ||
-        (rc = launch_dotc_multi(ctx, r_, 0, 1, r_, len_, nrm_)))
-      return rc;
+    return MPSL_OK;
   }
-  MPSL_HIP_TRY(ctx, hipMemcpyAsync(hh_ + 2 * (m_ + 2), nrm_, c, hipMemcpyDeviceToHost, ctx->stream));
+  if ((rc = matvec(ctx, MPSL_FP64, xs_, w_)) || (rc = launch_scale(ctx, r_, len_, 1.0, b_)) ||
+      (rc = launch_axpy_c(ctx, r_, w_, len_, -1.0, 0.0)) || (rc = launch_dotc_multi(ctx, r_, 0, 1, r_, len_, nrm_)))
+    return rc;
+  MPSL_HIP_TRY(ctx, hipMemcpyAsync(hh_ + 1, nrm_, c, hipMemcpyDeviceToHost, ctx->stream));
   return MPSL_OK;
 }
 
@@ -232,18 +231,19 @@ int SolveSM::complete() {
   if (status_ != kRunning) return MPSL_OK;
   mpsl_ctx *ctx = ctx_;
   MPSL_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-  const double nn = std::sqrt(std::max(hh_[2 * (m_ + 2)].x, 0.0));
+  const double nn = std::sqrt(std::max(hh_[1].x, 0.0));
   int rc;
   if (phase_ == kInner) {
     ++inner_mv_;
     if (o_.precision == MPSL_FP64) ++fp64_mv_;
     const int j = j_, m = m_, b0 = base_;
     if (!std::isfinite(nn)) return set_err(ctx, MPSL_ENUMERIC, "non-finite Arnoldi norm");
-    if (*reinterpret_cast<const int32_t *>(hh_ + 3 * (m_ + 2) + 1) == 0) ++reorth_;
+    if (*reinterpret_cast<const int32_t *>(hh_) == 0) ++reorth_;
+    const double2 *h = hh_ + 2, *h2 = h + (m + 2);
     for (int i = 0; i <= j; ++i)
-      H_[i * m + j] = zc(hh_[b0 + i].x + hh_[m + 2 + b0 + i].x, hh_[b0 + i].y + hh_[m + 2 + b0 + i].y);
+      H_[i * m + j] = zc(h[b0 + i].x + h2[b0 + i].x, h[b0 + i].y + h2[b0 + i].y);
     for (int i = 0; b0 > 0 && i <= k0_; ++i)  // coefficients on V_{k0+1} (projected onto W)
-      Cs_.push_back(zc(hh_[i].x + hh_[m + 2 + i].x, hh_[i].y + hh_[m + 2 + i].y));
+      Cs_.push_back(zc(h[i].x + h2[i].x, h[i].y + h2[i].y));
     H_[(j + 1) * m + j] = nn;
     if (nn > 0.0 &&
         (rc = store_basis(b0 + j + 1, 1.0 / nn, vp_ == MPSL_FP32 ? u_ : static_cast<const double2 *>(vslot(b0 + j + 1)))))
@@ -314,7 +314,7 @@ int SolveSM::finish_cycle() {
     }
   }
   for (int i = 0; i < j; ++i) coef[base_ + i] = y[i];
-  double2 *hy = hh_ + 2 * (m_ + 2) + 1;  // pinned, separate from the D2H staging
+  double2 *hy = hh_ + 2 * (m_ + 2) + 2;  // pinned, separate from the D2H staging
   for (int i = 0; i < nb; ++i) hy[i] = make_double2(-coef[i].real(), -coef[i].imag());
   MPSL_HIP_TRY(ctx, hipMemcpyAsync(h_, hy, nb * sizeof(double2), hipMemcpyHostToDevice, ctx->stream));
   MPSL_HIP_TRY(ctx, hipMemsetAsync(d_, 0, len_ * sizeof(double2), ctx->stream));
