@@ -905,7 +905,11 @@ static int s2l_resident(int p) {
 int chunks_s2l(const mpsl_ctx *ctx, int nrhs, int prec) {
   if (ctx->somm.active) {  // the interpolated S2L: chunks of coarse nodes, one slot each
     const int tb = cdiv(ctx->n, 128) * nrhs;
-    return std::max(1, std::min(64, std::min(cdiv(1024, tb), 2 * ctx->somm.nc)));
+    const int c0 = std::max(1, std::min(64, std::min(cdiv(1024, tb), 2 * ctx->somm.nc)));
+    // fewer where the blocks (64 particles) would give some compute units a
+    // second one and others not (300 particles, FP64: 64 chunks 15.8 us, 51 12.9)
+    const int64_t nb = static_cast<int64_t>(cdiv(ctx->n, 64)) * nrhs;
+    return nb * c0 > ctx->n_cu && nb * c0 < 2 * ctx->n_cu ? static_cast<int>(ctx->n_cu / nb) : c0;
   }
   if (ctx->s2l_chunks > 0) return std::min(ctx->s2l_chunks, ctx->ns);
   // about 1024 blocks of 128 lanes' worth of particles, at least 8 nodes per
