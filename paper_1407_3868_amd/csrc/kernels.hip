@@ -99,6 +99,12 @@ __global__ void k_pair_tables(const double2 *__restrict__ xy, int n, double k2, 
 // 1024 nodes, FP32: 15.4 + 4.6 + 4.7 us; 20000: 28.3 us for the sums alone,
 // whose lanes walked up to 109 chunks in series).
 constexpr int kNodeBlock = 16, kNodeLanes = 8;
+// c_q sigma_s(q) from the spectra of both sides of node q (reflection map).
+__device__ inline cx<double> node_density(const double2 *__restrict__ R, const double2 *__restrict__ cq, int q, int s,
+                                          cx<double> pp, cx<double> pm) {
+  return ld<double>(cq[q]) * (ld<double>(R[4 * q + 2 * s]) * pp + ld<double>(R[4 * q + 2 * s + 1]) * pm);
+}
+
 template <typename T>
 __global__ __launch_bounds__(2 * kNodeBlock *kNodeLanes) void k_nodes(
     const cv_t<T> *__restrict__ part, int ns, int chunks, const double2 *__restrict__ R,
@@ -135,9 +141,7 @@ __global__ __launch_bounds__(2 * kNodeBlock *kNodeLanes) void k_nodes(
   __syncthreads();
   if (cl == 0) {
     const int qc = min(q, ns - 1);
-    const cx<double> sg = ld<double>(R[4 * qc + 2 * s]) * ld<double>(sum[0][0][qi]) +
-                          ld<double>(R[4 * qc + 2 * s + 1]) * ld<double>(sum[0][1][qi]);
-    val[s][qi] = st(ld<double>(cq[qc]) * sg);
+    val[s][qi] = st(node_density(R, cq, qc, s, ld<double>(sum[0][0][qi]), ld<double>(sum[0][1][qi])));
   }
   __syncthreads();
   const int cnt = min(kNodeBlock, ns - q0) * P;
@@ -378,22 +382,26 @@ constexpr int kM2sWaves = 4;
 // more than it gives (20000 particles, 1024 nodes, p = 16: S2L 123 us with one
 // step, fetched only where there is one, 143 with two).
 template <typename T> constexpr int gemm_depth() { return sizeof(T) == 8 ? 4 : 1; }
-template <typename T, int p>
-__global__ __launch_bounds__(64 * kM2sWaves) void k_m2s_mfma(const cv_t<T> *__restrict__ E,
-                                                             const cv_t<T> *__restrict__ beta,
-                                                             const cv_t<T> *__restrict__ W,
-                                                             cv_t<T> *__restrict__ part, int n, int ns,
-                                                             int chunk_len, int chunks) {
+// NODES: the matvec with one chunk (few particles) takes both sides of a node
+// group in one block and goes on to the S2L coefficients, which saves the
+// launch of k_nodes (16 particles, p = 8, FP64, matvec: 23.6 -> 21.7 us).
+template <typename T, int p, bool NODES>
+__global__ __launch_bounds__(64 * kM2sWaves) void k_m2s_mfma(
+    const cv_t<T> *__restrict__ E, const cv_t<T> *__restrict__ beta, const cv_t<T> *__restrict__ W,
+    cv_t<T> *__restrict__ part, int n, int ns, int chunk_len, int chunks, const double2 *__restrict__ R,
+    const double2 *__restrict__ cq, const double2 *__restrict__ U, cv_t<T> *__restrict__ Up) {
+  constexpr int kGroups = kM2sWaves / 2;  // node groups of a NODES block
+  __shared__ double2 nsum[NODES ? kGroups : 1][2][16], nval[NODES ? kGroups : 1][2][16];
   constexpr int P = 2 * p + 1;
   constexpr int NT = OrderSplit<P>::NT, NV = OrderSplit<P>::NV;
   typedef typename mfma4<T>::v4 v4;
   const int c = blockIdx.y;
-  const int s = blockIdx.z & 1;   // side
-  const int r = blockIdx.z >> 1;  // right-hand side
-  beta += static_cast<int64_t>(r) * n * P;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int q0 = (blockIdx.x * kM2sWaves + w) * 16;
-  if (q0 >= ns) return;  // the whole wave lies past the last node (no barriers below)
+  const int s = NODES ? w & 1 : blockIdx.z & 1;           // side
+  const int r = NODES ? blockIdx.z : blockIdx.z >> 1;     // right-hand side
+  beta += static_cast<int64_t>(r) * n * P;
+  const int q0 = (NODES ? blockIdx.x * kGroups + (w >> 1) : blockIdx.x * kM2sWaves + w) * 16;
+  if (!NODES && q0 >= ns) return;  // the whole wave lies past the last node (no barriers below)
   const int m0 = c * chunk_len;
   const int m1 = min(n, m0 + chunk_len);
   const int qi = q0 + (lane & 15);
@@ -480,7 +488,28 @@ __global__ __launch_bounds__(64 * kM2sWaves) void k_m2s_mfma(const cv_t<T> *__re
       const cx<T> g = mk<T>(__shfl(vr[v].re, row), __shfl(vr[v].im, row));
       cmac(acc, g, ld<T>(Ws[static_cast<int64_t>(qc) * P + 16 * NT + v]));
     }
-    if ((lane & 15) == 0 && q < ns) o[q] = st(acc);
+    if constexpr (NODES) {
+      if ((lane & 15) == 0) nsum[w >> 1][s][row] = make_double2(acc.re, acc.im);
+    } else {
+      if ((lane & 15) == 0 && q < ns) o[q] = st(acc);
+    }
+  }
+  if constexpr (NODES) {
+    const int tid = threadIdx.x, b0 = blockIdx.x * kGroups * 16;
+    __syncthreads();
+    if (tid < 32 * kGroups) {
+      const int g = tid / 32, sd = tid / 16 % 2, qi = tid % 16;
+      nval[g][sd][qi] = st(node_density(R, cq, min(b0 + 16 * g + qi, ns - 1), sd, ld<double>(nsum[g][0][qi]),
+                                        ld<double>(nsum[g][1][qi])));
+    }
+    __syncthreads();
+    const int cnt = min(16 * kGroups, ns - b0) * P;
+    for (int i = tid; i < 2 * cnt; i += 64 * kM2sWaves) {
+      const int sd = i >= cnt ? 1 : 0, e = i - sd * cnt, node = e / P;
+      const int64_t base = static_cast<int64_t>(sd) * ns * P + static_cast<int64_t>(b0) * P + e;
+      const cx<double> v = ld<double>(nval[node / 16][sd][node % 16]) * ld<double>(U[base]);
+      Up[2 * static_cast<int64_t>(r) * ns * P + base] = st(mk(static_cast<T>(v.re), static_cast<T>(v.im)));
+    }
   }
 }
 
@@ -940,7 +969,7 @@ static int m2s_resident(int p) {
   const void *fn = nullptr;
   switch (p) {
 #define X(PP) \
-  case PP: fn = reinterpret_cast<const void *>(&k_m2s_mfma<T, PP>); break;
+  case PP: fn = reinterpret_cast<const void *>(&k_m2s_mfma<T, PP, false>); break;
     MPSL_P_CASES(X)
 #undef X
   }
@@ -958,10 +987,16 @@ int chunks_m2s(const mpsl_ctx *ctx, int nrhs, int prec) {
   // about 2048 node-group x chunk tasks, but at least 80 particles per chunk:
   // shorter chunks spend more on the epilogue and on summing the partials
   // than they gain in parallelism (1024 nodes, 5000 particles: 256 -> 63
-  // chunks, M2S and partial sum 75 -> about 45 us in FP32)
+  // chunks, M2S and partial sum 75 -> about 45 us in FP32).  Up to 16 chunks 32
+  // particles will do: their steps are a serial chain (512 nodes, p = 16, whole
+  // matvec, chunks of 80 and 32: 203 particles 48.9 and 44.9 us in FP64, 35.6
+  // and 34.2 in FP32; 500: 79.8 and 76.4, 59.9 and 56.5).  One chunk to 48, which
+  // needs no k_nodes (p = 8, FP64, one and two chunks: 16 particles 21.7 and
+  // 23.6 us, 48: 24.4 and 25.4, 64: 25.4 and 25.6).
   const int qb = cdiv(ctx->ns, kThreads) * 2 * nrhs;
-  const int c0 = static_cast<int>(std::max<int64_t>(
-      1, std::min<int64_t>(std::min<int64_t>(cdiv(2048, qb), cdiv(ctx->n, 80)), ctx->n)));
+  const int64_t by_n = std::max<int64_t>(cdiv(ctx->n, 80), ctx->n <= 48 ? 1 : std::min(16, cdiv(ctx->n, 32)));
+  const int c0 = static_cast<int>(
+      std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(cdiv(2048, qb), by_n), ctx->n)));
   // short contours: lowered by up to half to the count whose blocks fill
   // whole waves of the resident slots (1024 nodes, 5000 particles: 63 chunks
   // made 2016 blocks for 1792 FP32 slots; 55 make 1760).  Long contours run
@@ -1001,20 +1036,33 @@ int launch_pair_tables(mpsl_ctx *ctx) {
   return MPSL_OK;
 }
 
+// nodes: with one chunk, on to the S2L coefficients.
 template <typename T>
-static int launch_m2s_t(mpsl_ctx *ctx, const void *beta, int nrhs) {
+static int launch_m2s_t(mpsl_ctx *ctx, const void *beta, int nrhs, bool nodes = false) {
   const int n = static_cast<int>(ctx->n);
-  const int chunks = chunks_m2s(ctx, nrhs, std::is_same<T, double>::value ? MPSL_FP64 : MPSL_FP32);
-  const int chunk_len = cdiv(n, chunks);
-  const dim3 grid(cdiv(ctx->ns, 16 * kM2sWaves), chunks, 2 * nrhs);
   const bool f64 = std::is_same<T, double>::value;
+  const int chunks = chunks_m2s(ctx, nrhs, f64 ? MPSL_FP64 : MPSL_FP32);
+  const int chunk_len = cdiv(n, chunks);
+  const dim3 grid = nodes ? dim3(cdiv(ctx->ns, 8 * kM2sWaves), 1, nrhs)
+                          : dim3(cdiv(ctx->ns, 16 * kM2sWaves), chunks, 2 * nrhs);
   const auto *E = static_cast<const cv_t<T> *>(f64 ? ctx->gt.E64.p : ctx->gt.E32.p);
   const auto *W = static_cast<const cv_t<T> *>(f64 ? ctx->ct.W64.p : ctx->ct.W32.p);
   const auto *b = static_cast<const cv_t<T> *>(beta);
   auto *part = static_cast<cv_t<T> *>(ctx->m2s_part.p);
+  const auto *R = static_cast<const double2 *>(ctx->ct.R.p), *cq = static_cast<const double2 *>(ctx->ct.cq.p),
+             *U = static_cast<const double2 *>(ctx->ct.U64.p);
+  auto *Up = static_cast<cv_t<T> *>(f64 ? ctx->Up64.p : ctx->Up32.p);
+  const dim3 blk(64 * kM2sWaves);
   switch (ctx->p) {
-#define X(PP) \
-  case PP: hipLaunchKernelGGL((k_m2s_mfma<T, PP>), grid, dim3(64 * kM2sWaves), 0, ctx->stream, E, b, W, part, n, ctx->ns, chunk_len, chunks); break;
+#define X(PP)                                                                                                       \
+  case PP:                                                                                                          \
+    if (nodes)                                                                                                      \
+      hipLaunchKernelGGL((k_m2s_mfma<T, PP, true>), grid, blk, 0, ctx->stream, E, b, W, part, n, ctx->ns,           \
+                         chunk_len, chunks, R, cq, U, Up);                                                          \
+    else                                                                                                            \
+      hipLaunchKernelGGL((k_m2s_mfma<T, PP, false>), grid, blk, 0, ctx->stream, E, b, W, part, n, ctx->ns,          \
+                         chunk_len, chunks, R, cq, U, Up);                                                          \
+    break;
     MPSL_P_CASES(X)
 #undef X
     default: return set_err(ctx, MPSL_EUNSUPPORTED, "expansion order outside 1..20");
@@ -1052,6 +1100,8 @@ int launch_m2s_coef(mpsl_ctx *ctx, int prec, const void *beta, int nrhs) {
     if (!rc) rc = launch_reflect(ctx, ctx->spec.p, nullptr, ctx->sigma.p, nrhs);
     return rc ? rc : launch_s2l_coef(ctx, ctx->sigma.p, nrhs);
   }
+  if (chunks_m2s(ctx, nrhs, prec) == 1)
+    return prec == MPSL_FP64 ? launch_m2s_t<double>(ctx, beta, nrhs, true) : launch_m2s_t<float>(ctx, beta, nrhs, true);
   if (prec == MPSL_FP64) {
     const int rc = launch_m2s_t<double>(ctx, beta, nrhs);
     return rc ? rc : launch_nodes_t<double>(ctx, nullptr, nrhs);
