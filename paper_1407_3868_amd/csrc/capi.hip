@@ -485,13 +485,12 @@ int matvec(mpsl_ctx *ctx, int prec, const void *x, void *y, int nrhs) {
   int rc = build_tables(ctx);
   if (rc) return rc;
   if (nrhs < 1) return set_err(ctx, MPSL_EINVAL, "nrhs must be >= 1");
-  // the right-hand-side dimension already multiplies the grid: fewer chunks
   // (the FMM writes its own partials: near-field chunks and far field)
   const bool fmm = ctx->fmm.active;
   // many FP32 right-hand sides: one Toeplitz GEMM per pair on the matrix cores
   const bool mrhs = !fmm && prec == MPSL_FP32 && nrhs >= kMrhsMin;
   const int ca = fmm ? fmm_slots(ctx)
-                     : (mrhs ? chunks_m2l_mrhs(ctx, nrhs) : std::max(1, chunks_m2l(ctx, prec) / nrhs));
+                     : (mrhs ? chunks_m2l_mrhs(ctx, nrhs) : chunks_m2l(ctx, prec, nrhs));
   const int cb = chunks_s2l(ctx, nrhs, prec);
   const int cc = chunks_m2s(ctx, nrhs, prec);
   const int P = 2 * ctx->p + 1;

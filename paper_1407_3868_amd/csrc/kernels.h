@@ -57,7 +57,8 @@ int launch_s2l_coef(mpsl_ctx *ctx, const void *sigma, int nrhs = 1);
 // Row b3: partial local expansions of the layer field into part[0 .. chunks).
 int launch_s2l(mpsl_ctx *ctx, int prec, void *part, int chunks, int nrhs = 1, int64_t pstride = 0);
 // Sum of partial buffers: alpha = sum_{c < chunks} part[c] (alpha may be part).
-int launch_sum_parts(mpsl_ctx *ctx, int prec, const void *part, int chunks, void *alpha);
+int launch_sum_parts(mpsl_ctx *ctx, int prec, const void *part, int chunks, void *alpha, int nrhs = 1,
+                     int64_t stride = 0);
 // Row a2 (MFMA): y = x - S_rot alpha  (x may be null: y = S_rot alpha); alpha
 // of right-hand side r is the sum of `slots` buffers of n P entries at
 // alpha + r * astride.
@@ -112,7 +113,7 @@ int launch_field(mpsl_ctx *ctx, const FieldShape &s, const std::vector<double> &
                  void *scratch);
 
 // Source chunks of the M2L grid for precision prec (tuned, set, or automatic).
-int chunks_m2l(const mpsl_ctx *ctx, int prec);
+int chunks_m2l(const mpsl_ctx *ctx, int prec, int nrhs = 1);
 // Sources per chunk of the matrix-core M2L for a grid of `chunks` chunks
 // (whole groups of four sources).
 int m2l_mfma_chunk_len(int n, int chunks);

@@ -235,10 +235,13 @@ __device__ __forceinline__ cx<T> sum_slots(const cv_t<T> *part, int slots, int64
   return s;
 }
 
-// out[i] = sum_c part[c len + i] (out may be the first slot)
+// out[i] = sum_c part[c len + i] (out may be the first slot), for right-hand side
+// blockIdx.y with both buffers `stride` entries further on
 template <typename T>
 __global__ __launch_bounds__(256) void k_sum_parts(const cv_t<T> *part, int slots, int64_t len,
-                                                   cv_t<T> *out) {
+                                                   cv_t<T> *out, int64_t stride) {
+  part += blockIdx.y * stride;
+  out += blockIdx.y * stride;
   const int64_t t = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
   const int64_t i = t / kSumLanes;
   if (i >= len) return;
@@ -1163,15 +1166,15 @@ int launch_s2l(mpsl_ctx *ctx, int prec, void *part, int chunks, int nrhs, int64_
                            : launch_s2l_t<float>(ctx, part, chunks, nrhs, pstride);
 }
 
-int launch_sum_parts(mpsl_ctx *ctx, int prec, const void *part, int chunks, void *alpha) {
+int launch_sum_parts(mpsl_ctx *ctx, int prec, const void *part, int chunks, void *alpha, int nrhs, int64_t stride) {
   const int64_t len = ctx->n * static_cast<int64_t>(2 * ctx->p + 1);
-  const dim3 grid(cdiv(len * kSumLanes, 256));
+  const dim3 grid(cdiv(len * kSumLanes, 256), nrhs);
   if (prec == MPSL_FP64)
     hipLaunchKernelGGL(k_sum_parts<double>, grid, dim3(256), 0, ctx->stream, static_cast<const double2 *>(part), chunks,
-                       len, static_cast<double2 *>(alpha));
+                       len, static_cast<double2 *>(alpha), stride);
   else
     hipLaunchKernelGGL(k_sum_parts<float>, grid, dim3(256), 0, ctx->stream, static_cast<const float2 *>(part), chunks,
-                       len, static_cast<float2 *>(alpha));
+                       len, static_cast<float2 *>(alpha), stride);
   LAUNCH_CHECK(ctx);
   return MPSL_OK;
 }
@@ -1216,10 +1219,7 @@ int launch_sapply(mpsl_ctx *ctx, int prec, const void *x, void *alpha, int slots
   const size_t esz = prec == MPSL_FP64 ? sizeof(double2) : sizeof(float2);
   const size_t tile = 16 * (2 * ctx->p + 1) * esz * slots;
   if (slots > 1 && tile > kSapplySumBytes && static_cast<int64_t>(cdiv(ctx->n, 16)) * nrhs < ctx->n_cu) {
-    for (int r = 0; r < nrhs; ++r) {
-      char *a = static_cast<char *>(alpha) + r * astride * esz;
-      if (const int rc = launch_sum_parts(ctx, prec, a, slots, a)) return rc;
-    }
+    if (const int rc = launch_sum_parts(ctx, prec, alpha, slots, alpha, nrhs, astride)) return rc;
     slots = 1;
   }
   return prec == MPSL_FP64 ? launch_sapply_t<double>(ctx, x, alpha, slots, y, nrhs, astride)

@@ -1065,16 +1065,22 @@ static int m2l_variant(const mpsl_ctx *ctx, int prec) {
 // sixth more while a unit has one block only, plus the writing and summing of
 // the chunks' partials at HBM rate; the best of up to 128 counts.  (5000
 // particles FP32: 42 chunks and 1.49 ms, as 125, which left 3x the partials to
-// sum; 1000 particles FP64, p = 12: 63 chunks, 83 us.)
-static int m2l_mfma_chunks(const mpsl_ctx *ctx, int prec, int nt) {
+// sum; 1000 particles FP64, p = 12: 63 chunks, 83 us.)  Right-hand sides
+// multiply the blocks and the partials; all together have no more partial slots
+// than one right-hand side would to fill the chip with waves.  (1400 particles,
+// 15 right-hand sides, FP64, p = 16: dividing the count of one left a single
+// chunk, 330 blocks on 256 units, 6.40 ms; the rule's count 3.98.)
+static int m2l_mfma_chunks(const mpsl_ctx *ctx, int prec, int nt, int nrhs) {
   const int n = static_cast<int>(ctx->n), P = 2 * ctx->p + 1;
-  const int bpc = cdiv(n, 64 * nt), units = std::max(1, ctx->n_cu);
+  const int bpc = cdiv(n, 64 * nt) * nrhs, units = std::max(1, ctx->n_cu);
+  const int fill = std::max(1, std::min(cdiv(n, 4), 10000 / cdiv(n, 64)) / nrhs);
+  const int cmax = nrhs > 1 ? std::min(128, fill) : std::min(128, cdiv(n, 4));
   const bool f64 = prec == MPSL_FP64;
   const double t_group = (f64 ? 525.0 : 260.0) * P * nt / 2.3e3;                        // us
-  const double t_slot = 2.0 * n * P * (f64 ? sizeof(double2) : sizeof(float2)) / 4.5e6;  // us
+  const double t_slot = 2.0 * nrhs * n * P * (f64 ? sizeof(double2) : sizeof(float2)) / 4.5e6;  // us
   double best = 1e300;
   int bc = 1;
-  for (int c = 1; c <= std::min(128, cdiv(n, 4)); ++c) {
+  for (int c = 1; c <= cmax; ++c) {
     const int groups = m2l_mfma_chunk_len(n, c) / 4;
     if (cdiv(n, 4 * groups) != c) continue;  // trailing chunks empty
     const int rounds = cdiv(static_cast<int64_t>(bpc) * c, units);
@@ -1087,14 +1093,16 @@ static int m2l_mfma_chunks(const mpsl_ctx *ctx, int prec, int nt) {
   return bc;
 }
 
-int chunks_m2l(const mpsl_ctx *ctx, int prec) {
+int chunks_m2l(const mpsl_ctx *ctx, int prec, int nrhs) {
+  // the right-hand sides already multiply the grid: a count set for one is shared
   const int tuned = ctx->tune[prec == MPSL_FP64 ? 0 : 1].chunks;
-  if (tuned > 0) return static_cast<int>(std::min<int64_t>(tuned, ctx->n));
-  if (ctx->m2l_chunks > 0) return static_cast<int>(std::min<int64_t>(ctx->m2l_chunks, ctx->n));
+  if (tuned > 0) return std::max(1, static_cast<int>(std::min<int64_t>(tuned, ctx->n)) / nrhs);
+  if (ctx->m2l_chunks > 0) return std::max(1, static_cast<int>(std::min<int64_t>(ctx->m2l_chunks, ctx->n)) / nrhs);
   const int v = m2l_variant(ctx, prec);
-  if (v >= kM2LMfma) return m2l_mfma_chunks(ctx, prec, v == kM2LMfmaWide ? 2 : 1);
+  if (v >= kM2LMfma) return m2l_mfma_chunks(ctx, prec, v == kM2LMfmaWide ? 2 : 1, nrhs);
   // one lane per target: about 2560 blocks of 128 lanes
-  return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(cdiv(2560, cdiv(ctx->n, kThreads)), ctx->n)));
+  const int64_t c = std::max<int64_t>(1, std::min<int64_t>(cdiv(2560, cdiv(ctx->n, kThreads)), ctx->n));
+  return std::max(1, static_cast<int>(c) / nrhs);
 }
 
 // Sources per chunk of the matrix-core M2L: each MFMA step takes a group of
