@@ -382,11 +382,18 @@ __global__ __launch_bounds__(64 * kM2lWaves, 2) void k_m2l_f64(const double2 *__
 // Row a1 in FP32 on the bf16 matrix cores, one right-hand side: the same
 // product of shifted source coefficients and pair Hankel values as above,
 //   alpha_l[s'] = sum_{m, q} A_m[s'][q] h_q(m -> l),  A_m[s'][q] = beta_m[s' + q]
-// (slots s' = n' + p), with every FP32 operand split exactly into three bf16
-// parts, x = x1 + x2 + x3 (rounding to nearest leaves 9 more bits to each next
-// part, so the 24 bits of x fit), and the six products whose parts' weights
-// reach 2^-18 (11, 12, 21, 22, 13, 31) accumulated in FP32; the three left out
-// are below 2^-26 of the product, less than the rounding of one FP32 multiply.
+// (slots s' = n' + p), with every FP32 operand split into three bf16 parts,
+// x = x1 + x2 + x3 (rounding to nearest leaves 9 more bits to each next part, so
+// the 24 bits of x fit), and the six products whose parts' weights reach 2^-18
+// (11, 12, 21, 22, 13, 31) accumulated in FP32; the three left out are below
+// 2^-26 of the product, less than the rounding of one FP32 multiply.  The split
+// is exact where the last bit of x stays above the smallest bf16 subnormal,
+// 2^-133, and x1 rounds to a finite number, below 3.39e38.  Coefficients reach
+// below that range (high orders of small particles, vectors of small norm), so
+// those of a batch are scaled by 2^24, which brings every FP32 number into it,
+// and the pairs' Hankel values by 2^-24 (they are far above it, and their
+// recurrence is linear): the products stay as they were.  A batch with a
+// coefficient of 2^100 or more takes 2^-4 and 2^4 (BfScale).
 // Complex products take four real ones (no operand sums), each in its own
 // accumulators.  The matrix cores' bf16 sums do not round to nearest, so a
 // long chain of them drifts (chunks of 316 sources: 5.9e-7 relative error of a
@@ -423,8 +430,20 @@ typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
+// The power of two by which coefficients are multiplied before their split, and
+// its inverse for the Hankel values they meet.
+struct BfScale {
+  float up, down;
+};
+__device__ __forceinline__ bool bf_big(float2 b) {  // also true for a NaN
+  return !(fabsf(b.x) < 0x1p100f && fabsf(b.y) < 0x1p100f);
+}
+__device__ __forceinline__ BfScale bf_scale(bool big) {
+  return big ? BfScale{0x1p-4f, 0x1p4f} : BfScale{0x1p24f, 0x1p-24f};
+}
+
 // Eight FP32 values as three bf16 parts (round to nearest; the remainders are
-// exact).
+// exact within the range above).
 struct Split8 {
   bf8 v[3];
 };
@@ -462,6 +481,7 @@ __global__ __launch_bounds__(64 * kM2lBfWaves, NT == 1 ? 3 : 2) void k_m2l_bf(co
   __shared__ __align__(16) __bf16 sa[SB * kBfSrc];
   __shared__ float2 sv[VROW ? SB : 1][VROW ? P : 1];
   __shared__ v4 run[kM2lBfWaves][NT * NB * 2][64];  // sums over the batches, each lane its own entries
+  __shared__ int sbig[kM2lBfWaves];
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int r = lane & 15, g = lane >> 4;
   const int c = blockIdx.y;
@@ -505,22 +525,38 @@ __global__ __launch_bounds__(64 * kM2lBfWaves, NT == 1 ? 3 : 2) void k_m2l_bf(co
 
   for (int mb = m0; mb < m1; mb += SB) {
     const int sb = min(SB, m1 - mb);
+    constexpr int NL = (SB * P + 64 * kM2lBfWaves - 1) / (64 * kM2lBfWaves);
+    float2 bl[NL];
+    bool big = false;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const int e = threadIdx.x + 64 * kM2lBfWaves * i;
+      bl[i] = e < sb * P ? beta[static_cast<int64_t>(mb) * P + e] : make_float2(0.f, 0.f);
+      big |= bf_big(bl[i]);
+    }
+    big = __any(big);
+    if (lane == 0) sbig[w] = big;
     __syncthreads();  // previous batch consumed (and the zero fill done)
-    for (int e = threadIdx.x; e < SB * P; e += 64 * kM2lBfWaves) {
-      const int s = e / P, v = e - s * P;
-      const float2 b = s < sb ? beta[static_cast<int64_t>(mb + s) * P + v] : make_float2(0.f, 0.f);
-      if (VROW) sv[s][v] = b;
-      float x[2] = {b.x, b.y};
+    static_assert(kM2lBfWaves == 4, "flags of four waves");
+    const BfScale sc = bf_scale((sbig[0] | sbig[1] | sbig[2] | sbig[3]) != 0);
 #pragma unroll
-      for (int k = 0; k < 3; ++k)
+    for (int i = 0; i < NL; ++i) {
+      const int e = threadIdx.x + 64 * kM2lBfWaves * i;
+      if (e < SB * P) {
+        const int s = e / P, v = e - s * P;
+        float x[2] = {bl[i].x * sc.up, bl[i].y * sc.up};
+        if (VROW) sv[s][v] = make_float2(x[0], x[1]);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-          const __bf16 h = static_cast<__bf16>(x[i]);
-          x[i] -= static_cast<float>(h);
-          __bf16 *o = sa + s * kBfSrc + (2 * k + i) * 4 * kBfRow + v + 15;  // copy u holds slot v at v + 15 - u
+        for (int k = 0; k < 3; ++k)
 #pragma unroll
-          for (int u = 0; u < 4; ++u) o[u * kBfRow - u] = h;
-        }
+          for (int j = 0; j < 2; ++j) {
+            const __bf16 h = static_cast<__bf16>(x[j]);
+            x[j] -= static_cast<float>(h);
+            __bf16 *o = sa + s * kBfSrc + (2 * k + j) * 4 * kBfRow + v + 15;  // copy u holds slot v at v + 15 - u
+#pragma unroll
+            for (int u = 0; u < 4; ++u) o[u * kBfRow - u] = h;
+          }
+      }
     }
     __syncthreads();
     // a wave whose targets all lie past the last particle (the grid's tail)
@@ -542,7 +578,7 @@ __global__ __launch_bounds__(64 * kM2lBfWaves, NT == 1 ? 3 : 2) void k_m2l_bf(co
       };
 #pragma unroll
       for (int tt = 0; tt < NT; ++tt) {
-        cx<float> hp = ld<float>(pc[tt][0]), hc = ld<float>(pc[tt][1]);
+        cx<float> hp = sc.down * ld<float>(pc[tt][0]), hc = sc.down * ld<float>(pc[tt][1]);
         const cx<float> t = ld<float>(pc[tt][2]);
         cx<float> tq = t;
         const float tz = pc[tt][3].x;
