@@ -852,32 +852,36 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs(const float2 *__re
 // of 8 sources at a time into FP32 rows; per source each lane splits one h_q
 // and stores its parts in four copies, shifted by 0 .. 3 entries, from which
 // the A operand (eight consecutive q, ending at a lane's row) is read with
-// aligned 8-byte reads.  B, split once per call (k_rhs_split), is staged per
-// source for all waves of the block, double-buffered.  The matrix cores' bf16
-// sums do not round to nearest, so they are added to running FP32 sums after
-// every batch of 8 sources and start again from zero.
+// aligned 8-byte reads.  B, beta transposed as for the FP32 form, is split while
+// it is staged, four source orders of one right-hand side per thread, once per
+// source for all waves of the block, double-buffered, between the MFMAs.  (Split
+// beforehand, the parts were 1.5 to 2.4 times the size of the transposed beta,
+// which a context's memory budget may not have; the matvec of the case below
+// took 8.30 ms with them, 8.61 ms without.)  The matrix cores' bf16 sums do not
+// round to nearest, so they are added to running FP32 sums after every batch of
+// 8 sources and start again from zero.
 //
 // Bound by the matrix cores: 192 MFMAs of 16 cycles per pair and 64 right-hand
-// sides, where the FP32 form below needs 3 MT KP NT / 4 = 168 of 32.4 (p = 12).
+// sides, where the FP32 form above needs 3 MT KP NT / 4 = 168 of 32.4 (p = 12).
 // 64 right-hand sides, 2000 particles, p = 12: 10.9 -> 7.9 ms (MFMAs 65 % of the
 // cycles), the batch's error against 64 bits 1.3e-6 -> 1.0e-6.
 template <int p>
 __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *__restrict__ pairs,
-                                                                 const __bf16 *__restrict__ bt,
+                                                                 const float2 *__restrict__ bt,
                                                                  float2 *__restrict__ part, int n, int chunk_len,
                                                                  int nrhs, int r_pad, int64_t pstride) {
   constexpr int P = 2 * p + 1;
   static_assert(P > 16 && P <= 32, "two row blocks, one K step");
   constexpr int MT = 2, NT = 4;
   constexpr int OFF = 31;                    // row entry of h_q is q + OFF
+  constexpr int KP = (P + 3) / 4 * 4;        // rows of bt per source
   constexpr int PR = 6 * 64 * 32;            // B entries of one source
-  constexpr int BL = PR / 8 / (64 * kMrhsWaves);  // 16-byte loads per thread
-  static_assert(BL * 8 * 64 * kMrhsWaves == PR, "whole loads");
+  static_assert(4 * kMrhsWaves == 32, "four source orders per wave");
   typedef float v4 __attribute__((ext_vector_type(4)));
   __shared__ float2 H[kMrhsWaves][kMrhsBatch][65];
   __shared__ __align__(16) __bf16 Hs[2][kMrhsWaves][6][4][kBfRow];
   __shared__ __align__(16) __bf16 Bs[2][PR];  // [part, re / im][nu / 8][r][nu % 8]: a read's 16 columns are contiguous
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int l = blockIdx.x * kMrhsWaves + w;
   const int c = blockIdx.y;
   const int r0 = blockIdx.z * 64;
@@ -889,18 +893,31 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *_
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) acc[mt][ct][0] = acc[mt][ct][1] = v4{0, 0, 0, 0};
-  u32x4 pre[BL];
+  float2 pre[4];  // this thread's source orders 4 w .. 4 w + 3 of right-hand side r0 + lane
   auto load_b = [&](int m) {
     const int64_t mc = min(m, n - 1);  // past the chunk: loaded, never used
 #pragma unroll
-    for (int i = 0; i < BL; ++i) {
-      const int e = threadIdx.x + 64 * kMrhsWaves * i;  // 16-byte piece: (array, nu / 8) e / 64, right-hand side e % 64
-      pre[i] = *reinterpret_cast<const u32x4 *>(bt + ((mc * 24 + e / 64) * r_pad + r0 + e % 64) * 8);
-    }
+    for (int i = 0; i < 4; ++i)
+      pre[i] = 4 * w + i < P ? bt[(mc * KP + 4 * w + i) * r_pad + r0 + lane] : make_float2(0.f, 0.f);
   };
-  auto store_b = [&](int buf) {
+  auto store_b = [&](int buf, int j) {  // real (j = 0) or imaginary parts
+    {
+      f32x2 x[2];
 #pragma unroll
-    for (int i = 0; i < BL; ++i) *reinterpret_cast<u32x4 *>(&Bs[buf][8 * (threadIdx.x + 64 * kMrhsWaves * i)]) = pre[i];
+      for (int i = 0; i < 2; ++i)
+        x[i] = j ? f32x2{pre[2 * i].y, pre[2 * i + 1].y} : f32x2{pre[2 * i].x, pre[2 * i + 1].x};
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        bf2 h[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          h[i] = __builtin_convertvector(x[i], bf2);
+          if (k < 2) x[i] = x[i] - __builtin_convertvector(h[i], f32x2);
+        }
+        *reinterpret_cast<bf4 *>(&Bs[buf][(((2 * k + j) * 4 + w / 2) * 64 + lane) * 8 + w % 2 * 4]) =
+            __builtin_shufflevector(h[0], h[1], 0, 1, 2, 3);
+      }
+    }
   };
   // sums of the sources since the last flush into the running ones
   v4 run[MT][NT][2];
@@ -966,7 +983,10 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *_
         }
     };
     split_h(0, it & 1);
-    if (it == 0) store_b(0);
+    if (it == 0) {
+      store_b(0, 0);
+      store_b(0, 1);
+    }
     for (int s = 0; s < sb; ++s, ++it) {
       const int buf = it & 1;
       __syncthreads();       // B and the parts of h of this source stored
@@ -1009,8 +1029,8 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *_
             acc[mt][ct][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ai[mt][ka[x]], br[kb[x]], acc[mt][ct][1], 0, 0, 0);
           }
         }
+        if (ct == 1 || ct == 2) store_b(buf ^ 1, ct - 1);  // last read two sources ago
       }
-      store_b(buf ^ 1);  // last read two sources ago
     }
     flush();
   }
@@ -1027,25 +1047,6 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *_
           part[r * pstride + c * len + static_cast<int64_t>(l) * P + row] =
               make_float2(run[mt][ct][0][j], run[mt][ct][1][j]);
       }
-}
-
-// beta [r][m][P] -> bt [m][part, re / im][nu / 8][r_pad][nu % 8]: three bf16
-// parts of every coefficient, zeros for nu >= P and r >= nrhs.
-__global__ void k_rhs_split(const float2 *__restrict__ x, __bf16 *__restrict__ bt, int n, int P, int nrhs, int r_pad) {
-  const int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  if (i >= static_cast<int64_t>(n) * r_pad * 32) return;
-  const int k = static_cast<int>(i % 32), r = static_cast<int>(i / 32 % r_pad);
-  const int64_t m = i / 32 / r_pad;
-  const float2 v = (r < nrhs && k < P) ? x[(r * static_cast<int64_t>(n) + m) * P + k] : make_float2(0.f, 0.f);
-  float b[2] = {v.x, v.y};
-#pragma unroll
-  for (int u = 0; u < 3; ++u)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const __bf16 h = static_cast<__bf16>(b[j]);
-      b[j] -= static_cast<float>(h);
-      bt[(((m * 6 + 2 * u + j) * 4 + k / 8) * r_pad + r) * 8 + k % 8] = h;
-    }
 }
 
 // beta [r][m][P] -> bt [m][KP][r_pad] (r fastest; zero rows k >= P and
@@ -1240,37 +1241,6 @@ int launch_m2l_mrhs(mpsl_ctx *ctx, const void *beta, void *part, int chunks, int
   const int KP = (P + 3) / 4 * 4;
   const int64_t rows = static_cast<int64_t>(n) * KP;
   const int r_pad = 64 * cdiv(nrhs, 64);
-  // bf16 parts where one K step holds all orders (p = 8 .. 15; at p = 16 the
-  // 33 orders would pad to 64), unless the context's memory budget has no room
-  // for them: then, and else, the FP32 form
-  const size_t parts = static_cast<size_t>(n) * r_pad * 6 * 32 * sizeof(__bf16);
-  bool split = P > 16 && P <= 32 && parts < ctx->bt_refused;
-  if (split && parts > ctx->bt.bytes) {
-    split = ctx->hbm_budget == 0 || ctx->hbm_used - ctx->bt.bytes + parts <= ctx->hbm_budget;
-    if (split && dev_alloc(ctx, ctx->bt, parts) != MPSL_OK) {
-      split = false;
-      ctx->bt_refused = parts;  // not tried again: a later call may be under capture
-    }
-  }
-  if (split) {
-    auto *bt = static_cast<__bf16 *>(ctx->bt.p);
-    hipLaunchKernelGGL(k_rhs_split, dim3(cdiv(static_cast<int64_t>(n) * r_pad * 32, 256)), dim3(256), 0, ctx->stream,
-                       static_cast<const float2 *>(beta), bt, n, P, nrhs, r_pad);
-    LAUNCH_CHECK(ctx);
-    const dim3 grid(cdiv(n, kMrhsWaves), chunks, r_pad / 64);
-    switch (ctx->p) {
-#define X(PP)                                                                                                  \
-  case PP:                                                                                                     \
-    hipLaunchKernelGGL(k_m2l_mrhs_bf<PP>, grid, dim3(64 * kMrhsWaves), 0, ctx->stream,                         \
-                       static_cast<const float2 *>(ctx->gt.pair32.p), bt, static_cast<float2 *>(part), n,      \
-                       cdiv(n, chunks), nrhs, r_pad, pstride);                                                 \
-    break;
-      X(8) X(9) X(10) X(11) X(12) X(13) X(14) X(15)
-#undef X
-    }
-    LAUNCH_CHECK(ctx);
-    return MPSL_OK;
-  }
   int rc = dev_alloc(ctx, ctx->bt, static_cast<size_t>(rows) * r_pad * sizeof(float2));
   if (rc) return rc;
   hipLaunchKernelGGL(k_rhs_transpose, dim3(cdiv(rows * r_pad, 256)), dim3(256), 0, ctx->stream,
@@ -1281,9 +1251,18 @@ int launch_m2l_mrhs(mpsl_ctx *ctx, const void *beta, void *part, int chunks, int
   const auto *pairs = static_cast<const float2 *>(ctx->gt.pair32.p);
   const auto *bt = static_cast<const float2 *>(ctx->bt.p);
   auto *pp = static_cast<float2 *>(part);
+  // bf16 parts where one K step holds all orders (p = 8 .. 15; at p = 16 the
+  // 33 orders would pad to 64), else the FP32 form
   switch (ctx->p) {
-#define X(PP) \
-  case PP: hipLaunchKernelGGL((k_m2l_mrhs<PP>), grid, dim3(64 * kMrhsWaves), 0, ctx->stream, pairs, bt, pp, n, chunk_len, nrhs, r_pad, pstride); break;
+#define X(PP)                                                                                                      \
+  case PP:                                                                                                         \
+    if constexpr (PP >= 8 && PP <= 15)                                                                             \
+      hipLaunchKernelGGL((k_m2l_mrhs_bf<PP>), grid, dim3(64 * kMrhsWaves), 0, ctx->stream, pairs, bt, pp, n,       \
+                         chunk_len, nrhs, r_pad, pstride);                                                         \
+    else                                                                                                           \
+      hipLaunchKernelGGL((k_m2l_mrhs<PP>), grid, dim3(64 * kMrhsWaves), 0, ctx->stream, pairs, bt, pp, n,          \
+                         chunk_len, nrhs, r_pad, pstride);                                                         \
+    break;
     MPSL_P_CASES(X)
 #undef X
     default: return set_err(ctx, MPSL_EUNSUPPORTED, "expansion order outside 1..20");

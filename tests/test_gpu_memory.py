@@ -1,0 +1,58 @@
+"""Device memory that calls take from a context, and calls whose allocation
+was refused once: a later call is the one a fresh context makes, bit by bit.
+"""
+import numpy as np
+import pytest
+
+import paper_1407_3868_amd as mp
+from gpu_common import coeff_vector, gpu_context, make_workload
+
+pytestmark = pytest.mark.gpu
+
+
+def _rhs(wl, nrhs, dtype):
+    import torch
+    x = np.stack([coeff_vector(wl, 90 + r) for r in range(nrhs)]).astype(dtype)
+    return torch.from_numpy(x).cuda()
+
+
+def _batch(ctx, prec, x):
+    import torch
+    y = torch.full_like(x, float("nan"))
+    ctx.set_stream(torch.cuda.current_stream().cuda_stream)
+    ctx.apply_batch_dev(prec, x.shape[0], x, y)
+    torch.cuda.synchronize()
+    return y.cpu().numpy()
+
+
+@pytest.mark.parametrize("p", [7, 8, 12, 15, 16])
+def test_many_rhs_memory(p):
+    # beyond what the same call in FP64 holds: the transposed coefficients of
+    # whole groups of 64 right-hand sides, rows in fours
+    wl = make_workload("s70p8")
+    wl.p = p
+    ctx = gpu_context(wl)
+    x = _rhs(wl, 20, np.complex128)
+    _batch(ctx, 0, x)
+    before = ctx.memory()[0]
+    import torch
+    _batch(ctx, 1, x.to(torch.complex64))
+    assert ctx.memory()[0] - before <= wl.n * ((wl.P + 3) // 4 * 4) * 64 * 8
+
+
+def test_refused_call_leaves_no_trace():
+    import torch
+    wl = make_workload("s70p8")
+    wl.p = 12
+    x64 = _rhs(wl, 20, np.complex128)
+    x = x64.to(torch.complex64)
+    ref = _batch(gpu_context(wl), 1, x)
+    ctx = gpu_context(wl)
+    y64 = torch.empty_like(x64)
+    ctx.set_stream(torch.cuda.current_stream().cuda_stream)
+    batch = mp.Batch([(ctx, 0, 20, x64, y64)])  # holds the context's buffers
+    with pytest.raises(mp.MpslError) as e:
+        _batch(ctx, 1, x)
+    assert e.value.status == -4
+    batch.close()
+    assert np.array_equal(_batch(ctx, 1, x), ref)
