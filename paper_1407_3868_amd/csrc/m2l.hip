@@ -840,8 +840,8 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs(const float2 *__re
 
 // ---------------------------------------------------------------------------
 // Row a1 for many right-hand sides on the bf16 matrix cores (FP32 operands in
-// three exact bf16 parts and the six largest products of parts, as in
-// k_m2l_bf), for 16 < 2p + 1 <= 32: per pair one 16x16x32 MFMA step covers all
+// three bf16 parts and the six largest products of parts, scaled as in k_m2l_bf
+// by one power of two per source and 64 right-hand sides), for 16 < 2p + 1 <= 32: per pair one 16x16x32 MFMA step covers all
 // source orders.  alpha_l[n'][r] += sum_nu T[n'][nu] beta_m[nu][r] with
 // T[n'][nu] = h_{nu - n'} (M = n' in two 16-row blocks, K = nu, N = r in four
 // 16-column tiles); complex products in four real ones, re and im in one
@@ -857,7 +857,7 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs(const float2 *__re
 // source for all waves of the block, double-buffered, between the MFMAs.  (Split
 // beforehand, the parts were 1.5 to 2.4 times the size of the transposed beta,
 // which a context's memory budget may not have; the matvec of the case below
-// took 8.30 ms with them, 8.61 ms without.)  The matrix cores' bf16 sums do not
+// took 8.31 ms with them, 8.70 ms without.)  The matrix cores' bf16 sums do not
 // round to nearest, so they are added to running FP32 sums after every batch of
 // 8 sources and start again from zero.
 //
@@ -894,18 +894,20 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *_
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) acc[mt][ct][0] = acc[mt][ct][1] = v4{0, 0, 0, 0};
   float2 pre[4];  // this thread's source orders 4 w .. 4 w + 3 of right-hand side r0 + lane
+  float pre_up;   // and the source's power of two
   auto load_b = [&](int m) {
     const int64_t mc = min(m, n - 1);  // past the chunk: loaded, never used
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       pre[i] = 4 * w + i < P ? bt[(mc * KP + 4 * w + i) * r_pad + r0 + lane] : make_float2(0.f, 0.f);
+    pre_up = bt[(mc * KP + KP - 1) * r_pad + r0 + lane].x;
   };
   auto store_b = [&](int buf, int j) {  // real (j = 0) or imaginary parts
     {
       f32x2 x[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i)
-        x[i] = j ? f32x2{pre[2 * i].y, pre[2 * i + 1].y} : f32x2{pre[2 * i].x, pre[2 * i + 1].x};
+        x[i] = pre_up * (j ? f32x2{pre[2 * i].y, pre[2 * i + 1].y} : f32x2{pre[2 * i].x, pre[2 * i + 1].x});
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         bf2 h[2];
@@ -948,7 +950,9 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *_
       float2 *h = H[w][lane] + OFF;
       if (l < n && m != l) {
         const float2 *pe = pairs + 4 * (static_cast<int64_t>(m) * n + l);
-        cx<float> hp = ld<float>(pe[0]), hc = ld<float>(pe[1]);
+        // times the inverse of the source's power of two, 2^-24 or 2^4
+        const float down = 1.0f / bt[(static_cast<int64_t>(m) * KP + KP - 1) * r_pad + r0].x;
+        cx<float> hp = down * ld<float>(pe[0]), hc = down * ld<float>(pe[1]);
         const cx<float> t = ld<float>(pe[2]);
         const float tz = pe[3].x;
         h[0] = st(hp);
@@ -1050,17 +1054,32 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *_
 }
 
 // beta [r][m][P] -> bt [m][KP][r_pad] (r fastest; zero rows k >= P and
-// zero columns r >= nrhs), FP32.
-__global__ void k_rhs_transpose(const float2 *__restrict__ x, float2 *__restrict__ bt, int n, int P, int KP,
-                                int nrhs, int r_pad) {
-  const int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
-  const int64_t rows = static_cast<int64_t>(n) * KP;
-  if (i >= rows * r_pad) return;
-  const int64_t row = i / r_pad;
-  const int r = static_cast<int>(i % r_pad);
-  const int m = static_cast<int>(row / KP), k = static_cast<int>(row % KP);
-  bt[i] = (r < nrhs && k < P) ? x[r * static_cast<int64_t>(n) * P + static_cast<int64_t>(m) * P + k]
-                              : make_float2(0.f, 0.f);
+// zero columns r >= nrhs), FP32: one block per source and 64 right-hand sides,
+// through LDS.  With scale (the bf16 form, which has its own zeros) the last
+// row, KP - 1 >= P, holds the power of two for the split of this block's
+// coefficients.
+template <int P>
+__global__ __launch_bounds__(256) void k_rhs_transpose(const float2 *__restrict__ x, float2 *__restrict__ bt, int n,
+                                                       int nrhs, int r_pad, bool scale) {
+  constexpr int KP = (P + 3) / 4 * 4;
+  static_assert(KP > P, "a spare row");
+  __shared__ float2 t[P][65];
+  const int64_t m = blockIdx.x;
+  const int r0 = blockIdx.y * 64;
+  bool big = false;
+  for (int e = threadIdx.x; e < 64 * P; e += 256) {
+    const int r = e / P, k = e - r * P;
+    const float2 v = r0 + r < nrhs ? x[((r0 + r) * static_cast<int64_t>(n) + m) * P + k] : make_float2(0.f, 0.f);
+    t[k][r] = v;
+    big |= bf_big(v);
+  }
+  big = __syncthreads_or(big);
+  const float up = scale ? bf_scale(big).up : 0.f;
+  float2 *o = bt + m * KP * r_pad + r0;
+  for (int e = threadIdx.x; e < 64 * KP; e += 256) {
+    const int k = e / 64, r = e % 64;
+    o[static_cast<int64_t>(k) * r_pad + r] = k < P ? t[k][r] : make_float2(k == KP - 1 ? up : 0.f, 0.f);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1235,6 +1254,10 @@ int chunks_m2l_mrhs(const mpsl_ctx *ctx, int nrhs) {
   return hi;
 }
 
+// bf16 parts where one K step holds all orders (p = 8 .. 15; at p = 16 the 33
+// orders would pad to 64), else the FP32 form.
+static constexpr bool mrhs_bf(int p) { return p >= 8 && p <= 15; }
+
 int launch_m2l_mrhs(mpsl_ctx *ctx, const void *beta, void *part, int chunks, int nrhs, int64_t pstride) {
   const int n = static_cast<int>(ctx->n);
   const int P = 2 * ctx->p + 1;
@@ -1243,20 +1266,27 @@ int launch_m2l_mrhs(mpsl_ctx *ctx, const void *beta, void *part, int chunks, int
   const int r_pad = 64 * cdiv(nrhs, 64);
   int rc = dev_alloc(ctx, ctx->bt, static_cast<size_t>(rows) * r_pad * sizeof(float2));
   if (rc) return rc;
-  hipLaunchKernelGGL(k_rhs_transpose, dim3(cdiv(rows * r_pad, 256)), dim3(256), 0, ctx->stream,
-                     static_cast<const float2 *>(beta), static_cast<float2 *>(ctx->bt.p), n, P, KP, nrhs, r_pad);
+  switch (ctx->p) {
+#define X(PP)                                                                                                \
+  case PP:                                                                                                   \
+    hipLaunchKernelGGL(k_rhs_transpose<2 * PP + 1>, dim3(n, r_pad / 64), dim3(256), 0, ctx->stream,          \
+                       static_cast<const float2 *>(beta), static_cast<float2 *>(ctx->bt.p), n, nrhs, r_pad,  \
+                       mrhs_bf(PP));                                                                         \
+    break;
+    MPSL_P_CASES(X)
+#undef X
+    default: return set_err(ctx, MPSL_EUNSUPPORTED, "expansion order outside 1..20");
+  }
   LAUNCH_CHECK(ctx);
   const int chunk_len = cdiv(n, chunks);
   const dim3 grid(cdiv(n, kMrhsWaves), chunks, r_pad / 64);
   const auto *pairs = static_cast<const float2 *>(ctx->gt.pair32.p);
   const auto *bt = static_cast<const float2 *>(ctx->bt.p);
   auto *pp = static_cast<float2 *>(part);
-  // bf16 parts where one K step holds all orders (p = 8 .. 15; at p = 16 the
-  // 33 orders would pad to 64), else the FP32 form
   switch (ctx->p) {
 #define X(PP)                                                                                                      \
   case PP:                                                                                                         \
-    if constexpr (PP >= 8 && PP <= 15)                                                                             \
+    if constexpr (mrhs_bf(PP))                                                                                     \
       hipLaunchKernelGGL((k_m2l_mrhs_bf<PP>), grid, dim3(64 * kMrhsWaves), 0, ctx->stream, pairs, bt, pp, n,       \
                          chunk_len, nrhs, r_pad, pstride);                                                         \
     else                                                                                                           \

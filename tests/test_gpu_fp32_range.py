@@ -1,4 +1,4 @@
-"""FP32 M2L over the range of FP32: vectors scaled by powers of two against the
+"""FP32 M2L, for one and for many right-hand sides, over the range of FP32: vectors scaled by powers of two against the
 same vectors unscaled, and coefficients next to the largest FP32 number.
 
 Tolerances.  A scaling by 2^-k changes no rounding until products and sums
@@ -65,3 +65,25 @@ def test_largest_coefficient(p, variant):
     got = _apply(ctx, 1, x)
     assert np.isfinite(got[far]).all()
     assert np.linalg.norm((got[far] - ref[far]) / 1e38) <= 1e-6 * np.linalg.norm(ref[far] / 1e38)
+
+
+@pytest.mark.parametrize("p", [8, 12, 15])
+def test_small_coefficients_of_many_rhs(p):
+    # each right-hand side alone with its scale: y of several is linear in each;
+    # one vector next to the others' size in a group does not lose the others' bits
+    wl = _workload(p)
+    ctx = gpu_context(wl)
+    rng = np.random.default_rng(70 + p)
+    x = rng.uniform(1.0, 2.0, (16, wl.n, wl.P)) * np.exp(0.25j * np.pi * (1 + 2 * rng.integers(0, 4, (16, wl.n, wl.P))))
+    x = x.astype(np.complex64).astype(np.complex128)
+    ref = _apply(ctx, 16, x)
+    k = np.array([0, 60, 100, 104, 108, 110, 112, 114, 115, 116, 117, 118, 119, 120, 108, 30])
+    scale = 2.0 ** -k[:, None, None]
+    got = _apply(ctx, 16, x * scale) / scale
+    # a few FP32 roundings that fall the other way, 16 unit roundoffs, and the subnormals'
+    # own, independent over the products of the M2L and the terms of the other three steps
+    sums = np.sqrt(6 * wl.n * wl.P + 6 * (wl.n * wl.P + 2 * wl.n_nodes))
+    for r in range(16):
+        rms = np.sqrt(np.mean(np.abs(got[r] - ref[r]) ** 2))
+        size = np.sqrt(np.mean(np.abs(ref[r]) ** 2))
+        assert rms <= 16 * 2.0**-24 * size + 16 * sums * 2.0 ** (int(k[r]) - 149), (r, int(k[r]), rms / size)
