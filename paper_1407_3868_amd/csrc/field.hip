@@ -221,7 +221,9 @@ __global__ __launch_bounds__(kFieldThreads) void k_field_part(
     for (int m = m0; m < m1; ++m) {
       const double dx = X - xy[m].x, dy = Y - xy[m].y;
       const double d2 = dx * dx + dy * dy;
-      const double ri = rsqrt(d2), rr = d2 * ri;
+      // the root rounded as sqrt rounds it (one Newton step from d2 / sqrt(d2)): the
+      // phase of a far particle carries the distance's error times kc
+      const double ri = rsqrt(d2), r0 = d2 * ri, rr = fma(0.5 * ri, fma(-r0, r0, d2), r0);
       const double rad = types ? rtype[types[m]] : r_enc;
       if (!(rr > (1.0 + 1e-9) * rad) && sqrt(d2) < rad) inside = true;  // decided on the rounded root
       const double z = kc * rr, zi = ri / kc;

@@ -1,0 +1,47 @@
+"""The field far from a particle: one particle of order 0 in a strip whose three
+layers are the same medium, so that nothing is reflected and the particle's
+part, the difference of the fields with and without it, is b_0 H_0(k r).
+
+Distances between 1024 and 2048 are multiples of 2^-8 along the strip and
+k = 1: their squares and roots are exact in FP64, so that the argument of H_0
+is.  Tolerance 16 unit roundoffs: the reduced phase, its sine and cosine, the
+amplitude's root, the two short series, three products and the difference, two
+at most each.
+"""
+import numpy as np
+import pytest
+
+import paper_1407_3868_amd as mp
+
+pytestmark = pytest.mark.gpu
+
+
+def _h0(z):
+    """Hankel's expansion of H_0 in extended precision (z >= 1000)."""
+    z = z.astype(np.longdouble)
+    s = np.zeros(z.shape, np.clongdouble)
+    a = np.longdouble(1)
+    for k in range(12):
+        s = s + np.clongdouble(1j) ** k * a / z**k
+        a = a * -np.longdouble((2 * k + 1) ** 2) / (8 * (k + 1))
+    pi = np.longdouble("3.14159265358979323846264338327950288")
+    ph = z - pi / 4
+    return np.sqrt(2 / (pi * z)) * (np.cos(ph) + 1j * np.sin(ph)) * s
+
+
+def test_distance_of_far_receivers():
+    ctx = mp.Context(0)
+    ctx.set_layers(1.0, 1.0, 1.0, 4.0)
+    ctx.set_scattering_matrix(1, 0.25, np.eye(3, dtype=complex))
+    ctx.set_geometry(np.array([[0.0, -2.0]]), np.array([0.0]))
+    ctx.set_contour(128, 1e-4, 4.0)
+    rng = np.random.default_rng(9)
+    x = (1024 + rng.integers(0, 1 << 18, 2000) / 256.0) * rng.choice([-1.0, 1.0], 2000)
+    rcv = np.stack([x, np.full(x.size, -2.0)], 1)
+    src = np.array([0.0, 1.0])
+    beta = np.zeros((1, 3), np.complex128)
+    without = ctx.eval_field(src, beta, rcv)
+    beta[0, 1] = 2.0**40
+    part = (ctx.eval_field(src, beta, rcv) - without) * 2.0**-40
+    ref = _h0(np.abs(x))
+    assert np.abs((part - ref) / ref).max() <= 16 * 2.0**-53 * 2
