@@ -291,7 +291,7 @@ __global__ __launch_bounds__(64 * kM2lWaves, 2) void k_m2l_f64(const double2 *__
     for (int g0 = 0; g0 < sb && lt0 < n; g0 += 4) {
       const int s = g0 + g;  // this lane's source within the batch
       cx<double> hp[NT], hc[NT], t[NT], tq[NT];
-      double tz[NT], f[NT];
+      double tz[NT];
 #pragma unroll
       for (int tt = 0; tt < NT; ++tt) {
         hp[tt] = ld<double>(pa[tt][0]);
@@ -299,7 +299,6 @@ __global__ __launch_bounds__(64 * kM2lWaves, 2) void k_m2l_f64(const double2 *__
         t[tt] = ld<double>(pa[tt][2]);
         tq[tt] = t[tt];
         tz[tt] = pa[tt][3].x;
-        f[tt] = 0.0;
       }
       load_pairs(mb + s + 4);  // next group's entries in flight
       const double *ar = &sa[0][s][3 + (lane & 3)], *ai = &sa[1][s][3 + (lane & 3)], *as = &sa[2][s][3 + (lane & 3)];
@@ -314,8 +313,9 @@ __global__ __launch_bounds__(64 * kM2lWaves, 2) void k_m2l_f64(const double2 *__
             hq[tt] = hm[tt] = hp[tt];  // H_0
           } else {
             if (q >= 2) {
-              f[tt] += tz[tt];  // 2 (q - 1) / z
-              const cx<double> hn = mk(fma(f[tt], hc[tt].re, -hp[tt].re), fma(f[tt], hc[tt].im, -hp[tt].im));
+              // not a running sum of 2 / z: its roundings add up to four times the error of h_32
+              const double f = (q - 1) * tz[tt];  // 2 (q - 1) / z
+              const cx<double> hn = mk(fma(f, hc[tt].re, -hp[tt].re), fma(f, hc[tt].im, -hp[tt].im));
               hp[tt] = hc[tt];
               hc[tt] = hn;
               tq[tt] = tq[tt] * t[tt];
