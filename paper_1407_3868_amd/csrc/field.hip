@@ -227,23 +227,28 @@ __global__ __launch_bounds__(kFieldThreads) void k_field_part(
       const double rad = types ? rtype[types[m]] : r_enc;
       if (!(rr > (1.0 + 1e-9) * rad) && sqrt(d2) < rad) inside = true;  // decided on the rounded root
       const double z = kc * rr, zi = ri / kc;
-      const cx<double> t = mk(dx * ri, dy * ri);
+      // e^{i phi}, rounded as quotients: its powers multiply its error by the order
+      cx<double> t = mk(dx * ri, dy * ri);
+      t = mk(fma(fma(-t.re, rr, dx), ri, t.re), fma(fma(-t.im, rr, dy), ri, t.im));
       cx<double> hp, hc;
       hankel01(z, zi, hp, hc);
       const double2 *b = D + static_cast<int64_t>(m) * P;
       cmac(acc, hp, ld<double>(b[0]));
       cx<double> tq = t;
-      const double tz = 2.0 * zi;
-      double f = tz;
+      // 2q / z rounded once per order: 2 / z in two parts (a running sum, or the
+      // multiples of a rounded 2 / z, would carry their errors into every order)
+      const double tz = 2.0 * zi, tl = fma(-tz, z, 2.0) * zi;
+      double qd = 1.0;
 #pragma unroll 4
       for (int q = 1; q <= p; ++q) {
         const cx<double> dp = ld<double>(b[2 * q - 1]), dm = ld<double>(b[2 * q]);
         // tq b_q + (-1)^q conj(tq) b_{-q}
         cmac(acc, hc, mk(fma(tq.re, dp.re, -tq.im * dm.im), fma(tq.re, dp.im, tq.im * dm.re)));
+        const double f = fma(qd, tz, qd * tl);
         const cx<double> hn = mk(fma(f, hc.re, -hp.re), fma(f, hc.im, -hp.im));  // H_{q+1} = (2q / z) H_q - H_{q-1}
         hp = hc;
         hc = hn;
-        f += tz;
+        qd += 1.0;
         tq = tq * t;
       }
     }

@@ -45,3 +45,32 @@ def test_distance_of_far_receivers():
     part = (ctx.eval_field(src, beta, rcv) - without) * 2.0**-40
     ref = _h0(np.abs(x))
     assert np.abs((part - ref) / ref).max() <= 16 * 2.0**-53 * 2
+
+
+@pytest.mark.parametrize("side", [1, -1])
+def test_orders_of_near_receivers(side):
+    # one coefficient of order +-p: b H_p(k r) e^{+-ip phi} on a line, where the phase is +-1.
+    # Root mean square over the receivers in unit roundoffs: z once (0.41) and about 16 times
+    # over in H_16 (7), 15 rounded factors and multiply-adds (2), H_0 and H_1 up to 3 each (6)
+    import scipy.special as sp
+    p = 16
+    ctx = mp.Context(0)
+    ctx.set_layers(1.0, 1.0, 1.0, 4.0)
+    ctx.set_scattering_matrix(p, 0.01, np.eye(2 * p + 1, dtype=complex))
+    ctx.set_geometry(np.array([[0.0, -2.0]]), np.array([0.0]))
+    ctx.set_contour(128, 0.1, 4.0)
+    rng = np.random.default_rng(10)
+    x = rng.integers(1 << 10, 3 << 10, 2000) / 1024.0  # exact squares and roots
+    rcv = np.stack([x, np.full(x.size, -2.0)], 1)
+    src = np.array([0.0, 1.0])
+    beta = np.zeros((1, 2 * p + 1), np.complex128)
+    without = ctx.eval_field(src, beta, rcv)
+    beta[0, p + side * p] = 1.0  # |H_16| > 1e9 here
+    part = ctx.eval_field(src, beta, rcv) - without
+    z = x.astype(np.longdouble)
+    h = [sp.j0(x) + 1j * sp.y0(x).astype(np.clongdouble), sp.j1(x) + 1j * sp.y1(x).astype(np.clongdouble)]
+    for q in range(2, p + 1):
+        h.append(2 * (q - 1) / z * h[-1] - h[-2])
+    err = np.abs((part - h[p]) / h[p])
+    rms = float(np.sqrt(np.mean(err**2))) / 2.0**-53
+    assert rms <= 15, rms
