@@ -1121,16 +1121,26 @@ static int m2l_variant(const mpsl_ctx *ctx, int prec) {
 // sixth more while a unit has one block only, plus the writing and summing of
 // the chunks' partials at HBM rate; the best of up to 128 counts.  (5000
 // particles FP32: 42 chunks and 1.49 ms, as 125, which left 3x the partials to
-// sum; 1000 particles FP64, p = 12: 63 chunks, 83 us.)  Right-hand sides
-// multiply the blocks and the partials; all together have no more partial slots
-// than one right-hand side would to fill the chip with waves.  (1400 particles,
-// 15 right-hand sides, FP64, p = 16: dividing the count of one left a single
-// chunk, 330 blocks on 256 units, 6.40 ms; the rule's count 3.98.)
+// sum; 1000 particles FP64, p = 12: 63 chunks, 83 us.)  Right-hand sides multiply
+// the blocks and the partials, and neither one nor several of them get more
+// partial slots than m2l_slot_bound: partials of 20000 particles would take more
+// memory than all other work buffers.  (1400 particles, 15 right-hand sides,
+// FP64, p = 16: dividing the count of one left a single chunk, 330 blocks on 256
+// units, 6.40 ms; the rule's count 3.98.  250 particles, 32 right-hand sides,
+// FP64, p = 5: one chunk, 128 blocks, 163 us; the rule's count 90.)
+static int m2l_slot_bound(const mpsl_ctx *ctx, int from) {
+  // about 2560 blocks of 128 lanes, from order `from` on 10240 of 64
+  const int n = static_cast<int>(ctx->n);
+  if (ctx->p < from) return std::max(1, std::min(cdiv(2560, cdiv(n, kThreads)), n));
+  return cdiv(n, m2l_mfma_chunk_len(n, std::max(1, std::min(cdiv(10240, cdiv(n, 64)), n))));
+}
+
 static int m2l_mfma_chunks(const mpsl_ctx *ctx, int prec, int nt, int nrhs) {
   const int n = static_cast<int>(ctx->n), P = 2 * ctx->p + 1;
   const int bpc = cdiv(n, 64 * nt) * nrhs, units = std::max(1, ctx->n_cu);
-  const int fill = std::max(1, std::min(cdiv(n, 4), 10000 / cdiv(n, 64)) / nrhs);
-  const int cmax = nrhs > 1 ? std::min(128, fill) : std::min(128, cdiv(n, 4));
+  // a context's partials hold one right-hand side of either precision
+  const int slots = m2l_slot_bound(ctx, nrhs > 1 && prec == MPSL_FP64 ? 15 : 12) / nrhs;
+  const int cmax = std::max(1, std::min(std::min(128, slots), cdiv(n, 4)));
   const bool f64 = prec == MPSL_FP64;
   const double t_group = (f64 ? 525.0 : 260.0) * P * nt / 2.3e3;                        // us
   const double t_slot = 2.0 * nrhs * n * P * (f64 ? sizeof(double2) : sizeof(float2)) / 4.5e6;  // us

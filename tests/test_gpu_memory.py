@@ -56,3 +56,16 @@ def test_refused_call_leaves_no_trace():
     assert e.value.status == -4
     batch.close()
     assert np.array_equal(_batch(ctx, 1, x), ref)
+
+
+@pytest.mark.parametrize("p,most", [(1, 9), (8, 9), (11, 9), (12, 17), (16, 17)])
+def test_partial_slots_of_large_layouts(p, most):
+    # 40000 particles: 2560 blocks of 128 targets, from p = 12 on 10240 of 64
+    # (the geometry alone fixes the count; no tables are built)
+    ctx = mp.Context(0)
+    ctx.set_layers(6.0, 9.0, 12.0, 20.0)
+    ctx.set_scattering_matrix(p, 0.3, np.eye(2 * p + 1, dtype=complex))
+    i = np.arange(40000)
+    ctx.set_geometry(np.stack([0.75 * (i // 20), -1.0 - 0.8 * (i % 20)], 1), np.zeros(i.size))
+    for prec in (0, 1):
+        assert 1 <= ctx.get_tuning(prec)["chunks"] <= most
