@@ -31,7 +31,7 @@ constexpr int kM2LMfma = 2;
 constexpr int kM2LMfmaWide = 3;
 constexpr int kM2LMfmaMaxP = 16;
 // Variant used before any tuning: by expansion order, precision and size.
-int m2l_default_variant(const mpsl_ctx *ctx, int prec);
+int m2l_default_variant(const mpsl_ctx *ctx, int prec, int nrhs = 1);
 // nrhs right-hand sides: beta [nrhs][n][P]; part of rhs r at part + r * pstride.
 int launch_m2l(mpsl_ctx *ctx, int prec, const void *beta, void *part, int chunks, int variant = -1,
                int nrhs = 1, int64_t pstride = 0);

@@ -1096,20 +1096,32 @@ __global__ __launch_bounds__(256) void k_rhs_transpose(const float2 *__restrict_
     if (e_ != hipSuccess) return set_err(ctx, MPSL_EHIP, std::string("kernel launch: ") + hipGetErrorString(e_)); \
   } while (0)
 
-// The matrix-core forms win at every order they take (measured at 1000 and
-// 5000 particles; FP32 p = 16 1.49 against 3.04 ms, FP64 p = 12 0.083 against
-// 0.146 ms).  FP64 takes 32 targets per wave up to p = 12 (they share the
-// coefficient reads: 83 against 88 us at 1000 particles, p = 12; at p = 16 the
-// registers spill, 1245 against 1215 us at 3001) once that leaves enough
-// waves (203 particles, p = 12: 13.5 against 9.4 us).
-int m2l_default_variant(const mpsl_ctx *ctx, int prec) {
+// The matrix-core forms win from order 4 (FP64) and 6 (FP32) on (matvecs, one lane
+// per target and matrix cores, us: FP32 p = 6, 1000 and 5000 particles 59 and 54,
+// 704 and 641; p = 16 187 and 116, 3168 and 1781; FP64 p = 4 61 and 50, 536 and
+// 542; p = 8 111 and 81, 1363 and 1193).  Below, the padding to 16 or 4 rows costs
+// more than the vector units' work, once there are pairs enough for its one lane
+// per target to fill the chip: FP32 p <= 5 from 1e6 pairs on (p = 4: 500 particles
+// with one right-hand side 43 and 27, 1000 47 and 47, 2000 90 and 103, 5000 396
+// and 493, 3000 with eight 973 and 1296), FP64 p <= 3 from 3e7 (p = 3: 1400 with
+// eight 249 and 256, 3000 with 15 1734 and 1940, 5000 with two 791 and 840).
+// FP64 takes 32 targets per wave up to p = 12 (they share the coefficient reads;
+// at p = 16 the registers spill, 1245 against 1215 us at 3001 particles) once that
+// leaves enough waves (p = 12, 16 and 32 targets: 300 particles 41.7 and 44.2 us,
+// 600 71.2 and 71.0, 1000 130 and 125).
+int m2l_default_variant(const mpsl_ctx *ctx, int prec, int nrhs) {
   if (ctx->p > kM2LMfmaMaxP) return kM2LWhole;
-  return prec == MPSL_FP64 && ctx->p <= 12 && ctx->n >= 768 ? kM2LMfmaWide : kM2LMfma;
+  const double pairs = static_cast<double>(ctx->n) * ctx->n * nrhs;
+  if (prec == MPSL_FP64) {
+    if (ctx->p <= 3 && pairs >= 3e7) return kM2LWhole;
+    return ctx->p <= 12 && ctx->n >= 768 ? kM2LMfmaWide : kM2LMfma;
+  }
+  return ctx->p <= 5 && pairs >= 1e6 ? kM2LWhole : kM2LMfma;
 }
 
-static int m2l_variant(const mpsl_ctx *ctx, int prec) {
+static int m2l_variant(const mpsl_ctx *ctx, int prec, int nrhs) {
   int v = ctx->tune[prec == MPSL_FP64 ? 0 : 1].variant;
-  if (v < 0) v = m2l_default_variant(ctx, prec);
+  if (v < 0) v = m2l_default_variant(ctx, prec, nrhs);
   if (v >= kM2LMfma && ctx->p > kM2LMfmaMaxP) v = kM2LWhole;
   return v;
 }
@@ -1164,7 +1176,7 @@ int chunks_m2l(const mpsl_ctx *ctx, int prec, int nrhs) {
   const int tuned = ctx->tune[prec == MPSL_FP64 ? 0 : 1].chunks;
   if (tuned > 0) return std::max(1, static_cast<int>(std::min<int64_t>(tuned, ctx->n)) / nrhs);
   if (ctx->m2l_chunks > 0) return std::max(1, static_cast<int>(std::min<int64_t>(ctx->m2l_chunks, ctx->n)) / nrhs);
-  const int v = m2l_variant(ctx, prec);
+  const int v = m2l_variant(ctx, prec, nrhs);
   if (v >= kM2LMfma) return m2l_mfma_chunks(ctx, prec, v == kM2LMfmaWide ? 2 : 1, nrhs);
   // one lane per target: about 2560 blocks of 128 lanes
   const int64_t c = std::max<int64_t>(1, std::min<int64_t>(cdiv(2560, cdiv(ctx->n, kThreads)), ctx->n));
@@ -1243,7 +1255,7 @@ static int launch_m2l_t(mpsl_ctx *ctx, const void *beta, void *part, int chunks,
 
 int launch_m2l(mpsl_ctx *ctx, int prec, const void *beta, void *part, int chunks, int variant, int nrhs,
                int64_t pstride) {
-  if (variant < 0) variant = m2l_variant(ctx, prec);  // tuned or default; matrix cores up to p = 16
+  if (variant < 0) variant = m2l_variant(ctx, prec, nrhs);  // tuned or default; matrix cores up to p = 16
   return prec == MPSL_FP64 ? launch_m2l_t<double>(ctx, beta, part, chunks, variant, nrhs, pstride)
                            : launch_m2l_t<float>(ctx, beta, part, chunks, variant, nrhs, pstride);
 }
