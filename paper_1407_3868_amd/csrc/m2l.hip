@@ -857,7 +857,7 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs(const float2 *__re
 // source for all waves of the block, double-buffered, between the MFMAs.  (Split
 // beforehand, the parts were 1.5 to 2.4 times the size of the transposed beta,
 // which a context's memory budget may not have; the matvec of the case below
-// took 8.31 ms with them, 8.70 ms without.)  The matrix cores' bf16 sums do not
+// took 8.46 ms with them, 8.54 ms without.)  The matrix cores' bf16 sums do not
 // round to nearest, so they are added to running FP32 sums after every batch of
 // 8 sources and start again from zero.
 //
@@ -894,20 +894,18 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *_
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) acc[mt][ct][0] = acc[mt][ct][1] = v4{0, 0, 0, 0};
   float2 pre[4];  // this thread's source orders 4 w .. 4 w + 3 of right-hand side r0 + lane
-  float pre_up;   // and the source's power of two
   auto load_b = [&](int m) {
     const int64_t mc = min(m, n - 1);  // past the chunk: loaded, never used
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       pre[i] = 4 * w + i < P ? bt[(mc * KP + 4 * w + i) * r_pad + r0 + lane] : make_float2(0.f, 0.f);
-    pre_up = bt[(mc * KP + KP - 1) * r_pad + r0 + lane].x;
   };
   auto store_b = [&](int buf, int j) {  // real (j = 0) or imaginary parts
     {
       f32x2 x[2];
 #pragma unroll
       for (int i = 0; i < 2; ++i)
-        x[i] = pre_up * (j ? f32x2{pre[2 * i].y, pre[2 * i + 1].y} : f32x2{pre[2 * i].x, pre[2 * i + 1].x});
+        x[i] = j ? f32x2{pre[2 * i].y, pre[2 * i + 1].y} : f32x2{pre[2 * i].x, pre[2 * i + 1].x};
 #pragma unroll
       for (int k = 0; k < 3; ++k) {
         bf2 h[2];
@@ -950,8 +948,8 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *_
       float2 *h = H[w][lane] + OFF;
       if (l < n && m != l) {
         const float2 *pe = pairs + 4 * (static_cast<int64_t>(m) * n + l);
-        // times the inverse of the source's power of two, 2^-24 or 2^4
-        const float down = 1.0f / bt[(static_cast<int64_t>(m) * KP + KP - 1) * r_pad + r0].x;
+        // times the inverse of the source's power of two
+        const float down = bt[(static_cast<int64_t>(m) * KP + KP - 1) * r_pad + r0].x;
         cx<float> hp = down * ld<float>(pe[0]), hc = down * ld<float>(pe[1]);
         const cx<float> t = ld<float>(pe[2]);
         const float tz = pe[3].x;
@@ -1055,9 +1053,9 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *_
 
 // beta [r][m][P] -> bt [m][KP][r_pad] (r fastest; zero rows k >= P and
 // zero columns r >= nrhs), FP32: one block per source and 64 right-hand sides,
-// through LDS.  With scale (the bf16 form, which has its own zeros) the last
-// row, KP - 1 >= P, holds the power of two for the split of this block's
-// coefficients.
+// through LDS.  With scale (the bf16 form, which has its own zeros) the
+// coefficients are multiplied by the power of two for their split, and the last
+// row, KP - 1 >= P, holds its inverse.
 template <int P>
 __global__ __launch_bounds__(256) void k_rhs_transpose(const float2 *__restrict__ x, float2 *__restrict__ bt, int n,
                                                        int nrhs, int r_pad, bool scale) {
@@ -1074,11 +1072,12 @@ __global__ __launch_bounds__(256) void k_rhs_transpose(const float2 *__restrict_
     big |= bf_big(v);
   }
   big = __syncthreads_or(big);
-  const float up = scale ? bf_scale(big).up : 0.f;
+  const BfScale sc = scale ? bf_scale(big) : BfScale{1.f, 0.f};
   float2 *o = bt + m * KP * r_pad + r0;
   for (int e = threadIdx.x; e < 64 * KP; e += 256) {
     const int k = e / 64, r = e % 64;
-    o[static_cast<int64_t>(k) * r_pad + r] = k < P ? t[k][r] : make_float2(k == KP - 1 ? up : 0.f, 0.f);
+    o[static_cast<int64_t>(k) * r_pad + r] = k < P ? make_float2(sc.up * t[k][r].x, sc.up * t[k][r].y)
+                                                   : make_float2(k == KP - 1 ? sc.down : 0.f, 0.f);
   }
 }
 
