@@ -1,6 +1,7 @@
 // Row a1: the all-pairs free-space M2L, its forms for one and for many
 // right-hand sides, and the FMM's near field (the same pair translation).
 // Layouts as in kernels.hip.
+#include <atomic>
 #include <cmath>
 
 #include "kernels.h"
@@ -1259,25 +1260,52 @@ int launch_m2l(mpsl_ctx *ctx, int prec, const void *beta, void *part, int chunks
                            : launch_m2l_t<float>(ctx, beta, part, chunks, variant, nrhs, pstride);
 }
 
-// Source chunks: one block of either form runs per compute unit at a time, all
-// with the same work, so of the counts up to about 1024 blocks' worth the
-// smallest whose blocks fill their last round within 3 % of the best (2000
-// particles, 64 right-hand sides: 250 blocks, one chunk).
+// bf16 parts where one K step holds all orders (p = 8 .. 15; at p = 16 the 33
+// orders would pad to 64), else the FP32 form.
+static constexpr bool mrhs_bf(int p) { return p >= 8 && p <= 15; }
+
+// Blocks of the many-right-hand-side M2L resident per compute unit (occupancy
+// query, cached per order; 1 if the query fails).
+static int mrhs_resident(int p) {
+  static std::atomic<int> cache[kMaxP + 1];
+  if (p < kMinP || p > kMaxP) return 1;
+  int r = cache[p].load(std::memory_order_relaxed);
+  if (r > 0) return r;
+  const void *fn = nullptr;
+  switch (p) {
+#define X(PP)                                                                     \
+  case PP:                                                                        \
+    if constexpr (mrhs_bf(PP)) fn = reinterpret_cast<const void *>(&k_m2l_mrhs_bf<PP>); \
+    else fn = reinterpret_cast<const void *>(&k_m2l_mrhs<PP>);                    \
+    break;
+    MPSL_P_CASES(X)
+#undef X
+  }
+  int nb = 0;
+  if (!fn || hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, 64 * kMrhsWaves, 0) != hipSuccess || nb < 1) {
+    (void)hipGetLastError();
+    nb = 1;
+  }
+  cache[p].store(nb, std::memory_order_relaxed);
+  return nb;
+}
+
+// Source chunks: all blocks carry the same work, so of the counts up to about
+// 1024 blocks' worth the smallest whose blocks fill the last round of the
+// resident slots within 3 % of the best (2000 particles, 64 right-hand sides,
+// 250 blocks: one chunk at p = 12, one block per unit; at p = 4, two per unit, two
+// chunks, 2959 us where one took 3306 and five 2951).
 int chunks_m2l_mrhs(const mpsl_ctx *ctx, int nrhs) {
   const int64_t blocks = static_cast<int64_t>(cdiv(ctx->n, kMrhsWaves)) * cdiv(nrhs, 64);
   const int hi = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(cdiv(1024, blocks), cdiv(ctx->n, kMrhsBatch))));
-  const int units = std::max(1, ctx->n_cu);
-  auto cost = [&](int c) { return static_cast<double>(cdiv(blocks * c, units)) / c; };
+  const int64_t slots = static_cast<int64_t>(std::max(1, ctx->n_cu)) * mrhs_resident(ctx->p);
+  auto cost = [&](int c) { return static_cast<double>(cdiv(blocks * c, slots)) / c; };
   double best = 1e300;
   for (int c = 1; c <= hi; ++c) best = std::min(best, cost(c));
   for (int c = 1; c <= hi; ++c)
     if (cost(c) <= 1.03 * best) return c;
   return hi;
 }
-
-// bf16 parts where one K step holds all orders (p = 8 .. 15; at p = 16 the 33
-// orders would pad to 64), else the FP32 form.
-static constexpr bool mrhs_bf(int p) { return p >= 8 && p <= 15; }
 
 int launch_m2l_mrhs(mpsl_ctx *ctx, const void *beta, void *part, int chunks, int nrhs, int64_t pstride) {
   const int n = static_cast<int>(ctx->n);
