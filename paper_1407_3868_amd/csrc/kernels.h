@@ -123,6 +123,8 @@ inline int m2l_slots(const mpsl_ctx *ctx, int prec) { return chunks_m2l(ctx, pre
 int chunks_s2l(const mpsl_ctx *ctx, int nrhs, int prec);
 // Particle chunks of the M2S grid for precision prec.
 int chunks_m2s(const mpsl_ctx *ctx, int nrhs, int prec);
+// The chunks whose partials ctx->m2s_part holds; more go to a table that is free then.
+int m2s_part_chunks(const mpsl_ctx *ctx, int nrhs, int prec);
 
 // Sommerfeld transforms by tile-local interpolation (somm.hip): M2S spectra
 // into spec ([nrhs][2][ns], FP64) and S2L local expansions into one part slot

@@ -985,19 +985,9 @@ static int m2s_resident(int p) {
   return nb;
 }
 
-int chunks_m2s(const mpsl_ctx *ctx, int nrhs, int prec) {
-  if (ctx->m2s_chunks > 0) return static_cast<int>(std::min<int64_t>(ctx->m2s_chunks, ctx->n));
-  // about 2048 node-group x chunk tasks, but at least 80 particles per chunk:
-  // shorter chunks spend more on the epilogue and on summing the partials
-  // than they gain in parallelism (1024 nodes, 5000 particles: 256 -> 63
-  // chunks, M2S and partial sum 75 -> about 45 us in FP32).  Up to 16 chunks 32
-  // particles will do: their steps are a serial chain (512 nodes, p = 16, whole
-  // matvec, chunks of 80 and 32: 203 particles 48.9 and 44.9 us in FP64, 35.6
-  // and 34.2 in FP32; 500: 79.8 and 76.4, 59.9 and 56.5).  One chunk to 48, which
-  // needs no k_nodes (p = 8, FP64, one and two chunks: 16 particles 21.7 and
-  // 23.6 us, 48: 24.4 and 25.4, 64: 25.4 and 25.6).
+// M2S chunks with at most by_n of them for the particles' sake.
+static int m2s_count(const mpsl_ctx *ctx, int nrhs, int prec, int64_t by_n) {
   const int qb = cdiv(ctx->ns, kThreads) * 2 * nrhs;
-  const int64_t by_n = std::max<int64_t>(cdiv(ctx->n, 80), ctx->n <= 48 ? 1 : std::min(16, cdiv(ctx->n, 32)));
   const int c0 = static_cast<int>(
       std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(cdiv(2048, qb), by_n), ctx->n)));
   // short contours: lowered by up to half to the count whose blocks fill
@@ -1009,6 +999,38 @@ int chunks_m2s(const mpsl_ctx *ctx, int nrhs, int prec) {
   const int64_t bpc = static_cast<int64_t>(cdiv(ctx->ns, 16 * kM2sWaves)) * 2 * nrhs;
   const int64_t slots = static_cast<int64_t>(ctx->n_cu) * (f64 ? m2s_resident<double>(ctx->p) : m2s_resident<float>(ctx->p));
   return balanced_chunks(bpc, slots, std::max(1, c0 / 2), c0);
+}
+
+int m2s_part_chunks(const mpsl_ctx *ctx, int nrhs, int prec) {
+  if (ctx->m2s_chunks > 0) return static_cast<int>(std::min<int64_t>(ctx->m2s_chunks, ctx->n));
+  // about 2048 node-group x chunk tasks, but at least 80 particles per chunk:
+  // shorter chunks spend more on the epilogue and on summing the partials
+  // than they gain in parallelism (1024 nodes, 5000 particles: 256 -> 63
+  // chunks, M2S and partial sum 75 -> about 45 us in FP32).
+  return m2s_count(ctx, nrhs, prec, cdiv(ctx->n, 80));
+}
+
+int chunks_m2s(const mpsl_ctx *ctx, int nrhs, int prec) {
+  const int base = m2s_part_chunks(ctx, nrhs, prec);
+  if (ctx->m2s_chunks > 0) return base;
+  // Up to 16 chunks 32 particles will do: their steps are a serial chain (512
+  // nodes, p = 16, whole matvec, chunks of 80 and 32: 203 particles 48.9 and 44.9
+  // us in FP64, 35.6 and 34.2 in FP32; 500: 79.8 and 76.4, 59.9 and 56.5).  One
+  // chunk to 48, which needs no k_nodes (p = 8, FP64, one and two chunks: 16
+  // particles 21.7 and 23.6 us, 48: 24.4 and 25.4, 64: 25.4 and 25.6).  The
+  // partials of these chunks lie in the S2L coefficient table of the other
+  // precision (m2s_partials), which takes 2P of them in FP32 and P / 2 in FP64.
+  if (ctx->n <= 48) return base;
+  const int P = 2 * ctx->p + 1, most = std::min(16, prec == MPSL_FP64 ? P / 2 : 2 * P);
+  return std::max(base, std::min(most, m2s_count(ctx, nrhs, prec, std::max(cdiv(ctx->n, 80), std::min(16, cdiv(ctx->n, 32))))));
+}
+
+// Where the M2S writes its partials: m2s_part, sized for m2s_part_chunks, or with
+// more chunks the S2L coefficients of the other precision, which nothing reads
+// between the M2S and the end of the node sums.
+static void *m2s_partials(const mpsl_ctx *ctx, int nrhs, int prec, int chunks) {
+  if (chunks <= m2s_part_chunks(ctx, nrhs, prec)) return ctx->m2s_part.p;
+  return prec == MPSL_FP64 ? ctx->Up32.p : ctx->Up64.p;
 }
 
 #define LAUNCH_CHECK(ctx)                                                          \
@@ -1044,14 +1066,15 @@ template <typename T>
 static int launch_m2s_t(mpsl_ctx *ctx, const void *beta, int nrhs, bool nodes = false) {
   const int n = static_cast<int>(ctx->n);
   const bool f64 = std::is_same<T, double>::value;
-  const int chunks = chunks_m2s(ctx, nrhs, f64 ? MPSL_FP64 : MPSL_FP32);
+  const int prec = f64 ? MPSL_FP64 : MPSL_FP32;
+  const int chunks = chunks_m2s(ctx, nrhs, prec);
   const int chunk_len = cdiv(n, chunks);
   const dim3 grid = nodes ? dim3(cdiv(ctx->ns, 8 * kM2sWaves), 1, nrhs)
                           : dim3(cdiv(ctx->ns, 16 * kM2sWaves), chunks, 2 * nrhs);
   const auto *E = static_cast<const cv_t<T> *>(f64 ? ctx->gt.E64.p : ctx->gt.E32.p);
   const auto *W = static_cast<const cv_t<T> *>(f64 ? ctx->ct.W64.p : ctx->ct.W32.p);
   const auto *b = static_cast<const cv_t<T> *>(beta);
-  auto *part = static_cast<cv_t<T> *>(ctx->m2s_part.p);
+  auto *part = static_cast<cv_t<T> *>(m2s_partials(ctx, nrhs, prec, chunks));
   const auto *R = static_cast<const double2 *>(ctx->ct.R.p), *cq = static_cast<const double2 *>(ctx->ct.cq.p),
              *U = static_cast<const double2 *>(ctx->ct.U64.p);
   auto *Up = static_cast<cv_t<T> *>(f64 ? ctx->Up64.p : ctx->Up32.p);
@@ -1077,9 +1100,10 @@ static int launch_m2s_t(mpsl_ctx *ctx, const void *beta, int nrhs, bool nodes = 
 template <typename T>
 static int launch_nodes_t(mpsl_ctx *ctx, void *spec, int nrhs) {
   const bool f64 = std::is_same<T, double>::value;
-  const int chunks = chunks_m2s(ctx, nrhs, f64 ? MPSL_FP64 : MPSL_FP32);
+  const int prec = f64 ? MPSL_FP64 : MPSL_FP32;
+  const int chunks = chunks_m2s(ctx, nrhs, prec);
   hipLaunchKernelGGL(k_nodes<T>, dim3(cdiv(ctx->ns, kNodeBlock), nrhs), dim3(2 * kNodeBlock * kNodeLanes), 0,
-                     ctx->stream, static_cast<const cv_t<T> *>(ctx->m2s_part.p), ctx->ns, chunks,
+                     ctx->stream, static_cast<const cv_t<T> *>(m2s_partials(ctx, nrhs, prec, chunks)), ctx->ns, chunks,
                      static_cast<const double2 *>(ctx->ct.R.p), static_cast<const double2 *>(ctx->ct.cq.p),
                      static_cast<const double2 *>(ctx->ct.U64.p), 2 * ctx->p + 1, static_cast<double2 *>(spec),
                      static_cast<cv_t<T> *>(f64 ? ctx->Up64.p : ctx->Up32.p));

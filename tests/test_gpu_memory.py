@@ -69,3 +69,25 @@ def test_partial_slots_of_large_layouts(p, most):
     ctx.set_geometry(np.stack([0.75 * (i // 20), -1.0 - 0.8 * (i % 20)], 1), np.zeros(i.size))
     for prec in (0, 1):
         assert 1 <= ctx.get_tuning(prec)["chunks"] <= most
+
+
+def _lattice(n, p, budget=0, nodes=256, interp=False):
+    """n particles (geometry does not change the bytes held), nodes contour nodes."""
+    ctx = mp.Context(0, budget)
+    ctx.set_layers(6.0, 9.0, 12.0, 10.0)
+    ctx.set_scattering_matrix(p, 0.3, 1e-3 * np.eye(2 * p + 1, dtype=complex))
+    i = np.arange(n)
+    ctx.set_geometry(np.stack([1.8 * (i // 4 - n // 8), -1.5 - 1.8 * (i % 4)], 1), np.zeros(n))
+    ctx.set_contour(nodes, 0.05, 32.0)
+    return ctx
+
+
+def test_matvec_at_its_budget():
+    # 203 particles, p = 16, 256 nodes: tables and work buffers of both precisions, and the
+    # host calls' staging of two vectors
+    need = 20259656 + 2 * 203 * 33 * 16
+    free, tight = _lattice(203, 16), _lattice(203, 16, need)
+    rng = np.random.default_rng(95)
+    for prec, dt in ((0, np.complex128), (1, np.complex64)):
+        x = (rng.standard_normal((203, 33)) + 1j * rng.standard_normal((203, 33))).astype(dt)
+        assert np.array_equal(tight.apply(prec, x), free.apply(prec, x))
