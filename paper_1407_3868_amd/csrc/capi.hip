@@ -460,14 +460,17 @@ int build_tables(mpsl_ctx *ctx) {
   return ensure_work(ctx);
 }
 
+int work_slots(const mpsl_ctx *ctx) {
+  return std::max(chunks_m2l(ctx, MPSL_FP64), chunks_m2l(ctx, MPSL_FP32)) +
+         std::max(chunks_s2l(ctx, 1, MPSL_FP64), chunks_s2l(ctx, 1, MPSL_FP32));
+}
+
 int ensure_work(mpsl_ctx *ctx) {
   const int P = 2 * ctx->p + 1;
   const size_t len = static_cast<size_t>(ctx->n) * P;
-  const int ca = std::max(chunks_m2l(ctx, MPSL_FP64), chunks_m2l(ctx, MPSL_FP32));
-  const int cb = std::max(chunks_s2l(ctx, 1, MPSL_FP64), chunks_s2l(ctx, 1, MPSL_FP32));
   const int cc = std::max(m2s_part_chunks(ctx, 1, MPSL_FP64), m2s_part_chunks(ctx, 1, MPSL_FP32));
   int rc;
-  if ((rc = dev_alloc(ctx, ctx->part, (ca + cb) * len * sizeof(double2))) ||
+  if ((rc = dev_alloc(ctx, ctx->part, work_slots(ctx) * len * sizeof(double2))) ||
       (rc = dev_alloc(ctx, ctx->m2s_part, 2ull * cc * ctx->ns * sizeof(double2))) ||
       (rc = dev_alloc(ctx, ctx->spec, 2ull * ctx->ns * sizeof(double2))) ||
       (rc = dev_alloc(ctx, ctx->sigma, 4ull * ctx->ns * sizeof(double2))) ||

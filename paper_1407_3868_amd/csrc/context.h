@@ -263,6 +263,8 @@ int cluster_shape(int64_t n, const double *xy, int size, int *nc, int *mp);
 constexpr int kPcDefaultSize = 160;
 constexpr int kPcMaxDim = 16384;
 int ensure_work(mpsl_ctx *ctx);
+// Slots of n P FP64 entries that ensure_work gives the partial expansions.
+int work_slots(const mpsl_ctx *ctx);
 int matvec(mpsl_ctx *ctx, int prec, const void *x, void *y, int nrhs);
 int matvec(mpsl_ctx *ctx, int prec, const void *x, void *y);
 bool fmm_wanted(const mpsl_ctx *ctx);

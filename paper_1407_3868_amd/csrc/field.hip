@@ -296,22 +296,34 @@ __global__ __launch_bounds__(256) void k_field_sum(const double2 *__restrict__ p
 // About 2048 blocks for the particles and a quarter as many for the (cheaper)
 // nodes, with chunks of at least 16 particles and 32 nodes: shorter ones spend
 // more on writing and adding the partials than the lanes gain.  Receivers go
-// in batches, which bounds the partials to 11 MB; `small` (a context whose
-// memory budget has no room for them) takes 256 receivers and two slots at a time.
-FieldShape field_shape(const mpsl_ctx *ctx, int64_t nr, bool small) {
-  FieldShape s{1, 1, kFieldThreads};
-  if (small) return s;
-  s.batch = std::min<int64_t>(nr, 65536);
-  const int rb = cdiv(s.batch, kFieldThreads);
-  s.pchunks = std::max(1, std::min(cdiv(2048, rb), cdiv(ctx->n, 16)));
-  s.nchunks = std::max(1, std::min(cdiv(512, rb), cdiv(ctx->ns, 32)));
+// in batches, which bounds the partials to 10.5 MB.  With room (entries, at least
+// 32768) fewer blocks and smaller batches, so that the partials fit.
+FieldShape field_shape(const mpsl_ctx *ctx, int64_t nr, int64_t room) {
+  constexpr int64_t kBlocks = 2560;
+  const int64_t blocks = room > 0 ? std::min<int64_t>(kBlocks, room / kFieldThreads) : kBlocks;
+  const int nb = static_cast<int>(blocks / 5), pb = static_cast<int>(blocks) - nb;
+  FieldShape s{1, 1, std::min<int64_t>(nr, 65536)};
+  for (int pass = 0; pass < 2; ++pass) {
+    const int rb = cdiv(s.batch, kFieldThreads);
+    s.pchunks = std::max(1, std::min(pb / rb, cdiv(ctx->n, 16)));
+    s.nchunks = std::max(1, std::min(nb / rb, cdiv(ctx->ns, 32)));
+    if ((s.pchunks + s.nchunks) * s.batch <= blocks * kFieldThreads) break;
+    s.batch = std::min<int64_t>(s.batch, nb * static_cast<int64_t>(kFieldThreads));  // then no chunk count is raised to 1
+  }
   return s;
 }
 
-size_t field_scratch_bytes(const mpsl_ctx *ctx, const FieldShape &s) {
-  const size_t L = ctx->ks.size();
-  return sizeof(double2) * (3 * L * ctx->ns + static_cast<size_t>(s.pchunks + s.nchunks) * s.batch) +
-         sizeof(double) * (4 * L);
+size_t field_amp_bytes(const mpsl_ctx *ctx) { return sizeof(double2) * 3 * ctx->ks.size() * ctx->ns; }
+size_t field_part_bytes(const FieldShape &s) { return sizeof(double2) * (s.pchunks + s.nchunks) * s.batch; }
+
+double2 *field_idle(const mpsl_ctx *ctx, int64_t *room) {
+  const int64_t len = ctx->n * static_cast<int64_t>(2 * ctx->p + 1), stack = 2 * static_cast<int64_t>(ctx->ks.size());
+  // (the sizes that the buffers have from the start: what other calls made of them must not change the sums)
+  const int64_t a = std::min<int64_t>(ctx->scal.bytes / sizeof(double2), 65536) - stack;
+  const int64_t slots = work_slots(ctx) - 1;
+  const int64_t b = std::min<int64_t>(slots * len, static_cast<int64_t>(ctx->part.bytes / sizeof(double2)) - len);
+  *room = std::max(a, b);
+  return a >= b ? static_cast<double2 *>(ctx->scal.p) + stack : static_cast<double2 *>(ctx->part.p) + len;
 }
 
 std::vector<double> field_stack(const mpsl_ctx *ctx) {
@@ -329,15 +341,15 @@ std::vector<double> field_stack(const mpsl_ctx *ctx) {
 
 int launch_field(mpsl_ctx *ctx, const FieldShape &s, const std::vector<double> &layers, const void *beta,
                  const void *spec, const void *sigma, const double *src, int64_t nr, const void *rcv, void *u,
-                 void *scratch) {
+                 void *amp, double2 *part) {
   const int L = static_cast<int>(ctx->ks.size()), ns = ctx->ns, n = static_cast<int>(ctx->n), p = ctx->p;
   const int64_t len = static_cast<int64_t>(n) * (2 * p + 1);
-  auto *gl = static_cast<double2 *>(scratch);
+  auto *gl = static_cast<double2 *>(amp);
   auto *A = gl + static_cast<size_t>(L) * ns, *B = A + static_cast<size_t>(L) * ns;
-  auto *part = B + static_cast<size_t>(L) * ns;
-  auto *stack = reinterpret_cast<double *>(part + static_cast<size_t>(s.pchunks + s.nchunks) * s.batch);
+  auto *stack = static_cast<double *>(ctx->scal.p);  // the solver's reductions, free here
   auto *D = static_cast<double2 *>(ctx->part.p);  // the matvec's partials, free here, hold n P entries at least
-  if (ctx->part.bytes < len * sizeof(double2)) return set_err(ctx, MPSL_ESTATE, "work buffers not sized");
+  if (ctx->part.bytes < len * sizeof(double2) || ctx->scal.bytes < layers.size() * sizeof(double))
+    return set_err(ctx, MPSL_ESTATE, "work buffers not sized");
   MPSL_HIP_TRY(ctx, hipMemcpyAsync(stack, layers.data(), layers.size() * sizeof(double), hipMemcpyHostToDevice,
                                    ctx->stream));
   const auto *lam = static_cast<const double2 *>(ctx->ct.lam.p);

@@ -103,14 +103,18 @@ struct FieldShape {
   int pchunks, nchunks;  // chunks of the particles and of the contour nodes
   int64_t batch;         // receivers per launch
 };
-FieldShape field_shape(const mpsl_ctx *ctx, int64_t nr, bool small);
-// Bytes of the scratch that launch_field needs.
-size_t field_scratch_bytes(const mpsl_ctx *ctx, const FieldShape &s);
+// Partials of at most room entries (0: 10.5 MB).
+FieldShape field_shape(const mpsl_ctx *ctx, int64_t nr, int64_t room);
+// Bytes of the amplitudes and of the partials that launch_field needs, and the
+// larger of the work buffers that are free meanwhile, for the partials.
+size_t field_amp_bytes(const mpsl_ctx *ctx);
+size_t field_part_bytes(const FieldShape &s);
+double2 *field_idle(const mpsl_ctx *ctx, int64_t *room);
 // Layer data that launch_field uploads; the caller keeps it until the stream is done.
 std::vector<double> field_stack(const mpsl_ctx *ctx);
 int launch_field(mpsl_ctx *ctx, const FieldShape &s, const std::vector<double> &layers, const void *beta,
                  const void *spec, const void *sigma, const double *src, int64_t nr, const void *rcv, void *u,
-                 void *scratch);
+                 void *amp, double2 *part);
 
 // Source chunks of the M2L grid for precision prec (tuned, set, or automatic).
 int chunks_m2l(const mpsl_ctx *ctx, int prec, int nrhs = 1);

@@ -423,18 +423,26 @@ int eval_field_one(mpsl_ctx *ctx, const double *src, const mpsl_c128 *beta, int6
   if ((rc = mpsl::launch_m2s(ctx, MPSL_FP64, ctx->xbuf.p, ctx->spec.p))) return rc;
   if ((rc = mpsl::launch_reflect(ctx, ctx->spec.p, src, ctx->sigma.p))) return rc;
   const size_t rb = static_cast<size_t>(n_rcv) * sizeof(double2);
-  mpsl::FieldShape shape = mpsl::field_shape(ctx, n_rcv, false);
-  rc = mpsl::dev_alloc(ctx, ctx->ybuf, 2 * rb + mpsl::field_scratch_bytes(ctx, shape));
+  const size_t ab = mpsl::field_amp_bytes(ctx);
+  mpsl::FieldShape shape = mpsl::field_shape(ctx, n_rcv, 0);
+  double2 *part = nullptr;
+  // partials beside the staging, or, where the context's memory has a budget or is
+  // at its end, in the work buffers that it has anyway
+  rc = ctx->hbm_budget > 0 ? MPSL_ENOMEM
+                           : mpsl::dev_alloc(ctx, ctx->ybuf, 2 * rb + ab + mpsl::field_part_bytes(shape));
   if (rc == MPSL_ENOMEM) {
-    shape = mpsl::field_shape(ctx, n_rcv, true);
-    rc = mpsl::dev_alloc(ctx, ctx->ybuf, 2 * rb + mpsl::field_scratch_bytes(ctx, shape));
+    int64_t room = 0;
+    part = mpsl::field_idle(ctx, &room);
+    shape = mpsl::field_shape(ctx, n_rcv, room);
+    rc = mpsl::dev_alloc(ctx, ctx->ybuf, 2 * rb + ab);
   }
   if (rc) return rc;
   const std::vector<double> layers = mpsl::field_stack(ctx);
-  char *d_rcv = static_cast<char *>(ctx->ybuf.p), *d_u = d_rcv + rb;
+  char *d_rcv = static_cast<char *>(ctx->ybuf.p), *d_u = d_rcv + rb, *d_amp = d_u + rb;
+  if (!part) part = reinterpret_cast<double2 *>(d_amp + ab);
   MPSL_HIP_TRY(ctx, hipMemcpyAsync(d_rcv, rcv, rb, hipMemcpyHostToDevice, ctx->stream));
   if ((rc = mpsl::launch_field(ctx, shape, layers, ctx->xbuf.p, ctx->spec.p, ctx->sigma.p, src, n_rcv, d_rcv, d_u,
-                               d_u + rb)))
+                               d_amp, part)))
     return rc;
   MPSL_HIP_TRY(ctx, hipMemcpyAsync(u_out, d_u, rb, hipMemcpyDeviceToHost, ctx->stream));
   MPSL_HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));

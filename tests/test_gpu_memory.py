@@ -71,6 +71,26 @@ def test_partial_slots_of_large_layouts(p, most):
         assert 1 <= ctx.get_tuning(prec)["chunks"] <= most
 
 
+@pytest.mark.parametrize("n,p,nr", [(16, 8, 1), (16, 8, 70000), (70, 8, 300), (70, 8, 4096), (203, 16, 4096),
+                                    (203, 16, 66000)])
+def test_field_at_its_budget(n, p, nr):
+    # beyond the tables, the work buffers and one vector (rhs holds one too): receivers,
+    # values, three complex numbers per node and layer and the two interfaces
+    src = np.array([0.3, 1.5])
+    free = _lattice(n, p)
+    free.rhs(src)
+    need = free.memory()[0] + 2 * nr * 16 + 3 * 3 * 256 * 16 + 2 * 8
+    tight = _lattice(n, p, need)
+    tight.rhs(src)
+    rng = np.random.default_rng(96)
+    beta = 1e-3 * (rng.standard_normal((n, 2 * p + 1)) + 1j * rng.standard_normal((n, 2 * p + 1)))
+    rcv = np.stack([rng.uniform(-50.0, 50.0, nr), rng.choice([-0.4, -9.2, -12.0, 0.5, 2.0], nr)], 1)
+    want = free.eval_field(src, beta, rcv)
+    got = tight.eval_field(src, beta, rcv)
+    assert np.linalg.norm(got - want) <= 1e-11 * np.linalg.norm(want)
+    assert np.array_equal(got, tight.eval_field(src, beta, rcv))
+
+
 def _lattice(n, p, budget=0, nodes=256, interp=False):
     """n particles (geometry does not change the bytes held), nodes contour nodes."""
     ctx = mp.Context(0, budget)
