@@ -650,9 +650,12 @@ int s2l_interp_t(mpsl_ctx *ctx, void *part, int chunks, int nrhs, int64_t pstrid
   const int64_t rows = 2ll * nrhs * pl.nT;
   int nchunk = 1, nsum = 0;
   if (pl.nint > 0) {
-    // node chunks so that the waves fill the chip once (7 per SIMD in FP32)
+    // node chunks so that the waves fill the chip once (7 per SIMD in FP32), with no
+    // more partials than 2048 blocks of four waves over the tiles would write
     const int tb = cdv(pl.nrow, 16 * coarse_rb<T>());
-    nchunk = std::max(1, std::min(16, static_cast<int>(28 * ctx->n_cu / (static_cast<int64_t>(pl.nint) * tb * 2 * nrhs))));
+    const int64_t per = static_cast<int64_t>(pl.nint) * 2 * nrhs;
+    const int most = std::min(16, cdv(2048, per * cdv(pl.nT, 64 * coarse_rb<T>())));
+    nchunk = std::max(1, std::min(most, static_cast<int>(28 * ctx->n_cu / (per * tb))));
     if ((rc = dev_alloc(ctx, pl.Bp, static_cast<size_t>(nchunk) * rows * nci * sizeof(cv_t<T>)))) return rc;
     nsum = cdv(rows * nci, 256);
     hipLaunchKernelGGL(k_si_coarseB_mfma<T>, dim3(pl.nint, tb, nchunk * 2 * nrhs), dim3(64), 0,

@@ -98,7 +98,12 @@ def _lattice(n, p, budget=0, nodes=256, interp=False):
     ctx.set_scattering_matrix(p, 0.3, 1e-3 * np.eye(2 * p + 1, dtype=complex))
     i = np.arange(n)
     ctx.set_geometry(np.stack([1.8 * (i // 4 - n // 8), -1.5 - 1.8 * (i % 4)], 1), np.zeros(n))
-    ctx.set_contour(nodes, 0.05, 32.0)
+    if interp:
+        b, h = mp.span_contour_params(1.8 * n / 4, 1e-6)
+        ctx.set_contour_span(b, 24.0, h)
+        ctx.set_sommerfeld_method(mp.SOMM_INTERP)
+    else:
+        ctx.set_contour(nodes, 0.05, 32.0)
     return ctx
 
 
@@ -111,3 +116,16 @@ def test_matvec_at_its_budget():
     for prec, dt in ((0, np.complex128), (1, np.complex64)):
         x = (rng.standard_normal((203, 33)) + 1j * rng.standard_normal((203, 33))).astype(dt)
         assert np.array_equal(tight.apply(prec, x), free.apply(prec, x))
+
+
+@pytest.mark.parametrize("n,p,most", [(300, 8, 116960836), (300, 16, 158043460)])
+def test_interpolated_batch_memory(n, p, most):
+    # four right-hand sides over the interpolated transforms: no more than their partials'
+    # earlier shape (blocks of four waves) held in all
+    import torch
+    ctx = _lattice(n, p, interp=True)
+    ctx.set_stream(torch.cuda.current_stream().cuda_stream)
+    x = torch.zeros(4, n, 2 * p + 1, dtype=torch.complex64, device="cuda")
+    ctx.apply_batch_dev(1, 4, x, torch.empty_like(x))
+    torch.cuda.synchronize()
+    assert ctx.memory()[0] <= most
