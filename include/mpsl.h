@@ -467,7 +467,8 @@ int mpsl_eval_field(mpsl_ctx *ctx, int n_rhs, const double *src_xy, const mpsl_c
  * input, HIP events on the context stream, each launch with the summation of
  * its partial slots) and keeps the fastest (a later candidate must be more
  * than 1 % faster, so near-ties keep the default); mpsl_set_tuning forces a choice
- * (chunks 0 = default).  Tuning is kept until changed; it never changes
+ * (chunks 0 = default).  mpsl_get_tuning reports 0 chunks while no geometry is
+ * set.  Tuning is kept until changed; it never changes
  * results beyond floating-point summation order. */
 int mpsl_autotune(mpsl_ctx *ctx, int prec);
 int mpsl_set_tuning(mpsl_ctx *ctx, int prec, int variant, int chunks);

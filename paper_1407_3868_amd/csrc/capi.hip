@@ -1150,7 +1150,7 @@ int mpsl_get_tuning(const mpsl_ctx *ctx, int prec, int *variant, int *chunks, do
   if (!ctx || (prec != MPSL_FP64 && prec != MPSL_FP32)) return MPSL_EINVAL;
   const auto &t = ctx->tune[prec == MPSL_FP64 ? 0 : 1];
   if (variant) *variant = t.variant >= 0 ? t.variant : mpsl::m2l_default_variant(ctx, prec);
-  if (chunks) *chunks = mpsl::chunks_m2l(ctx, prec);
+  if (chunks) *chunks = ctx->n > 0 ? mpsl::chunks_m2l(ctx, prec) : 0;  // the rule divides by the particles' blocks
   if (ms) *ms = t.ms;
   return MPSL_OK;
 }

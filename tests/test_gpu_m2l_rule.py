@@ -40,3 +40,17 @@ def test_sides(prec, p, n, nrhs, form):
     assert np.array_equal(y[None], y[form])
     for v in (0, 2, 3):
         assert rel_err(y[None], y[v]) < (2e-5 if prec else 1e-11), v
+
+
+def test_tuning_of_a_context_without_geometry():
+    # the form and the time are known, the chunk count is not: 0 (the rule used to divide by zero)
+    import paper_1407_3868_amd as mp
+    ctx = mp.Context(0)
+    for prec in (0, 1):
+        t = ctx.get_tuning(prec)
+        assert t["chunks"] == 0 and t["variant"] in (0, 1, 2, 3)
+    ctx.set_layers(6.0, 9.0, 12.0, 4.0)
+    ctx.set_scattering_matrix(4, 0.3, np.eye(9, dtype=complex))
+    assert ctx.get_tuning(0)["chunks"] == 0
+    ctx.set_geometry(np.array([[0.0, -2.0]]), np.zeros(1))
+    assert ctx.get_tuning(0)["chunks"] == 1 and ctx.get_tuning(1)["chunks"] == 1
