@@ -87,6 +87,7 @@ struct SommPlan {
   DBuf dir;         // int32[ndir][2]: contour node and coarse node of each direct node
   DBuf G;           // work [nrhs][2][nT][nc] in the matvec precision
   DBuf fblk;        // M2S interval-node blocks: (interval, first node)
+  bool sparse = false;  // the tiles of trow stand apart: no groups
   DBuf trow;        // int32[nrow][2]: tiles in row-major order (by y, then x) and their steps, in groups of four
   DBuf tgrp;        // double2[nrow / 4]: centre of each group's first tile
   DBuf Fx;          // double2[ns]: e^{i lam_q w}, the factor between horizontally adjacent tiles
