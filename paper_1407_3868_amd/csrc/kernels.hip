@@ -255,16 +255,17 @@ __global__ __launch_bounds__(256) void k_sum_parts(const cv_t<T> *part, int slot
 // per tile of 16 particles: all lanes sum the partials of the tile's
 // expansions (a contiguous range of 16 P entries; HBM-bound where the slots
 // are many) and rotate them into LDS as B[K = n'][N = particle]; wave w < MT
-// then
-// multiplies row tile w of the shared S (A[M = n][K = n'], zero-padded to
+// then multiplies row tile w of the shared S (A[M = n][K = n'], zero-padded to
 // 16 MT x KP) by B with 16x16x4 MFMA, the complex product as four real
 // chains (re += Sr Br - Si Bi, im += Sr Bi + Si Br); the result goes back
-// through LDS for coalesced stores.
+// through LDS for coalesced stores.  With more than kSapplyFew slots four lanes
+// sum an entry, in blocks of 512; else one, in blocks of 256 (the strides are
+// constants: read from the launch, they cost the step by itself 0.1 to 0.3 us).
 //   (MFMA operand layout: mfma4 in common.h.)
-constexpr int kSapplyThreads = 512;  // with more than 8 partials to sum; 256 else
+constexpr int kSapplyFew = 8;
 
-template <typename T, int p>
-__global__ __launch_bounds__(kSapplyThreads) void k_sapply(const cv_t<T> *__restrict__ x,
+template <typename T, int p, int nthr>
+__global__ __launch_bounds__(nthr) void k_sapply(const cv_t<T> *__restrict__ x,
                                                            const cv_t<T> *__restrict__ alpha, int slots,
                                                            const cv_t<T> *__restrict__ S,
                                                            const cv_t<T> *__restrict__ rot, int n,
@@ -286,7 +287,7 @@ __global__ __launch_bounds__(kSapplyThreads) void k_sapply(const cv_t<T> *__rest
   __shared__ int32_t tt[16];  // particle types of the tile (-1 past the end)
   const int tid = threadIdx.x;
   const int l0 = blockIdx.x * 16;
-  for (int i = tid; i < KP * 16; i += blockDim.x) {
+  for (int i = tid; i < KP * 16; i += nthr) {
     Bre[i / 16][i % 16] = 0;
     Bim[i / 16][i % 16] = 0;
   }
@@ -294,9 +295,8 @@ __global__ __launch_bounds__(kSapplyThreads) void k_sapply(const cv_t<T> *__rest
   __syncthreads();
   const int cnt = min(16, n - l0) * P;  // entries of the tile
   const int64_t base = static_cast<int64_t>(l0) * P;
-  const int nthr = blockDim.x;
   const int64_t len = static_cast<int64_t>(n) * P;
-  if (slots <= 8) {  // few slots: one lane per entry
+  if constexpr (nthr == 256) {  // few slots: one lane per entry
     for (int i = tid; i < cnt; i += nthr) {
       cx<T> s = ld<T>(alpha[base + i]);
 #pragma unroll 4
@@ -1211,7 +1211,6 @@ static int launch_sapply_t(mpsl_ctx *ctx, const void *x, const void *alpha, int 
   const auto *S = static_cast<const cv_t<T> *>(f64 ? ctx->S64.p : ctx->S32.p);
   const auto *rot = static_cast<const cv_t<T> *>(f64 ? ctx->gt.rot64.p : ctx->gt.rot32.p);
   const dim3 grid(cdiv(n, 16), nrhs);
-  const dim3 block(slots > 8 ? kSapplyThreads : 256);
   const auto *xx = static_cast<const cv_t<T> *>(x);
   const auto *aa = static_cast<const cv_t<T> *>(alpha);
   auto *yy = static_cast<cv_t<T> *>(y);
@@ -1221,7 +1220,14 @@ static int launch_sapply_t(mpsl_ctx *ctx, const void *x, const void *alpha, int 
   const int nt = typed ? ctx->n_types : 1;
   switch (ctx->p) {
 #define X(PP) \
-  case PP: hipLaunchKernelGGL((k_sapply<T, PP>), grid, block, 0, ctx->stream, xx, aa, slots, S, rot, n, yy, astride, ty, nt); break;
+  case PP:                                                                                                         \
+    if (slots > kSapplyFew)                                                                                        \
+      hipLaunchKernelGGL((k_sapply<T, PP, 512>), grid, dim3(512), 0, ctx->stream, xx, aa, slots, S, rot, n, yy,    \
+                         astride, ty, nt);                                                                         \
+    else                                                                                                           \
+      hipLaunchKernelGGL((k_sapply<T, PP, 256>), grid, dim3(256), 0, ctx->stream, xx, aa, slots, S, rot, n, yy,    \
+                         astride, ty, nt);                                                                         \
+    break;
     MPSL_P_CASES(X)
 #undef X
     default: return set_err(ctx, MPSL_EUNSUPPORTED, "expansion order outside 1..20");
