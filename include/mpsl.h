@@ -468,8 +468,10 @@ int mpsl_eval_field(mpsl_ctx *ctx, int n_rhs, const double *src_xy, const mpsl_c
  * its partial slots) and keeps the fastest (a later candidate must be more
  * than 1 % faster, so near-ties keep the default); mpsl_set_tuning forces a choice
  * (chunks 0 = default).  mpsl_get_tuning reports 0 chunks while no geometry is
- * set.  Tuning is kept until changed; it never changes
- * results beyond floating-point summation order. */
+ * set.  Tuning is kept until changed.  The variants form the same sums in
+ * different ways (0 and 1: complex multiply-adds; 2, 3: three real products for
+ * four in FP64, products of three-part bf16 operands in FP32), so results differ
+ * by rounding, within the error of the precision. */
 int mpsl_autotune(mpsl_ctx *ctx, int prec);
 int mpsl_set_tuning(mpsl_ctx *ctx, int prec, int variant, int chunks);
 int mpsl_get_tuning(const mpsl_ctx *ctx, int prec, int *variant, int *chunks, double *m2l_ms);

@@ -47,8 +47,8 @@ template <typename T> __host__ __device__ inline void cmac(cx<T> &acc, cx<T> a, 
 }
 
 // sin and cos of r, |r| <= pi / 4, by their Taylor series (terms up to r^9
-// and r^10 in FP32, r^17 and r^18 in FP64: the first term left out is below
-// 2e-10 and 1e-19 there).
+// and r^10 in FP32, r^17 and r^18 in FP64: the first term left out is at most
+// 1.8e-9 and 1.2e-10 in FP32, 8.4e-20 and 3.3e-21 in FP64).
 __device__ inline void sincos_quarter(float r, float &s, float &c) {
   const float r2 = r * r;
   s = r * (1.0f + r2 * (-1.0f / 6 + r2 * (1.0f / 120 + r2 * (-1.0f / 5040 + r2 * (1.0f / 362880)))));

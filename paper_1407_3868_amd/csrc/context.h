@@ -73,7 +73,7 @@ struct FmmStage {
 struct SommPlan {
   bool active = false;
   int nT = 0, nrow = 0, nc = 0, nint = 0, ndir = 0, nfb = 0;
-  double tile_w = 0.0, tile_h = 0.0, L_I = 0.0, d_dir = 0.0;
+  double tile_w = 0.0, L_I = 0.0, d_dir = 0.0;
   DBuf perm;        // int32[n]: particles ordered by tile
   DBuf tstart;      // int32[nT + 1]
   DBuf txy;         // double2[nT]: tile centres

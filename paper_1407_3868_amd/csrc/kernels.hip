@@ -939,7 +939,9 @@ int chunks_s2l(const mpsl_ctx *ctx, int nrhs, int prec) {
     const int tb = cdiv(ctx->n, 128) * nrhs;
     const int c0 = std::max(1, std::min(64, std::min(cdiv(1024, tb), 2 * ctx->somm.nc)));
     // fewer where the blocks (64 particles) would give some compute units a
-    // second one and others not (300 particles, FP64: 64 chunks 15.8 us, 51 12.9)
+    // second one and others not: with 256 units and one right-hand side that is
+    // 257 to 448 particles, where the cap of 64 chunks binds, and nowhere else
+    // (300 particles, FP64: 64 chunks 15.8 us, 51 12.9)
     const int64_t nb = static_cast<int64_t>(cdiv(ctx->n, 64)) * nrhs;
     return nb * c0 > ctx->n_cu && nb * c0 < 2 * ctx->n_cu ? static_cast<int>(ctx->n_cu / nb) : c0;
   }

@@ -743,7 +743,6 @@ int somm_build(mpsl_ctx *ctx) {
   const int64_t n = ctx->n;
   const int ns = ctx->ns, p = ctx->p, P = 2 * p + 1;
   pl.tile_w = kTileW;
-  pl.tile_h = kTileH;
   pl.L_I = kIntervalL;
   pl.d_dir = kDirect;
   // tiles of the particle bounding box
