@@ -867,7 +867,7 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs(const float2 *__re
 //
 // Bound by the matrix cores: 192 MFMAs of 16 cycles per pair and 64 right-hand
 // sides, where the FP32 form above needs 3 MT KP NT / 4 = 168 of 32.4 (p = 12).
-// 64 right-hand sides, 2000 particles, p = 12: 10.9 -> 7.9 ms (MFMAs 65 % of the
+// 64 right-hand sides, 2000 particles, p = 12: 10.9 -> 8.0 ms (MFMAs 66 % of the
 // cycles), the batch's error against 64 bits 1.3e-6 -> 1.0e-6.
 template <int p>
 __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs_bf(const float2 *__restrict__ pairs,
