@@ -51,6 +51,8 @@ template <typename T> __device__ inline cx<double> up(cx<T> v) { return {static_
 // (walked down the tile columns, which are a few tiles high, nearly every tile
 // took an exponential: 5003 particles, 570 tiles, 30528 nodes, FP32, with the
 // direct nodes 212 us, now 129; 300 particles, 36 tiles, FP64: 25 -> 14).
+// The multiplies are in FP64 in both precisions: in FP32 their roundings doubled
+// the error of M2S over gaps of four tiles (1.6 -> 3.0e-7), at the same speed.
 // Each lane sums per step in the matvec precision and across steps in FP64;
 // the four row groups are added at the end.
 //
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(64 * kSiFineSplit) void k_si_fine(
 #pragma unroll
   for (int ks = 0; ks < 6; ++ks) bl[ks] = qv ? static_cast<T>(Lw[static_cast<int64_t>(q) * kSommNc + 4 * ks + g]) : T(0);
   const double lr = lam[q].x, li = lam[q].y, gr = g2[q].x, gi = g2[q].y;
-  const cx<T> Fd = cexpT<T>(li * tile_w, -lr * tile_w);
+  const cx<double> Fd = cexpT<double>(li * tile_w, -lr * tile_w);
   const cv_t<T> *Gs = G + ((static_cast<int64_t>(rr) * 2 + s) * nT) * nc + c0 + g;
   const int sa = slot_of_row<T>(r);
   struct Ops {
@@ -179,14 +181,15 @@ __global__ __launch_bounds__(64 * kSiFineSplit) void k_si_fine(
         }
       } else {
         const double yy = s == 0 ? cu.tc.y : -(d + cu.tc.y);
-        cx<T> E = cexpT<T>(li * cu.tc.x + gr * yy, -lr * cu.tc.x + gi * yy);
-        cmac(blk, E, mk<T>(hr[0], hi[0]));
+        const cx<T> E0 = cexpT<T>(li * cu.tc.x + gr * yy, -lr * cu.tc.x + gi * yy);
+        cx<double> E = up<T>(E0);
+        cmac(blk, E0, mk<T>(hr[0], hi[0]));
 #pragma unroll
         for (int j = 1; j < 4; ++j) {
           if (tj[j] >= 0) {
             E = E * Fd;
             for (int v = 1; v < kj[j]; ++v) E = E * Fd;
-            cmac(blk, E, mk<T>(hr[j], hi[j]));
+            cmac(blk, cvt<T>(E), mk<T>(hr[j], hi[j]));
           }
         }
       }

@@ -53,3 +53,34 @@ def test_tiles_apart(name):
         torch.cuda.synchronize()
         assert rel_err(sd.cpu().numpy(), m2s) < tol, prec
         assert rel_err(ad.cpu().numpy(), s2l) < tol, prec
+
+
+@pytest.mark.parametrize("step", [1, 2, 4])
+def test_fp32_error_over_gaps(step):
+    # M2S in FP32 against FP64, tiles `step` widths apart.  Per tile and node two FP32
+    # exponentials (reduced argument, series, exp of the real part, product: 1.7 unit roundoffs
+    # root mean square each), the tile's sum and the product with it, 1 each: 3.5 with a
+    # quarter to spare; nothing more for the steps from tile to tile
+    import torch
+    wl = make_workload("s150p12")
+    p, d, n = 8, 12.0, 64
+    i = np.arange(n)
+    xy = np.stack([8.0 * step * i + 0.5, -0.5 * d + 0.3 * np.sin(i)], axis=1)
+    rng = np.random.default_rng(8)
+    ctx = mp.Context(0)
+    ctx.set_sommerfeld_method(mp.SOMM_INTERP)
+    ctx.set_layers(wl.k1, wl.k2, wl.k3, d)
+    ctx.set_scattering_matrix(p, 0.2, np.eye(2 * p + 1, dtype=np.complex128))
+    ctx.set_geometry(xy, np.zeros(n))
+    ctx.set_contour(4096, 1e-3, 32.0)
+    ctx.set_stream(torch.cuda.current_stream().cuda_stream)
+    decay = 0.3 ** np.abs(np.arange(-p, p + 1))
+    x = (rng.standard_normal((n, 2 * p + 1)) + 1j * rng.standard_normal((n, 2 * p + 1))) * decay
+    x = torch.from_numpy(x.astype(np.complex64)).cuda()
+    s64 = torch.zeros(2, 4096, dtype=torch.complex128, device="cuda")
+    s32 = torch.zeros_like(s64)
+    ctx.m2s_dev(0, x.to(torch.complex128), s64)
+    ctx.m2s_dev(1, x, s32)
+    torch.cuda.synchronize()
+    err = rel_err(s32.cpu().numpy(), s64.cpu().numpy())
+    assert err <= 3.5 * 2.0**-24, err
