@@ -202,37 +202,39 @@ __global__ void k_s2l_coef(const double2 *__restrict__ sigma, const double2 *__r
 // takes the slots g, g + 4, ..., eight loads in flight, and the four sums are
 // added by two exchanges (a fixed order; every lane of the four gets the sum).
 // One lane per entry left small problems waiting for their loads in series
-// (1000 particles, p = 12, FP64: 25000 lanes, 384 slots, 35 us).
+// (1000 particles, p = 12, FP64: 25000 lanes, 384 slots, 35 us).  FP32 slots
+// are added in pairs and the pairs in FP64: 8 % off the error of FP32 matvecs of 50
+// to 3000 particles on average; every slot converted cost the matvec of 100
+// particles 1.2 us, pairs nothing that shows.
 constexpr int kSumLanes = 4;
 template <typename T>
 __device__ __forceinline__ cx<T> sum_slots(const cv_t<T> *part, int slots, int64_t len, int g) {
-  T re[2] = {0, 0}, im[2] = {0, 0};
+  double re[2] = {0, 0}, im[2] = {0, 0};
+  auto add = [&](const cv_t<T> *v) {
+#pragma unroll
+    for (int u = 0; u < 8; u += 2) {
+      re[u / 2 & 1] += v[u].x + v[u + 1].x;
+      im[u / 2 & 1] += v[u].y + v[u + 1].y;
+    }
+  };
   int c = g;
   for (; c + 7 * kSumLanes < slots; c += 8 * kSumLanes) {
     cv_t<T> v[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) v[u] = part[(c + u * kSumLanes) * len];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      re[u & 1] += v[u].x;
-      im[u & 1] += v[u].y;
-    }
+    add(v);
   }
   cv_t<T> v[8];
 #pragma unroll
   for (int u = 0; u < 8; ++u) v[u] = c + u * kSumLanes < slots ? part[(c + u * kSumLanes) * len] : st(mk<T>(0, 0));
-#pragma unroll
-  for (int u = 0; u < 8; ++u) {
-    re[u & 1] += v[u].x;
-    im[u & 1] += v[u].y;
-  }
-  cx<T> s = mk<T>(re[0] + re[1], im[0] + im[1]);
+  add(v);
+  cx<double> s = mk(re[0] + re[1], im[0] + im[1]);
 #pragma unroll
   for (int o = 1; o < kSumLanes; o <<= 1) {
     s.re += __shfl_xor(s.re, o);
     s.im += __shfl_xor(s.im, o);
   }
-  return s;
+  return mk<T>(static_cast<T>(s.re), static_cast<T>(s.im));
 }
 
 // out[i] = sum_c part[c len + i] (out may be the first slot), for right-hand side
@@ -296,12 +298,16 @@ __global__ __launch_bounds__(nthr) void k_sapply(const cv_t<T> *__restrict__ x,
   const int cnt = min(16, n - l0) * P;  // entries of the tile
   const int64_t base = static_cast<int64_t>(l0) * P;
   const int64_t len = static_cast<int64_t>(n) * P;
-  if constexpr (nthr == 256) {  // few slots: one lane per entry
+  if constexpr (nthr == 256) {  // few slots: one lane per entry, summed in FP64
     for (int i = tid; i < cnt; i += nthr) {
-      cx<T> s = ld<T>(alpha[base + i]);
+      cx<double> z = mk<double>(alpha[base + i].x, alpha[base + i].y);
 #pragma unroll 4
-      for (int c = 1; c < slots; ++c) s = s + ld<T>(alpha[c * len + base + i]);
-      s = s * ld<T>(rot[base + i]);
+      for (int c = 1; c < slots; ++c) {
+        const cv_t<T> v = alpha[c * len + base + i];
+        z.re += v.x;
+        z.im += v.y;
+      }
+      const cx<T> s = mk<T>(static_cast<T>(z.re), static_cast<T>(z.im)) * ld<T>(rot[base + i]);
       Bre[i % P][i / P] = s.re;
       Bim[i % P][i / P] = s.im;
     }

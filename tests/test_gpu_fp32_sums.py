@@ -1,0 +1,58 @@
+"""Sums of the FP32 far field over the partial slots.
+
+Particles in free space (three equal layers), S = 1: y - x is the summed M2L.
+"""
+import numpy as np
+import pytest
+
+import paper_1407_3868_amd as mp
+
+pytestmark = pytest.mark.gpu
+
+
+def _context(xy, p):
+    import torch
+    ctx = mp.Context(0)
+    ctx.set_layers(1.0, 1.0, 1.0, 200.0)
+    ctx.set_scattering_matrix(p, 0.01, np.eye(2 * p + 1, dtype=complex))
+    ctx.set_geometry(xy, np.zeros(len(xy)))
+    ctx.set_contour(128, 0.1, 4.0)
+    ctx.set_stream(torch.cuda.current_stream().cuda_stream)
+    return ctx
+
+
+def _apply(ctx, prec, x):
+    import torch
+    y = torch.empty_like(x)
+    ctx.apply_batch_dev(prec, x.shape[0], x, y)
+    torch.cuda.synchronize()
+    return y
+
+
+def _m2l(ctx, prec, x):
+    import torch
+    y = torch.empty_like(x)
+    ctx.m2l_dev(prec, x, y)
+    torch.cuda.synchronize()
+    return y
+
+
+@pytest.mark.parametrize("n", [7, 12, 33, 41])
+def test_slots_that_cancel(n):
+    # one source per slot; those of coefficients 1 and -1 at the same distance
+    # cancel at order 0 of the last particle, and what a third adds stays.  In
+    # unit roundoffs: H_0 1, S and the rotation a few; 16 with room.
+    import torch
+    p, small = 1, 2.0**-13
+    a, b, c = (0, 1, 2) if n < 33 else (0, 8, 16)
+    xy = np.stack([5.0 + 1.5 * np.arange(n), np.full(n, -100.0)], 1)
+    xy[a, 0], xy[b, 0], xy[c, 0], xy[n - 1, 0] = 1.0, 1.5, -1.0, 0.0
+    ctx = _context(xy, p)
+    ctx.set_tuning(1, 0, n)
+    x = np.zeros((n, 2 * p + 1), np.complex128)
+    x[a, p], x[b, p], x[c, p] = 1.0, small, -1.0
+    x64 = torch.from_numpy(x).cuda()
+    x32 = x64.to(torch.complex64)
+    ref = complex(_m2l(ctx, 0, x64)[n - 1, p])
+    for got in (complex(_m2l(ctx, 1, x32)[n - 1, p]), -complex(_apply(ctx, 1, x32[None])[0, n - 1, p])):
+        assert abs(got - ref) <= 16 * 2.0**-24 * abs(ref), (got, ref)
