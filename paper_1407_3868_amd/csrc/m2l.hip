@@ -480,6 +480,15 @@ __global__ __launch_bounds__(64 * kM2lBfWaves, NT == 1 ? 3 : 2) void k_m2l_bf(co
   constexpr int NM = (P - (VROW ? 1 : 0) + 7) / 8;  // octets of q <= 0 that the matrix rows need
   constexpr int NO = NJ > NM ? NJ : NM;
   static_assert(NO <= 4, "octets");
+  // The matrix cores' sums are rounded downwards, so the errors of one source
+  // after another add up (700 particles, p = 4: 1.2 times the vector form's error).
+  // With one row block, where that shows most, each octet's products start from
+  // zero, are added to acc rounded to nearest, and every second group of four
+  // sources is multiplied negated (0.9 times; 2000 particles, p = 8: 145 -> 150 us
+  // a matvec; with two blocks the registers spill, 12 % at p = 10).  With more, every
+  // second batch is negated (p = 10: 1.02 -> 1.00 times; at p = 16, with its row on the
+  // vector units, 5 % slower and left out).
+  constexpr bool RN = NB == 1, ALT = RN || !VROW;
   constexpr int SB = kM2lBfBatch;
   typedef float v4 __attribute__((ext_vector_type(4)));
   __shared__ __align__(16) __bf16 sa[SB * kBfSrc];
@@ -567,6 +576,7 @@ __global__ __launch_bounds__(64 * kM2lBfWaves, NT == 1 ? 3 : 2) void k_m2l_bf(co
     // stages its share of the batch and meets the barriers, but multiplies nothing
     for (int g0 = 0; g0 < sb && lt0 < n; g0 += 4) {
       const int s = g0 + g;  // this lane's source within the batch
+      const float sg = ALT && (RN ? g0 / 4 : mb / SB) & 1 ? -1.f : 1.f, down = sg * sc.down;
       float2 pc[NT][4];
 #pragma unroll
       for (int tt = 0; tt < NT; ++tt)
@@ -582,7 +592,8 @@ __global__ __launch_bounds__(64 * kM2lBfWaves, NT == 1 ? 3 : 2) void k_m2l_bf(co
       };
 #pragma unroll
       for (int tt = 0; tt < NT; ++tt) {
-        cx<float> hp = sc.down * ld<float>(pc[tt][0]), hc = sc.down * ld<float>(pc[tt][1]);
+        if (VROW && ALT) zc[tt] = sg * zc[tt];
+        cx<float> hp = down * ld<float>(pc[tt][0]), hc = down * ld<float>(pc[tt][1]);
         const cx<float> t = ld<float>(pc[tt][2]);
         cx<float> tq = t;
         const float tz = pc[tt][3].x;
@@ -599,15 +610,24 @@ __global__ __launch_bounds__(64 * kM2lBfWaves, NT == 1 ? 3 : 2) void k_m2l_bf(co
                 ar[b][k] = frag(k, 0, t0 + 2 * b);
                 ai[b][k] = frag(k, 1, t0 + 2 * b);
               }
+            v4 sum[NB][4];
+#pragma unroll
+            for (int b = b0; b < b1; ++b)
+#pragma unroll
+              for (int k = 0; k < 4; ++k) sum[b][k] = RN ? v4{0, 0, 0, 0} : acc[tt][b][k];
 #pragma unroll
             for (int x = 0; x < 6; ++x)
 #pragma unroll
               for (int b = b0; b < b1; ++b) {
-                acc[tt][b][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar[b][ka[x]], br.v[kb[x]], acc[tt][b][0], 0, 0, 0);
-                acc[tt][b][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ai[b][ka[x]], bi.v[kb[x]], acc[tt][b][1], 0, 0, 0);
-                acc[tt][b][2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar[b][ka[x]], bi.v[kb[x]], acc[tt][b][2], 0, 0, 0);
-                acc[tt][b][3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ai[b][ka[x]], br.v[kb[x]], acc[tt][b][3], 0, 0, 0);
+                sum[b][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar[b][ka[x]], br.v[kb[x]], sum[b][0], 0, 0, 0);
+                sum[b][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ai[b][ka[x]], bi.v[kb[x]], sum[b][1], 0, 0, 0);
+                sum[b][2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar[b][ka[x]], bi.v[kb[x]], sum[b][2], 0, 0, 0);
+                sum[b][3] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ai[b][ka[x]], br.v[kb[x]], sum[b][3], 0, 0, 0);
               }
+#pragma unroll
+            for (int b = b0; b < b1; ++b)
+#pragma unroll
+              for (int k = 0; k < 4; ++k) acc[tt][b][k] = RN ? acc[tt][b][k] + sg * sum[b][k] : sum[b][k];
           }
         };
         float pr[8], pi[8], nr[8], ni[8];  // h_{8j+1 ..} and h_{-8j-7 ..}
@@ -663,16 +683,18 @@ __global__ __launch_bounds__(64 * kM2lBfWaves, NT == 1 ? 3 : 2) void k_m2l_bf(co
         if constexpr (NO > 1) octet(std::integral_constant<int, 1>{});
         if constexpr (NO > 2) octet(std::integral_constant<int, 2>{});
         if constexpr (NO > 3) octet(std::integral_constant<int, 3>{});
+        if (VROW && ALT) zc[tt] = sg * zc[tt];
       }
     }
     // the batch's products into the running sums (rounded to nearest)
+    const float bsg = ALT && !RN && (mb / SB) & 1 ? -1.f : 1.f;
 #pragma unroll
     for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
       for (int b = 0; b < NB; ++b) {
         v4 *s = &run[w][(tt * NB + b) * 2][lane];
-        s[0] = s[0] + (acc[tt][b][0] - acc[tt][b][1]);
-        s[64] = s[64] + (acc[tt][b][2] + acc[tt][b][3]);
+        s[0] = s[0] + bsg * (acc[tt][b][0] - acc[tt][b][1]);
+        s[64] = s[64] + bsg * (acc[tt][b][2] + acc[tt][b][3]);
 #pragma unroll
         for (int k = 0; k < 4; ++k) acc[tt][b][k] = v4{0, 0, 0, 0};
       }
