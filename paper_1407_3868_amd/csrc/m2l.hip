@@ -736,6 +736,11 @@ __global__ __launch_bounds__(64 * kM2lBfWaves, NT == 1 ? 3 : 2) void k_m2l_bf(co
 // [m][nu][r] (r fastest, zero rows and columns as padding), is staged per
 // source in LDS for all waves of the block, double-buffered: the next
 // source's loads are in flight during the current source's MFMAs.
+//
+// The error grows with the length of the sums.  With one row block (p <= 7) they
+// are added to running ones every `run` batches, so that a chunk's length
+// costs no accuracy (700 particles, 16 right-hand sides, p = 1: 1.08 -> 0.99 times
+// the error of twelve chunks; every batch would cost 4 %).
 constexpr int kMrhsWaves = 8;
 constexpr int kMrhsBatch = 8;
 
@@ -743,11 +748,12 @@ template <int p>
 __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs(const float2 *__restrict__ pairs,
                                                               const float2 *__restrict__ bt,
                                                               float2 *__restrict__ part, int n, int chunk_len,
-                                                              int nrhs, int r_pad, int64_t pstride) {
+                                                              int nrhs, int r_pad, int64_t pstride, int run) {
   constexpr int P = 2 * p + 1;
   constexpr int MT = (P + 15) / 16;
   constexpr int KP = (P + 3) / 4 * 4;
   constexpr int NT = 4;                      // 64 right-hand sides per block
+  constexpr bool RUN = MT == 1;              // running sums: registers for them
   constexpr int OFF = 16 * MT - 1;           // H index of q = k - row is q + OFF
   constexpr int HQ = KP + OFF;               // zero outside |q| <= 2p
   constexpr int BE = KP * 64;                // B entries of one source
@@ -767,6 +773,9 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs(const float2 *__re
   for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
     for (int ct = 0; ct < NT; ++ct) P1[mt][ct] = P2[mt][ct] = P3[mt][ct] = v4{0, 0, 0, 0};
+  v4 Sr[NT], Si[NT];  // RUN: running sums
+#pragma unroll
+  for (int ct = 0; ct < NT; ++ct) Sr[ct] = Si[ct] = v4{0, 0, 0, 0};
   const int col = lane & 15, kq = lane >> 4;
   // B of source m: rows k (zero rows k >= P in bt), 64 right-hand sides
   float2 pre[BL];
@@ -845,6 +854,16 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs(const float2 *__re
         }
       }
     }
+    if constexpr (RUN) {
+      if (((mb - m0) / kMrhsBatch + 1) % run == 0 || mb + kMrhsBatch >= m1) {
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) {
+          Sr[ct] += P1[0][ct] - P2[0][ct];
+          Si[ct] += P3[0][ct] - P1[0][ct] - P2[0][ct];
+          P1[0][ct] = P2[0][ct] = P3[0][ct] = v4{0, 0, 0, 0};
+        }
+      }
+    }
     __syncthreads();
   }
   if (l >= n) return;
@@ -860,7 +879,8 @@ __global__ __launch_bounds__(64 * kMrhsWaves) void k_m2l_mrhs(const float2 *__re
         const int r = r0 + ct * 16 + col;
         const float p1 = P1[mt][ct][j], p2 = P2[mt][ct][j], p3 = P3[mt][ct][j];
         if (row < P && r < nrhs)
-          part[r * pstride + c * len + static_cast<int64_t>(l) * P + row] = make_float2(p1 - p2, p3 - p1 - p2);
+          part[r * pstride + c * len + static_cast<int64_t>(l) * P + row] =
+              RUN ? make_float2(Sr[ct][j], Si[ct][j]) : make_float2(p1 - p2, p3 - p1 - p2);
       }
 }
 
@@ -1315,21 +1335,34 @@ static int mrhs_resident(int p) {
   return nb;
 }
 
-// Source chunks: all blocks carry the same work, so of the counts up to about
-// 1024 blocks' worth the smallest whose blocks fill the last round of the
-// resident slots within 3 % of the best (2000 particles, 64 right-hand sides,
-// 250 blocks: one chunk at p = 12, one block per unit; at p = 4, two per unit, two
-// chunks, 2959 us where one took 3306 and five 2951).
+// The most source chunks: about 1024 blocks' worth, of no less than one batch.
+static int mrhs_most(const mpsl_ctx *ctx, int nrhs) {
+  const int64_t blocks = static_cast<int64_t>(cdiv(ctx->n, kMrhsWaves)) * cdiv(nrhs, 64);
+  return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(cdiv(1024, blocks), cdiv(ctx->n, kMrhsBatch))));
+}
+
+// Source chunks: all blocks carry the same work, so of the counts up to mrhs_most
+// one whose blocks fill the last round of the resident slots within 3 % of the
+// best.  Of these the bf16 form, one block per unit, takes the smallest (2000
+// particles, 64 right-hand sides, p = 12, 250 blocks: one chunk), the FP32 form
+// the largest: shorter sums, and blocks that the units finish at different
+// times (p = 4, two per unit, 16 right-hand sides: four chunks 2.65 ms, two 2.70,
+// five, which leave the third round half empty, 2.64; 500 particles: eight
+// 0.206, sixteen 0.221).
 int chunks_m2l_mrhs(const mpsl_ctx *ctx, int nrhs) {
   const int64_t blocks = static_cast<int64_t>(cdiv(ctx->n, kMrhsWaves)) * cdiv(nrhs, 64);
-  const int hi = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(cdiv(1024, blocks), cdiv(ctx->n, kMrhsBatch))));
+  const int hi = mrhs_most(ctx, nrhs);
   const int64_t slots = static_cast<int64_t>(std::max(1, ctx->n_cu)) * mrhs_resident(ctx->p);
   auto cost = [&](int c) { return static_cast<double>(cdiv(blocks * c, slots)) / c; };
   double best = 1e300;
   for (int c = 1; c <= hi; ++c) best = std::min(best, cost(c));
-  for (int c = 1; c <= hi; ++c)
-    if (cost(c) <= 1.03 * best) return c;
-  return hi;
+  int pick = hi;
+  for (int c = hi; c >= 1; --c)
+    if (cost(c) <= 1.03 * best) {
+      pick = c;
+      if (!mrhs_bf(ctx->p)) break;
+    }
+  return pick;
 }
 
 int launch_m2l_mrhs(mpsl_ctx *ctx, const void *beta, void *part, int chunks, int nrhs, int64_t pstride) {
@@ -1353,6 +1386,8 @@ int launch_m2l_mrhs(mpsl_ctx *ctx, const void *beta, void *part, int chunks, int
   }
   LAUNCH_CHECK(ctx);
   const int chunk_len = cdiv(n, chunks);
+  // as many batches as the shortest chunk has
+  const int run = std::max(1, cdiv(n, mrhs_most(ctx, nrhs)) / kMrhsBatch);
   const dim3 grid(cdiv(n, kMrhsWaves), chunks, r_pad / 64);
   const auto *pairs = static_cast<const float2 *>(ctx->gt.pair32.p);
   const auto *bt = static_cast<const float2 *>(ctx->bt.p);
@@ -1365,7 +1400,7 @@ int launch_m2l_mrhs(mpsl_ctx *ctx, const void *beta, void *part, int chunks, int
                          chunk_len, nrhs, r_pad, pstride);                                                         \
     else                                                                                                           \
       hipLaunchKernelGGL((k_m2l_mrhs<PP>), grid, dim3(64 * kMrhsWaves), 0, ctx->stream, pairs, bt, pp, n,          \
-                         chunk_len, nrhs, r_pad, pstride);                                                         \
+                         chunk_len, nrhs, r_pad, pstride, run);                                                    \
     break;
     MPSL_P_CASES(X)
 #undef X
