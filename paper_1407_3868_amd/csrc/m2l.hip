@@ -482,13 +482,13 @@ __global__ __launch_bounds__(64 * kM2lBfWaves, NT == 1 ? 3 : 2) void k_m2l_bf(co
   static_assert(NO <= 4, "octets");
   // The matrix cores' sums are rounded downwards, so the errors of one source
   // after another add up (700 particles, p = 4: 1.2 times the vector form's error).
-  // With one row block, where that shows most, each octet's products start from
-  // zero, are added to acc rounded to nearest, and every second group of four
-  // sources is multiplied negated (0.9 times; 2000 particles, p = 8: 145 -> 150 us
-  // a matvec; with two blocks the registers spill, 12 % at p = 10).  With more, every
-  // second batch is negated (p = 10: 1.02 -> 1.00 times; at p = 16, with its row on the
-  // vector units, 5 % slower and left out).
-  constexpr bool RN = NB == 1, ALT = RN || !VROW;
+  // Up to p = 7, where that shows most, each octet's products start from zero, are
+  // added to acc rounded to nearest, and every second group of four sources is
+  // multiplied negated (0.9 times; 2000 particles, p = 7: 127 -> 131 us a matvec;
+  // with two row blocks the registers spill, 12 % at p = 10).  From p = 9 every
+  // second batch is negated (p = 10: 1.02 -> 1.00 times); with a row on the vector
+  // units neither (p = 8: 1.02 times with or without; p = 16: 5 % slower).
+  constexpr bool RN = NB == 1 && !VROW, ALT = !VROW;
   constexpr int SB = kM2lBfBatch;
   typedef float v4 __attribute__((ext_vector_type(4)));
   __shared__ __align__(16) __bf16 sa[SB * kBfSrc];
@@ -592,7 +592,6 @@ __global__ __launch_bounds__(64 * kM2lBfWaves, NT == 1 ? 3 : 2) void k_m2l_bf(co
       };
 #pragma unroll
       for (int tt = 0; tt < NT; ++tt) {
-        if (VROW && ALT) zc[tt] = sg * zc[tt];
         cx<float> hp = down * ld<float>(pc[tt][0]), hc = down * ld<float>(pc[tt][1]);
         const cx<float> t = ld<float>(pc[tt][2]);
         cx<float> tq = t;
@@ -683,7 +682,6 @@ __global__ __launch_bounds__(64 * kM2lBfWaves, NT == 1 ? 3 : 2) void k_m2l_bf(co
         if constexpr (NO > 1) octet(std::integral_constant<int, 1>{});
         if constexpr (NO > 2) octet(std::integral_constant<int, 2>{});
         if constexpr (NO > 3) octet(std::integral_constant<int, 3>{});
-        if (VROW && ALT) zc[tt] = sg * zc[tt];
       }
     }
     // the batch's products into the running sums (rounded to nearest)
